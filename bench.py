@@ -3,8 +3,7 @@
 One *step* = one full plain-method solve of the four-object packing skeleton
 (4 pick-place steps, 84-D particles, 60 robot spheres, 8 obstacle boxes,
 pairwise goal cost): uniform initialization of 8192 particles on the GPU,
-then 500 fused cost + gradient + Adam + mask iterations replayed as one
-captured graph.  The metric is particle-iterations per second.
+then 500 fused cost + gradient + Adam + mask iterations.  The metric is particle-iterations per second.
 
 Also reported on the same JSON line:
   * time to the first satisfying particle of the plain method (fixed
@@ -207,7 +206,7 @@ def config1_line(args, dev, q):
         fz = grasp_frozen(prob, dev)
         adam = default_adam(n)
         gp.seed_uniform(1000 + s, X, M, V, n)
-        gp.optimize(X, M, V, n, 0, iters, adam, frozen=fz, cost=cost, mask=mask, first_sat=flag)   # captures
+        gp.optimize(X, M, V, n, 0, iters, adam, frozen=fz, cost=cost, mask=mask, first_sat=flag)   # warm-up
         gp.seed_uniform(1000 + s, X, M, V, n)
         flag.fill_(INT32_MAX)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -357,11 +356,11 @@ def compositional(args, dev, n, q):
             gp = GpuProblem(prob, dev)
             ci = CompositionalInit(prob, n_sub, dev)
             seed = 4242 + s
-            ci.solve(gp, n_part, seed, max_iters=100, first_check=50, chunk=50, refine_budget=20)   # captures
+            ci.solve(gp, n_part, seed, max_iters=100, first_check=50, chunk=50, refine_budget=20)   # warm-up
             r = ci.solve(gp, n_part, seed, max_iters=args.sampling_iters, first_check=50, chunk=50,
                          refine_budget=args.eval_budget)
             rs = sampling_solve(ci, gp, n_part, seed, ik_iters=args.sampling_iters, max_rounds=args.sampling_rounds)
-            plain_solve(gp, n_part, 20, seed=seed, adam=default_adam(n_part))                       # captures
+            plain_solve(gp, n_part, 20, seed=seed, adam=default_adam(n_part))                       # warm-up
             rp = plain_solve(gp, n_part, args.plain_budget, seed=seed, adam=default_adam(n_part))
             comp.append(r)
             samp.append(rs)
@@ -466,7 +465,7 @@ def al_heldout(args, dev, n, lg, prop=None, self_collision=False, budget=None, m
         if prop is not None:
             pre = prop.prepare(prob)
             init = lambda X, M, V: prop.seed(pre, seed, X, M, V, n)  # noqa: E731
-        al_solve(gp, n, 20, seed, rho=args.al_rho, outer=args.al_outer, init=init, mode=mode)   # captures graphs
+        al_solve(gp, n, 20, seed, rho=args.al_rho, outer=args.al_outer, init=init, mode=mode)   # warm-up
         r = al_solve(gp, n, budget, seed, rho=args.al_rho, outer=args.al_outer, init=init, mode=mode)
         first.append(r.first_sat_iter)
         times.append(r.time_to_first_s)
@@ -810,7 +809,7 @@ def main():
         for mode in ("persistent", "per_skeleton"):
             gb.set_tuning(bsplit, bwg, mode == "persistent")
             gb.seed(2)
-            gb.optimize(0, bi, badam)          # capture + warm-up
+            gb.optimize(0, bi, badam)          # warm-up
             torch.cuda.synchronize()
             gb.seed(3)
             e0.record(stream)
@@ -820,7 +819,7 @@ def main():
             res_b[mode] = e0.elapsed_time(e1) / 1e3
         batch = {
             "workload": "64 skeletons, 1-6 pick-place steps (uniform), 512-8192 particles each (log-uniform, "
-                        f"{gb.particles} in total), 2-12 obstacle boxes, {bi} Adam iterations, one captured graph",
+                        f"{gb.particles} in total), 2-12 obstacle boxes, {bi} Adam iterations",
             "split": bsplit, "workgroups": bwg,
             "persistent_s": res_b["persistent"],
             "per_skeleton_launches_s": res_b["per_skeleton"],

@@ -34,7 +34,7 @@
  *  - A particle with a non-finite coordinate gets a non-finite cost, mask 0,
  *    and is left untouched by Adam; this is not an error.
  *  - A problem handle is immutable after creation except for its tuning
- *    choice and graph cache; calls on one handle must not overlap in time
+ *    choice and ct_optimize's workspace; calls on one handle must not overlap in time
  *    from several host threads.  Separate handles are independent.
  */
 #ifndef CUTAMP_H
@@ -163,8 +163,7 @@ int ct_problem_create(const ct_robot *robot, const ct_scene *scene, const ct_ske
                       ct_problem **out);
 
 /* Release a handle and its device tables (NULL is accepted).  Waits for the
- * device to finish (launches on any stream may still read the tables) and
- * for every replay of the handle's captured loop before releasing it. */
+ * device to finish (launches on any stream may still read the tables). */
 int ct_problem_destroy(ct_problem *problem);
 
 /*
@@ -268,16 +267,18 @@ int ct_step(const ct_problem *problem, float *X, float *M, float *V, int64_t n, 
             int32_t *first_sat, void *stream);
 
 /*
- * `iters` fused steps with updates t0+1 .. t0+iters, launched as one HIP
- * graph.  The graph is captured on first use for an argument set (t0 is not
- * part of it: the update number comes from a device counter the call sets
- * before launching) and cached in the handle; a call with other arguments
- * re-captures, which may allocate graph resources.  cost / mask hold the
+ * `iters` fused steps with updates t0+1 .. t0+iters, in one kernel launch
+ * for every 64 of them: a workgroup keeps its particles on chip from the
+ * first update of a launch to the last.  cost / mask hold the
  * values of the last executed step; first_sat as in ct_step.  With
  * stop_at_first != 0 (first_sat required), a step whose predecessors already
  * produced a satisfying particle does nothing, so a whole iteration budget
  * can be enqueued at once and still stops at the first solution
- * (Sec. IV-B, stopping criterion); in that mode a particle the step finds
+ * (Sec. IV-B, stopping criterion).  This mode keeps copies of the state in a
+ * workspace of the handle (3 dim ld floats, allocated on the first such call
+ * and when a larger one needs more); on a stream that is being captured, or
+ * when the memory cannot be had, it launches one iteration at a time instead,
+ * with the same results.  In that mode a particle the step finds
  * satisfying is not updated, so after the stop the rows of X whose mask is 1
  * are exactly the satisfying iterates (the other rows took that step's
  * update).
@@ -357,8 +358,8 @@ int ct_feasibility_noalloc(const ct_problem *problem, const float *terms, int64_
  * caller keeps it alive and may rewrite it between calls) instead of the
  * fixed lambda_c of Eq. (2).  The call's ld must equal this ld
  * (CT_ERR_INVALID_ARG otherwise).  Terms, masks and first_sat stay
- * unweighted.  W = NULL restores lambda.  A change drops the captured loop of
- * ct_optimize.  The many-skeleton calls (ct_batch_*) always use lambda.
+ * unweighted.  W = NULL restores lambda.  The many-skeleton calls (ct_batch_*)
+ * always use lambda.
  *
  * ct_al_update is the method-of-multipliers step between inner solves: with
  * terms [n_terms][ld] as written by ct_cost and multipliers mu [n_terms][ld]
@@ -404,7 +405,7 @@ int ct_gather_block(const float *Xs, int64_t lds, int32_t rows, int64_t n_src, c
  * Many skeletons at once (the backtracking search of Alg. 1 keeps several
  * skeletons' particle batches alive; each is optimized on its own batch mean,
  * Eq. (4)).  A batch binds problems of any lengths (K = 1..6) to their
- * caller-owned particle buffers; one optimizer iteration of every skeleton is
+ * caller-owned particle buffers; the iterations of every skeleton are
  * then ONE persistent kernel launch in which a fixed set of workgroups pull
  * (skeleton, particle tile) items from a device queue, largest first.
  * ------------------------------------------------------------------------ */
@@ -437,8 +438,7 @@ int ct_batch_set_tuning(ct_batch *batch, int32_t split, int32_t workgroups, int3
  * (adam->grad_scale is ignored: each skeleton uses 1/n[s]). */
 int ct_batch_step(ct_batch *batch, int64_t t, const ct_adam *adam, void *stream);
 
-/* iters batch steps t0+1 .. t0+iters as one captured graph (cached like
- * ct_optimize's). */
+/* iters batch steps t0+1 .. t0+iters, one launch for every 64 of them. */
 int ct_batch_optimize(ct_batch *batch, int64_t t0, int32_t iters, const ct_adam *adam, void *stream);
 
 /*

@@ -96,9 +96,6 @@ __global__ __launch_bounds__(256) void adam_kernel(int D, float* __restrict__ X,
     }
 }
 
-// Device counter of applied Adam updates, set before a captured loop.
-__global__ void counter_set_kernel(int32_t* c, int32_t v) { *c = v; }
-
 // Tolerance of constraint term c (per step: Kin position / rotation at the
 // pick and at the place, grasp box, placement, two joint-limit terms, three
 // collision terms; then the motion-collision terms, then the self-collision

@@ -80,6 +80,16 @@ struct Tables {
 // particles per workgroup tile for a K-step skeleton and SPLIT lanes per slot
 __host__ __device__ constexpr int tile_particles(int K, int SPLIT) { return WG / (2 * K * SPLIT); }
 
+// Stop-at-first of the fused step: on = leave after the first iteration that
+// finds a satisfying particle; with several iterations per launch, the copies
+// [D][ld] of the state the launch started from, the iterations each workgroup
+// ran, and whether this is the second launch that runs tiles back from them.
+struct StopArgs {
+    int32_t on, redo;
+    float *Xb, *Mb, *Vb;
+    int32_t* ran;
+};
+
 // One skeleton of a batch, as the persistent kernel sees it.
 struct BatchSkel {
     const Tables* T;

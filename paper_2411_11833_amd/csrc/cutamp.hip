@@ -1,6 +1,6 @@
 // Host side of the C ABI declared in include/cutamp.h: descriptor validation,
 // construction of the device tables of one skeleton's CSP, kernel dispatch,
-// the graph-captured optimization loop and the split autotuner.
+// the optimization loop and the split autotuner.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,22 +18,10 @@
 
 namespace {
 
-struct GraphKey {
-    float *X = nullptr, *M = nullptr, *V = nullptr, *cost = nullptr;
-    uint8_t* mask = nullptr;
-    int32_t* first_sat = nullptr;
-    const uint8_t* frozen = nullptr;
-    const float* wts = nullptr;
-    int64_t n = -1, ld = -1;
-    int32_t iters = -1, split = -1, stop = -1;
-    float lr = 0, b1 = 0, b2 = 0, eps = 0, gs = 0;
-    bool operator==(const GraphKey& o) const {
-        return X == o.X && M == o.M && V == o.V && cost == o.cost && mask == o.mask &&
-               first_sat == o.first_sat && frozen == o.frozen && wts == o.wts && n == o.n && ld == o.ld &&
-               iters == o.iters && split == o.split && stop == o.stop && lr == o.lr && b1 == o.b1 && b2 == o.b2 &&
-               eps == o.eps && gs == o.gs;
-    }
-};
+// Iterations of one launch of the fused step at most: bounds a launch's time
+// (an iteration of 200,000 particles takes about a millisecond) at a
+// staging cost of a few microseconds every 64 iterations.
+constexpr int32_t MAX_LAUNCH_ITERS = 64;
 
 }  // namespace
 
@@ -42,13 +30,14 @@ struct ct_problem {
     ct::Tables* d = nullptr;    // device copy
     int K = 0, D = 0, n_terms = 0, nc = 0;
     int split = 0;              // 0 = default
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    hipStream_t capture_stream = nullptr;
-    hipEvent_t replayed = nullptr;   // recorded after every replay of gexec on the caller's stream
-    int32_t* t_dev = nullptr;   // two-slot device counter of applied updates for captured loops,
-                                // followed by n_constraint per-constraint counts (feasibility)
-    GraphKey key;
+    int32_t* counts = nullptr;  // n_constraint per-constraint counts (feasibility)
+    // stop-at-first workspace of ct_optimize (copies of X, M, V and the
+    // iterations each workgroup ran), grown on demand; `ws_used` is recorded
+    // after every use, so that a call on another stream waits for it
+    void* ws = nullptr;
+    size_t ws_bytes = 0;
+    hipEvent_t ws_used = nullptr;
+    hipStream_t ws_stream = nullptr;
     const float* wts = nullptr;  // per-particle term weights (ct_set_term_weights), or null
     int64_t wts_ld = 0;
 };
@@ -183,20 +172,6 @@ int run_pk(const ct_problem* P, int mode, const PkArgs& a, hipStream_t st, int s
     PkFn f = pick_kernel(split ? split : effective_split(P, a.n), P->K, mode, P->h.self_on || b.wts);
     if (!f) return CT_ERR_UNSUPPORTED;
     return err_of(f(P->d, b, st));
-}
-
-// A graph exec must not be destroyed while a replay of it is still queued or
-// running: its kernel-argument storage is released with it, and the queued
-// dispatches (and a profiler's completion handler reading them) would then
-// touch freed memory.  Every replay records `replayed` on the caller's
-// stream; dropping the graph first waits for that event.
-void drop_graph(ct_problem* P) {
-    if (P->gexec && P->replayed) hipEventSynchronize(P->replayed);
-    if (P->gexec) hipGraphExecDestroy(P->gexec);
-    if (P->graph) hipGraphDestroy(P->graph);
-    P->gexec = nullptr;
-    P->graph = nullptr;
-    P->key = GraphKey();
 }
 
 }  // namespace
@@ -391,14 +366,14 @@ extern "C" int ct_problem_create(const ct_robot* robot, const ct_scene* scene, c
         delete P;
         return CT_ERR_ALLOC;
     }
-    if (hipMalloc(&P->t_dev, (2 + (size_t)P->nc) * sizeof(int32_t)) != hipSuccess) {
+    if (hipMalloc(&P->counts, (size_t)P->nc * sizeof(int32_t)) != hipSuccess) {
         hipFree(P->d);
         delete P;
         return CT_ERR_ALLOC;
     }
     if (hipMemcpy(P->d, &T, sizeof(ct::Tables), hipMemcpyHostToDevice) != hipSuccess) {
         hipFree(P->d);
-        hipFree(P->t_dev);
+        hipFree(P->counts);
         delete P;
         return CT_ERR_DEVICE;
     }
@@ -410,11 +385,10 @@ extern "C" int ct_problem_destroy(ct_problem* P) {
     if (!P) return CT_OK;
     // eager launches on any stream may still read the tables and counters
     hipDeviceSynchronize();
-    drop_graph(P);
-    if (P->replayed) hipEventDestroy(P->replayed);
-    if (P->capture_stream) hipStreamDestroy(P->capture_stream);
+    if (P->ws_used) hipEventDestroy(P->ws_used);
+    if (P->ws) hipFree(P->ws);
     if (P->d) hipFree(P->d);
-    if (P->t_dev) hipFree(P->t_dev);
+    if (P->counts) hipFree(P->counts);
     delete P;
     return CT_OK;
 }
@@ -422,7 +396,6 @@ extern "C" int ct_problem_destroy(ct_problem* P) {
 extern "C" int ct_set_term_weights(ct_problem* P, const float* W, int64_t ld) {
     if (!P) return CT_ERR_INVALID_ARG;
     if (W && (ld <= 0 || !good_layout(W, 1, ld))) return CT_ERR_INVALID_ARG;
-    if (W != P->wts || (W && ld != P->wts_ld)) drop_graph(P);   // a captured loop holds the old pointer
     P->wts = W;
     P->wts_ld = W ? ld : 0;
     return CT_OK;
@@ -460,7 +433,7 @@ extern "C" int ct_feasibility(const ct_problem* P, const float* terms, int64_t n
     if (n < 0 || ld < n || ld % 64 != 0 || (n > 0 && !terms)) return CT_ERR_INVALID_ARG;
     if (terms && ((uintptr_t)terms % 256)) return CT_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    int32_t* cnt = counts ? counts : P->t_dev + 2;
+    int32_t* cnt = counts ? counts : P->counts;
     hipLaunchKernelGGL(ct::feas_count_kernel, dim3(P->nc), dim3(256), 0, st, P->d, terms, n, ld, cnt);
     if (H) hipLaunchKernelGGL(ct::feas_h_kernel, dim3(1), dim3(64), 0, st, cnt, P->nc, penalty, H);
     return err_of(hipGetLastError());
@@ -628,8 +601,7 @@ extern "C" int ct_adam_apply(const ct_problem* P, float* X, float* M, float* V, 
 namespace {
 int step_impl(const ct_problem* P, float* X, float* M, float* V, int64_t n, int64_t ld, int64_t t,
               const ct_adam* adam, const uint8_t* frozen, float* cost, uint8_t* mask, int32_t* first_sat,
-              hipStream_t st, int split, const int32_t* t_in = nullptr, int32_t* t_out = nullptr,
-              int32_t stop_at_first = 0) {
+              hipStream_t st, int split, int32_t iters = 1, const ct::StopArgs& stop = {}) {
     PkArgs a{};
     a.X = X;
     a.M = M;
@@ -642,10 +614,54 @@ int step_impl(const ct_problem* P, float* X, float* M, float* V, int64_t n, int6
     a.ld = ld;
     a.a = adam_args(adam);
     a.t = (int32_t)t;
-    a.t_in = t_in;
-    a.t_out = t_out;
-    a.stop_at_first = stop_at_first;
+    a.iters = iters;
+    a.stop = stop;
     return run_pk(P, ct::MODE_STEP, a, st, split);
+}
+
+// Workspace of a stop-at-first launch over several iterations: the copies of
+// X, M and V and one counter per workgroup, ready for use on `st`.  False
+// when it cannot be had (`st` is being captured, so a replay could overlap
+// another user of the buffer, or device memory is short): the caller then
+// launches one iteration at a time, which needs none.
+bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t st, ct::StopArgs& out) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+    const size_t state = (size_t)P->D * (size_t)ld;
+    const int64_t per = ct::tile_particles(P->K, split);
+    const size_t bytes = (3 * state + (size_t)((n + per - 1) / per)) * sizeof(float);
+    if (!P->ws_used && hipEventCreateWithFlags(&P->ws_used, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        P->ws_used = nullptr;
+        return false;
+    }
+    if (bytes > P->ws_bytes) {
+        if (P->ws) {
+            hipEventSynchronize(P->ws_used);
+            hipFree(P->ws);
+        }
+        P->ws = nullptr;
+        P->ws_bytes = 0;
+        if (hipMalloc(&P->ws, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            P->ws = nullptr;
+            return false;
+        }
+        P->ws_bytes = bytes;
+    } else if (st != P->ws_stream && hipStreamWaitEvent(st, P->ws_used, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    P->ws_stream = st;
+    out.Xb = (float*)P->ws;
+    out.Mb = out.Xb + state;
+    out.Vb = out.Mb + state;
+    out.ran = (int32_t*)(out.Vb + state);
+    return true;
 }
 
 bool valid_step_args(const ct_problem* P, float* X, float* M, float* V, int64_t n, int64_t ld,
@@ -671,56 +687,29 @@ extern "C" int ct_optimize(ct_problem* P, float* X, float* M, float* V, int64_t 
         return CT_ERR_INVALID_ARG;
     if (stop_at_first && !first_sat) return CT_ERR_INVALID_ARG;
     if (n == 0 || iters == 0) return CT_OK;
-    GraphKey key;
-    key.X = X; key.M = M; key.V = V; key.cost = cost; key.mask = mask; key.first_sat = first_sat;
-    key.frozen = frozen; key.wts = P->wts; key.n = n; key.ld = ld; key.iters = iters;
-    key.split = effective_split(P, n);
-    key.stop = stop_at_first ? 1 : 0;
-    key.lr = adam->lr; key.b1 = adam->beta1; key.b2 = adam->beta2; key.eps = adam->eps;
-    key.gs = adam->grad_scale;
-    if (!(P->gexec && P->key == key)) {
-        // capture iters steps; the update number comes from the device
-        // counter (two slots used alternately), so one graph serves every t0
-        drop_graph(P);
-        if (!P->capture_stream && hipStreamCreateWithFlags(&P->capture_stream, hipStreamNonBlocking) != hipSuccess)
-            return CT_ERR_DEVICE;
-        if (hipStreamBeginCapture(P->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
-            return CT_ERR_DEVICE;
-        int rc = CT_OK;
-        for (int32_t it = 0; it < iters && rc == CT_OK; ++it) {
-            rc = step_impl(P, X, M, V, n, ld, 0, adam, frozen, cost, mask, first_sat, P->capture_stream, key.split,
-                           P->t_dev + (it & 1), P->t_dev + ((it + 1) & 1), key.stop);
+    hipStream_t st = (hipStream_t)stream;
+    const int split = effective_split(P, n);
+    int32_t per = MAX_LAUNCH_ITERS;
+    ct::StopArgs stop{};
+    stop.on = stop_at_first ? 1 : 0;
+    if (stop.on && iters > 1 && !stop_workspace(P, n, ld, split, st, stop)) per = 1;
+    int rc = CT_OK;
+    for (int32_t done = 0; done < iters && rc == CT_OK;) {
+        const int32_t c = std::min(per, iters - done);
+        rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, stop);
+        if (rc == CT_OK && stop.Xb) {
+            ct::StopArgs redo = stop;
+            redo.redo = 1;
+            rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, redo);
         }
-        hipGraph_t g = nullptr;
-        const hipError_t ec = hipStreamEndCapture(P->capture_stream, &g);
-        if (rc != CT_OK || ec != hipSuccess || !g) {
-            if (g) hipGraphDestroy(g);
-            return rc != CT_OK ? rc : CT_ERR_DEVICE;
-        }
-        hipGraphExec_t ge = nullptr;
-        if (hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess) {
-            hipGraphDestroy(g);
-            return CT_ERR_DEVICE;
-        }
-        P->graph = g;
-        P->gexec = ge;
-        P->key = key;
+        done += c;
     }
-    if (!P->replayed && hipEventCreateWithFlags(&P->replayed, hipEventDisableTiming) != hipSuccess) {
-        P->replayed = nullptr;
-        return CT_ERR_DEVICE;
-    }
-    hipLaunchKernelGGL(ct::counter_set_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, P->t_dev, (int32_t)t0);
-    int rc = err_of(hipGetLastError());
-    if (rc != CT_OK) return rc;
-    rc = err_of(hipGraphLaunch(P->gexec, (hipStream_t)stream));
-    if (rc != CT_OK) return rc;
-    return err_of(hipEventRecord(P->replayed, (hipStream_t)stream));
+    if (stop.Xb && hipEventRecord(P->ws_used, st) != hipSuccess && rc == CT_OK) rc = CT_ERR_DEVICE;
+    return rc;
 }
 
 extern "C" int ct_set_split(ct_problem* P, int32_t split) {
     if (!P || !(split == 0 || split == 1 || split == 2 || split == 4)) return CT_ERR_INVALID_ARG;
-    if (split != P->split) drop_graph(P);
     P->split = split;
     return CT_OK;
 }
@@ -793,27 +782,11 @@ struct ct_batch {
     int2* d_items = nullptr;
     int32_t n_items = 0;
     int32_t* d_queue = nullptr;   // [0] next item, [1] workgroups done
-    int32_t* t_dev = nullptr;     // two-slot step counter
     int split = 0, workgroups = 0, persistent = 1;
     int n_cu = 256;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    hipStream_t capture_stream = nullptr;
-    hipEvent_t replayed = nullptr;   // recorded after every replay of gexec (see drop_graph)
-    int32_t g_iters = -1, g_split = -1, g_wg = -1, g_pers = -1;
-    float g_lr = 0, g_b1 = 0, g_b2 = 0, g_eps = 0;
 };
 
 namespace {
-
-void batch_drop_graph(ct_batch* B) {
-    if (B->gexec && B->replayed) hipEventSynchronize(B->replayed);
-    if (B->gexec) hipGraphExecDestroy(B->gexec);
-    if (B->graph) hipGraphDestroy(B->graph);
-    B->gexec = nullptr;
-    B->graph = nullptr;
-    B->g_iters = -1;
-}
 
 int batch_split(const ct_batch* B) { return B->split ? B->split : 1; }
 int batch_workgroups(const ct_batch* B) { return B->workgroups ? B->workgroups : 2 * B->n_cu; }
@@ -843,7 +816,7 @@ int batch_build_items(ct_batch* B) {
     return CT_OK;
 }
 
-int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, const int32_t* t_in, int32_t* t_out, hipStream_t st) {
+int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, int32_t iters, hipStream_t st) {
     AdamArgs a = adam_args(adam);
     if (B->persistent) {
         if (B->n_items == 0) return CT_OK;
@@ -859,19 +832,16 @@ int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, const int32_t* t_i
         g.n_workgroups = batch_workgroups(B);
         g.a = a;
         g.t = t;
-        g.t_in = t_in;
-        g.t_out = t_out;
+        g.iters = iters;
         return err_of(f(g, st));
     }
-    // reference point: one ordinary launch per skeleton; every launch reads
-    // the same counter slot and only the last writes the next one
+    // reference point: one ordinary launch per skeleton
     for (size_t s = 0; s < B->probs.size(); ++s) {
         const ct::BatchSkel& k = B->skels[s];
         if (k.n == 0) continue;
         PkArgs p{};
         p.X = k.X; p.M = k.M; p.V = k.V; p.cost = k.cost; p.mask = k.mask; p.first_sat = k.first_sat;
-        p.frozen = k.frozen; p.n = k.n; p.ld = k.ld; p.a = a; p.a.gs = k.gscale; p.t = t; p.t_in = t_in;
-        p.t_out = (s + 1 == B->probs.size()) ? t_out : nullptr;
+        p.frozen = k.frozen; p.n = k.n; p.ld = k.ld; p.a = a; p.a.gs = k.gscale; p.t = t; p.iters = iters;
         const int rc = run_pk(B->probs[s], ct::MODE_STEP, p, st, batch_split(B), false);
         if (rc != CT_OK) return rc;
     }
@@ -915,8 +885,7 @@ extern "C" int ct_batch_create(int32_t count, ct_problem* const* problems, float
     }
     int rc = CT_OK;
     if (hipMalloc(&B->d_skels, count * sizeof(ct::BatchSkel)) != hipSuccess ||
-        hipMalloc(&B->d_queue, 2 * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(&B->t_dev, 2 * sizeof(int32_t)) != hipSuccess)
+        hipMalloc(&B->d_queue, 2 * sizeof(int32_t)) != hipSuccess)
         rc = CT_ERR_ALLOC;
     if (rc == CT_OK && hipMemcpy(B->d_skels, B->skels.data(), count * sizeof(ct::BatchSkel),
                                  hipMemcpyHostToDevice) != hipSuccess)
@@ -934,13 +903,9 @@ extern "C" int ct_batch_create(int32_t count, ct_problem* const* problems, float
 extern "C" int ct_batch_destroy(ct_batch* B) {
     if (!B) return CT_OK;
     hipDeviceSynchronize();   // eager launches may still read the work list and queue
-    batch_drop_graph(B);
-    if (B->replayed) hipEventDestroy(B->replayed);
-    if (B->capture_stream) hipStreamDestroy(B->capture_stream);
     if (B->d_skels) hipFree(B->d_skels);
     if (B->d_items) hipFree(B->d_items);
     if (B->d_queue) hipFree(B->d_queue);
-    if (B->t_dev) hipFree(B->t_dev);
     delete B;
     return CT_OK;
 }
@@ -951,59 +916,21 @@ extern "C" int ct_batch_set_tuning(ct_batch* B, int32_t split, int32_t workgroup
     B->split = split;
     B->workgroups = workgroups;
     B->persistent = persistent ? 1 : 0;
-    batch_drop_graph(B);
     return rebuild ? batch_build_items(B) : CT_OK;
 }
 
 extern "C" int ct_batch_step(ct_batch* B, int64_t t, const ct_adam* adam, void* stream) {
     if (!B || t < 1 || t > INT32_MAX || !valid_adam(adam)) return CT_ERR_INVALID_ARG;
-    return batch_launch(B, adam, (int32_t)t, nullptr, nullptr, (hipStream_t)stream);
+    return batch_launch(B, adam, (int32_t)t, 1, (hipStream_t)stream);
 }
 
 extern "C" int ct_batch_optimize(ct_batch* B, int64_t t0, int32_t iters, const ct_adam* adam, void* stream) {
     if (!B || t0 < 0 || iters < 0 || t0 + iters > INT32_MAX || !valid_adam(adam)) return CT_ERR_INVALID_ARG;
-    if (iters == 0) return CT_OK;
-    const bool same = B->gexec && B->g_iters == iters && B->g_split == batch_split(B) &&
-                      B->g_wg == batch_workgroups(B) && B->g_pers == B->persistent && B->g_lr == adam->lr &&
-                      B->g_b1 == adam->beta1 && B->g_b2 == adam->beta2 && B->g_eps == adam->eps;
-    if (!same) {
-        batch_drop_graph(B);
-        if (!B->capture_stream && hipStreamCreateWithFlags(&B->capture_stream, hipStreamNonBlocking) != hipSuccess)
-            return CT_ERR_DEVICE;
-        if (hipStreamBeginCapture(B->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
-            return CT_ERR_DEVICE;
-        int rc = CT_OK;
-        for (int32_t it = 0; it < iters && rc == CT_OK; ++it)
-            rc = batch_launch(B, adam, 0, B->t_dev + (it & 1), B->t_dev + ((it + 1) & 1), B->capture_stream);
-        hipGraph_t g = nullptr;
-        const hipError_t ec = hipStreamEndCapture(B->capture_stream, &g);
-        if (rc != CT_OK || ec != hipSuccess || !g) {
-            if (g) hipGraphDestroy(g);
-            return rc != CT_OK ? rc : CT_ERR_DEVICE;
-        }
-        hipGraphExec_t ge = nullptr;
-        if (hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess) {
-            hipGraphDestroy(g);
-            return CT_ERR_DEVICE;
-        }
-        B->graph = g;
-        B->gexec = ge;
-        B->g_iters = iters;
-        B->g_split = batch_split(B);
-        B->g_wg = batch_workgroups(B);
-        B->g_pers = B->persistent;
-        B->g_lr = adam->lr; B->g_b1 = adam->beta1; B->g_b2 = adam->beta2; B->g_eps = adam->eps;
-    }
-    if (!B->replayed && hipEventCreateWithFlags(&B->replayed, hipEventDisableTiming) != hipSuccess) {
-        B->replayed = nullptr;
-        return CT_ERR_DEVICE;
-    }
-    hipLaunchKernelGGL(ct::counter_set_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, B->t_dev, (int32_t)t0);
-    int rc = err_of(hipGetLastError());
-    if (rc != CT_OK) return rc;
-    rc = err_of(hipGraphLaunch(B->gexec, (hipStream_t)stream));
-    if (rc != CT_OK) return rc;
-    return err_of(hipEventRecord(B->replayed, (hipStream_t)stream));
+    int rc = CT_OK;
+    for (int64_t done = 0; done < iters && rc == CT_OK; done += MAX_LAUNCH_ITERS)
+        rc = batch_launch(B, adam, (int32_t)(t0 + done + 1), (int32_t)std::min<int64_t>(MAX_LAUNCH_ITERS, iters - done),
+                          (hipStream_t)stream);
+    return rc;
 }
 
 extern "C" int ct_batch_autotune(ct_batch* B, int32_t* chosen, void* stream) {
@@ -1019,9 +946,9 @@ extern "C" int ct_batch_autotune(ct_batch* B, int32_t* chosen, void* stream) {
         for (int per_cu : {1, 2, 3, 4}) {
             rc = ct_batch_set_tuning(B, split, per_cu * B->n_cu, 1);
             if (rc != CT_OK) break;
-            for (int w = 0; w < 2 && rc == CT_OK; ++w) rc = batch_launch(B, &adam, 1, nullptr, nullptr, st);
+            for (int w = 0; w < 2 && rc == CT_OK; ++w) rc = batch_launch(B, &adam, 1, 1, st);
             hipEventRecord(e0, st);
-            for (int r = 0; r < 5 && rc == CT_OK; ++r) rc = batch_launch(B, &adam, 2 + r, nullptr, nullptr, st);
+            for (int r = 0; r < 5 && rc == CT_OK; ++r) rc = batch_launch(B, &adam, 2 + r, 1, st);
             hipEventRecord(e1, st);
             if (rc != CT_OK) break;
             if (hipEventSynchronize(e1) != hipSuccess) { rc = CT_ERR_DEVICE; break; }

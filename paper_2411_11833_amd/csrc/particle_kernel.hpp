@@ -1067,6 +1067,7 @@ struct TileSmem {
     int okp[128 / SPLIT];
     float4 osl[CT_MAX_STEPS * CT_MAX_OBJ_SPHERES];
     int any_sat;
+    int halt;
 };
 
 // What one tile reads and writes (one skeleton's buffers).
@@ -1080,14 +1081,25 @@ struct TileIO {
     int64_t n, ld;
     float gscale;
     const float* wts;   // per-particle term weights [n_terms][ld] (extended kernels), or null
-    int keep_sat = 0;   // stop-at-first: a satisfying particle is not updated, so X keeps it
+    // stop-at-first: a satisfying particle is not updated, so X keeps it, and a
+    // tile leaves its iteration loop after a step that found one
+    int stop = 0;
+    float *Xb = nullptr, *Mb = nullptr, *Vb = nullptr;   // copies of the state the launch started from, or null
+    int redo = 0;   // start from those copies, run every iteration, report nothing
     int32_t* hits = nullptr;   // cost mode: touching sphere-box pairs per particle, or null
 };
 
 
+// The fused step runs `iters` updates t, t + 1, ... of the tile: particles are
+// independent of each other (Eq. 4 is a mean, Adam is per coordinate), so X,
+// M and V stay in LDS from the first update to the last and cross HBM once
+// per launch, and no tile waits for another between iterations.  One launch
+// per iteration paid the staging, the store, a launch gap and the slowest
+// tile's tail every time.  cost and mask are those of the last iteration.
+// Returns the number of iterations run (stop-at-first may leave early).
 template <int KT, int SPLIT, int MODE, bool EXT>
-__device__ __forceinline__ void run_tile(const TileIO& io, int64_t p0, TileSmem<SPLIT>& sm, float lr, float b1,
-                                         float b2, float eps, int32_t t) {
+__device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<SPLIT>& sm, float lr, float b1,
+                                        float b2, float eps, int32_t t, int iters) {
     const Tables* __restrict__ T = io.T;
     const int K = KT ? KT : T->K;
     const int SLOTS = 2 * K;
@@ -1097,7 +1109,6 @@ __device__ __forceinline__ void run_tile(const TileIO& io, int64_t p0, TileSmem<
     const int NP = 18 + 3 * K;
     const int64_t n = io.n, ld = io.ld;
     const int tid = threadIdx.x;
-    const int32_t iter = t - 1;
 
     // phase 0: stage this tile's particles (coalesced along particles) and,
     // for the fused step, their Adam moments and the frozen flags; the
@@ -1117,8 +1128,13 @@ __device__ __forceinline__ void run_tile(const TileIO& io, int64_t p0, TileSmem<
             xv[u] = mv[u] = vv[u] = 0.f;
             if (idx < D * P && i < n) {
                 const int64_t a = d * ld + i;
-                xv[u] = io.X[a];
-                if (MV) { mv[u] = io.M[a]; vv[u] = io.V[a]; }
+                if (MV && io.redo) {
+                    xv[u] = io.Xb[a]; mv[u] = io.Mb[a]; vv[u] = io.Vb[a];
+                } else {
+                    xv[u] = io.X[a];
+                    if (MV) { mv[u] = io.M[a]; vv[u] = io.V[a]; }
+                    if (MV && io.Xb) { io.Xb[a] = xv[u]; io.Mb[a] = mv[u]; io.Vb[a] = vv[u]; }
+                }
             }
         }
         if (MV && tid < D) sm.frz[tid] = io.frozen ? io.frozen[tid] : 0;
@@ -1135,162 +1151,216 @@ __device__ __forceinline__ void run_tile(const TileIO& io, int64_t p0, TileSmem<
         sm.osl[idx] = T->os[idx / CT_MAX_OBJ_SPHERES][idx % CT_MAX_OBJ_SPHERES];
     for (int idx = tid; idx < T->link_start[9]; idx += WG) sm.rs[idx] = T->rs[idx];
     if (tid < T->n_static) sm.sbx[tid] = T->sbox[tid];
-    if (tid == 0) sm.any_sat = 0;
-    __syncthreads();
-    for (int idx = tid; idx < K * P; idx += WG) {
-        const int j = idx / P, p = idx - j * P;
-        const float* col = sm.xs + p;
-        float sj, cj;
-        sincosf(col[(CT_STEP_DIM * j + 20) * P], &sj, &cj);
-        sm.plc[idx] = make_float4(col[(CT_STEP_DIM * j + 18) * P], col[(CT_STEP_DIM * j + 19) * P], cj, sj);
+    if (tid == 0) {
+        sm.any_sat = 0;
+        sm.halt = 0;
     }
     __syncthreads();
 
-    // phase 1: every lane evaluates its slot.  Lanes are slot-major (the SPLIT
-    // lanes of a slot adjacent, then the tile's particles, then the slots), so
-    // a wave serves one or two slots of many particles: the same step and kind
-    // of configuration, hence uniform branches and coherent box masks.
-    {
-        const int si = tid % SPLIT, rest = tid / SPLIT;
-        const int slot = rest / P, p = rest - slot * P;
-        if (slot < SLOTS) {
-            const int64_t i = p0 + p;
-            const bool wt = (MODE == MODE_COST) && io.terms != nullptr && i < n;
-            const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(T, sm.xs + p, P, sm.plc + p, sm.osl, sm.rs, sm.sbx, K, slot, si,
-                                                     sm.part + (size_t)((p * SLOTS + slot) * SPLIT + si) * NP,
-                                                     io.terms, ld, i, wt, i < n ? io.wts : nullptr);
-            if (si == 0) {
-                sm.cpart[p * SLOTS + slot] = o.cost;
-                sm.tpart[p * SLOTS + slot] = o.traj;
-                sm.flg[p * SLOTS + slot] = o.flags;
-                if (MODE == MODE_COST) sm.hpart[p * SLOTS + slot] = o.hits;
-            }
+    int done = 0;
+    bool reported = false;
+    float J = 0.f;   // cost and mask of the iteration (lanes tid < P)
+    int m = 0;
+    for (;;) {
+        const int32_t tn = t + done, iter = tn - 1;   // update number of this iteration, its 0-based index
+        const bool last = MODE != MODE_STEP || done + 1 == iters;
+        // stop-at-first: an earlier iteration of another tile found a particle
+        if (MODE == MODE_STEP && io.stop && tid == 0)
+            sm.halt = __hip_atomic_load(io.first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < iter ? 1 : 0;
+        for (int idx = tid; idx < K * P; idx += WG) {
+            const int j = idx / P, p = idx - j * P;
+            const float* col = sm.xs + p;
+            float sj, cj;
+            sincosf(col[(CT_STEP_DIM * j + 20) * P], &sj, &cj);
+            sm.plc[idx] = make_float4(col[(CT_STEP_DIM * j + 18) * P], col[(CT_STEP_DIM * j + 19) * P], cj, sj);
         }
-    }
-    __syncthreads();
+        __syncthreads();
+        if (MODE == MODE_STEP && sm.halt) break;   // workgroup-uniform
 
-    // phase 1.5: per-particle cost, mask, update permission
-    if (tid < P) {
-        const int64_t i = p0 + tid;
-        float J = 0.f;
-        int m = 1, ok = 1;
-        for (int s = 0; s < SLOTS; ++s) {
-            J += sm.cpart[tid * SLOTS + s];
-            m &= sm.flg[tid * SLOTS + s] & 1;
-            ok &= (sm.flg[tid * SLOTS + s] >> 1) & 1;
-        }
-        ok &= __builtin_isfinite(J) ? 1 : 0;
-        m &= __builtin_isfinite(J) ? 1 : 0;
-        // the solution returned on stop is the satisfying iterate itself
-        // (the pre-update x the mask describes), so it keeps its value
-        sm.okp[tid] = ok & (io.keep_sat ? 1 - m : 1);
-        if (i < n) {
-            if (MODE == MODE_COST && io.terms && T->traj_term >= 0) {
-                float tl = 0.f;
-                for (int s = 0; s < SLOTS; ++s) tl += sm.tpart[tid * SLOTS + s];
-                io.terms[(int64_t)T->traj_term * ld + i] = tl;
+        // phase 1: every lane evaluates its slot.  Lanes are slot-major (the SPLIT
+        // lanes of a slot adjacent, then the tile's particles, then the slots), so
+        // a wave serves one or two slots of many particles: the same step and kind
+        // of configuration, hence uniform branches and coherent box masks.
+        {
+            const int si = tid % SPLIT, rest = tid / SPLIT;
+            const int slot = rest / P, p = rest - slot * P;
+            if (slot < SLOTS) {
+                const int64_t i = p0 + p;
+                const bool wt = (MODE == MODE_COST) && io.terms != nullptr && i < n;
+                const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(T, sm.xs + p, P, sm.plc + p, sm.osl, sm.rs, sm.sbx, K, slot, si,
+                                                         sm.part + (size_t)((p * SLOTS + slot) * SPLIT + si) * NP,
+                                                         io.terms, ld, i, wt, i < n ? io.wts : nullptr);
+                if (si == 0) {
+                    sm.cpart[p * SLOTS + slot] = o.cost;
+                    sm.tpart[p * SLOTS + slot] = o.traj;
+                    sm.flg[p * SLOTS + slot] = o.flags;
+                    if (MODE == MODE_COST) sm.hpart[p * SLOTS + slot] = o.hits;
+                }
             }
-            if (io.cost) io.cost[i] = J;
-            if (io.mask) io.mask[i] = (uint8_t)m;
-            if (MODE == MODE_COST && io.hits) {
-                int h = 0;
-                for (int s = 0; s < SLOTS; ++s) h += sm.hpart[tid * SLOTS + s];
-                io.hits[i] = h;
-            }
-            if (m) sm.any_sat = 1;
         }
-    }
-    __syncthreads();
-    if (io.first_sat && tid == 0 && sm.any_sat) atomicMin(io.first_sat, iter);
+        __syncthreads();
 
-    if (MODE != MODE_COST) {
-        // phase 2: sum each coordinate's partials over slots and split lanes
-        // in a fixed order, then write G or apply Adam in place
-        const float bc1 = 1.f - powf(b1, (float)t), bc2 = 1.f - powf(b2, (float)t);
-        const int FQ = 11 + 3 * K;   // foreign-configuration partials
+        // phase 1.5: per-particle cost, mask, update permission
+        if (tid < P) {
+            const int64_t i = p0 + tid;
+            int ok = 1;
+            J = 0.f;
+            m = 1;
+            for (int s = 0; s < SLOTS; ++s) {
+                J += sm.cpart[tid * SLOTS + s];
+                m &= sm.flg[tid * SLOTS + s] & 1;
+                ok &= (sm.flg[tid * SLOTS + s] >> 1) & 1;
+            }
+            ok &= __builtin_isfinite(J) ? 1 : 0;
+            m &= __builtin_isfinite(J) ? 1 : 0;
+            // the solution returned on stop is the satisfying iterate itself
+            // (the pre-update x the mask describes), so it keeps its value
+            sm.okp[tid] = ok & (io.stop ? 1 - m : 1);
+            if (i < n) {
+                if (MODE == MODE_COST && io.terms && T->traj_term >= 0) {
+                    float tl = 0.f;
+                    for (int s = 0; s < SLOTS; ++s) tl += sm.tpart[tid * SLOTS + s];
+                    io.terms[(int64_t)T->traj_term * ld + i] = tl;
+                }
+                if (MODE == MODE_COST && io.hits) {
+                    int h = 0;
+                    for (int s = 0; s < SLOTS; ++s) h += sm.hpart[tid * SLOTS + s];
+                    io.hits[i] = h;
+                }
+                if (m) sm.any_sat = 1;
+            }
+        }
+        __syncthreads();
+        const bool sat = sm.any_sat;   // workgroup-uniform; stays set: only the first iteration counts
+        if (sat && !reported && io.first_sat && !io.redo && tid == 0) atomicMin(io.first_sat, iter);
+        reported = reported || sat;
+
+        if (MODE != MODE_COST) {
+            // phase 2: sum each coordinate's partials over slots and split lanes
+            // in a fixed order, then write G or apply Adam in place
+            const float bc1 = 1.f - powf(b1, (float)tn), bc2 = 1.f - powf(b2, (float)tn);
+            const int FQ = 11 + 3 * K;   // foreign-configuration partials
+            for (int idx = tid; idx < D * P; idx += WG) {
+                const int d = idx / P, p = idx - d * P;
+                const int64_t i = p0 + p;
+                if (i >= n) continue;
+                const int k = d / CT_STEP_DIM, r = d - CT_STEP_DIM * k;
+                const float* pp = sm.part + (size_t)p * SLOTS * SPLIT * NP;
+                auto lane = [&](int slot, int si) { return pp + (size_t)(slot * SPLIT + si) * NP; };
+                float g = 0.f;
+#pragma unroll
+                for (int si = 0; si < SPLIT; ++si) {
+                    if (r < 7) {
+                        // q_grasp of step k: its slot, plus the start of the holding transition
+                        g += lane(2 * k, si)[r] + lane(2 * k + 1, si)[FQ + r];
+                    } else if (r < 14) {
+                        // q_place of step k: its slot, plus the start of the next free transition
+                        g += lane(2 * k + 1, si)[r - 7];
+                        if (k + 1 < K) g += lane(2 * k + 2, si)[FQ + (r - 7)];
+                    } else if (r < 18) {
+                        g += lane(2 * k, si)[7 + (r - 14)] + lane(2 * k + 1, si)[7 + (r - 14)];
+                    } else {
+                        for (int s = 0; s < SLOTS; ++s) g += lane(s, si)[11 + 3 * k + (r - 18)];
+                    }
+                }
+                if (MODE == MODE_GRAD) {
+                    const int64_t a = d * ld + i;
+                    io.G[a] = io.gw ? io.gw[i] * g : g;
+                } else if (!sm.frz[d]) {
+                    if (!sm.okp[p]) continue;
+                    const float gs = io.gscale * g;
+                    const float m1 = b1 * sm.ms[idx] + (1.f - b1) * gs;
+                    const float v1 = b2 * sm.vs[idx] + (1.f - b2) * gs * gs;
+                    const float mh = m1 / bc1, vh = v1 / bc2;
+                    sm.xs[idx] = sm.xs[idx] - lr * mh / (sqrtf(vh) + eps);
+                    sm.ms[idx] = m1;
+                    sm.vs[idx] = v1;
+                }
+            }
+        }
+        ++done;
+        if (last || (io.stop && sat && !io.redo)) break;   // workgroup-uniform
+        __syncthreads();
+    }
+
+    if (tid < P && p0 + tid < n) {
+        if (io.cost) io.cost[p0 + tid] = J;
+        if (io.mask) io.mask[p0 + tid] = (uint8_t)m;
+    }
+    if (MODE == MODE_STEP) {
+        // every entry by the lane that updated it in phase 2
         for (int idx = tid; idx < D * P; idx += WG) {
             const int d = idx / P, p = idx - d * P;
             const int64_t i = p0 + p;
-            if (i >= n) continue;
-            const int k = d / CT_STEP_DIM, r = d - CT_STEP_DIM * k;
-            const float* pp = sm.part + (size_t)p * SLOTS * SPLIT * NP;
-            auto lane = [&](int slot, int si) { return pp + (size_t)(slot * SPLIT + si) * NP; };
-            float g = 0.f;
-#pragma unroll
-            for (int si = 0; si < SPLIT; ++si) {
-                if (r < 7) {
-                    // q_grasp of step k: its slot, plus the start of the holding transition
-                    g += lane(2 * k, si)[r] + lane(2 * k + 1, si)[FQ + r];
-                } else if (r < 14) {
-                    // q_place of step k: its slot, plus the start of the next free transition
-                    g += lane(2 * k + 1, si)[r - 7];
-                    if (k + 1 < K) g += lane(2 * k + 2, si)[FQ + (r - 7)];
-                } else if (r < 18) {
-                    g += lane(2 * k, si)[7 + (r - 14)] + lane(2 * k + 1, si)[7 + (r - 14)];
-                } else {
-                    for (int s = 0; s < SLOTS; ++s) g += lane(s, si)[11 + 3 * k + (r - 18)];
-                }
-            }
+            if (i >= n || sm.frz[d]) continue;
             const int64_t a = d * ld + i;
-            if (MODE == MODE_GRAD) {
-                io.G[a] = io.gw ? io.gw[i] * g : g;
-            } else if (sm.okp[p] && !sm.frz[d]) {
-                const float gs = io.gscale * g;
-                const float m1 = b1 * sm.ms[idx] + (1.f - b1) * gs;
-                const float v1 = b2 * sm.vs[idx] + (1.f - b2) * gs * gs;
-                const float mh = m1 / bc1, vh = v1 / bc2;
-                io.X[a] = sm.xs[idx] - lr * mh / (sqrtf(vh) + eps);
-                io.M[a] = m1;
-                io.V[a] = v1;
-            }
+            io.X[a] = sm.xs[idx];
+            io.M[a] = sm.ms[idx];
+            io.V[a] = sm.vs[idx];
         }
     }
+    return done;
 }
 
 // ---------------------------------------------------------------------------
 // One skeleton of KT steps: one workgroup per tile (XCD-aware tile order).
+// Stop-at-first over several iterations: tiles do not wait for each other, so
+// a tile may run past the iteration at which another found the first
+// satisfying particle.  The launch therefore keeps a copy of the state it
+// started from, and a second launch (redo) runs the tiles that went past that
+// iteration again, from the copy, up to it; when no particle was found in the
+// launch it returns at once.  A launch of one iteration needs neither.
 template <int SPLIT, int MODE, int KT, bool EXT>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void particle_kernel(
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
     float* __restrict__ G, float* __restrict__ cost, float* __restrict__ terms, uint8_t* __restrict__ mask,
     int32_t* __restrict__ first_sat, const uint8_t* __restrict__ frozen, int64_t n, int64_t ld, float lr,
-    float b1, float b2, float eps, float gscale, int32_t t_arg, const int32_t* __restrict__ t_in,
-    int32_t* __restrict__ t_out, int32_t stop_at_first, const float* __restrict__ gw,
+    float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, StopArgs stop, const float* __restrict__ gw,
     const float* __restrict__ wts, int32_t* __restrict__ hits) {
     __shared__ TileSmem<SPLIT> sm;
-    // update number t: explicit, or one past the device counter of applied
-    // updates; a captured loop alternates two counter slots (read t_in,
-    // write t_out), so no launch writes a slot that its own workgroups read
-    const int32_t t = t_in ? *t_in + 1 : t_arg;
-    if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = t;
-    // stop-at-first: once an earlier iteration produced a satisfying
-    // particle, the remaining steps of a captured loop do nothing (every
-    // workgroup reads the same value: this launch only writes iter itself)
-    if (stop_at_first && first_sat && *first_sat < t - 1) return;
+    int run = iters;
+    if (MODE == MODE_STEP && stop.on) {
+        // every workgroup takes the same branch: this launch only writes
+        // values >= t - 1, a redo launch none
+        const int32_t f = __hip_atomic_load(first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (f < t - 1) return;   // stopped before this launch
+        if (stop.redo) {
+            if (f > t - 2 + iters) return;   // no particle found by the launch
+            run = f - t + 2;
+            if (stop.ran[blockIdx.x] == run) return;
+        }
+    }
     // XCD-aware tile order: consecutive workgroups are dealt round-robin to the
     // 8 XCDs, so give each XCD a contiguous range of particle tiles; tiles
     // that share cache lines of X, M and V then share one L2
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const TileIO io{T, X, M, V, G, cost, terms, mask, first_sat, frozen, gw, n, ld, gscale, EXT ? wts : nullptr,
-                    stop_at_first ? 1 : 0, MODE == MODE_COST ? hits : nullptr};
-    run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT), sm, lr, b1, b2, eps, t);
+    TileIO io{T, X, M, V, G, cost, terms, mask, first_sat, frozen, gw, n, ld, gscale, EXT ? wts : nullptr};
+    if (MODE == MODE_COST) io.hits = hits;
+    if (MODE == MODE_STEP) {
+        io.stop = stop.on;
+        io.Xb = stop.Xb;
+        io.Mb = stop.Mb;
+        io.Vb = stop.Vb;
+        io.redo = stop.redo;
+    }
+    const int ran =
+        run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT), sm, lr, b1, b2, eps, t, run);
+    if (MODE == MODE_STEP && stop.ran && !stop.redo && threadIdx.x == 0) stop.ran[blockIdx.x] = ran;
 }
 
 
-// Many skeletons of different lengths and sizes, one launch per iteration:
-// a fixed number of workgroups pull (skeleton, tile) items from a device
-// queue (items ordered by cost, largest first) until it is empty; the last
+// Many skeletons of different lengths and sizes, `iters` iterations in one
+// launch: a fixed number of workgroups pull (skeleton, tile) items from a
+// device queue (items ordered by cost, largest first) until it is empty, and
+// run every iteration of an item before they take the next; the last
 // workgroup to leave resets the queue for the next launch.
 template <int SPLIT, bool EXT>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void batch_kernel(const BatchSkel* __restrict__ skels,
                                                    const int2* __restrict__ items, int32_t n_items,
                                                    int32_t* __restrict__ queue, float lr, float b1, float b2,
-                                                   float eps, int32_t t_arg, const int32_t* __restrict__ t_in,
-                                                   int32_t* __restrict__ t_out) {
+                                                   float eps, int32_t t, int32_t iters) {
     __shared__ TileSmem<SPLIT> sm;
     __shared__ int item_s;
-    const int32_t t = t_in ? *t_in + 1 : t_arg;
-    if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = t;
     for (;;) {
         if (threadIdx.x == 0) item_s = atomicAdd(&queue[0], 1);
         __syncthreads();
@@ -1303,7 +1373,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ba
         const BatchSkel& b = skels[w.x];
         const TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
                         b.n, b.ld, b.gscale};
-        run_tile<0, SPLIT, MODE_STEP, EXT>(io, (int64_t)w.y * tile_particles(b.T->K, SPLIT), sm, lr, b1, b2, eps, t);
+        run_tile<0, SPLIT, MODE_STEP, EXT>(io, (int64_t)w.y * tile_particles(b.T->K, SPLIT), sm, lr, b1, b2, eps, t,
+                                           iters);
         __syncthreads();
     }
     if (threadIdx.x == 0) {

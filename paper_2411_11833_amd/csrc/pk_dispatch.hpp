@@ -17,10 +17,9 @@ struct PkArgs {
     const uint8_t* frozen;
     int64_t n, ld;
     AdamArgs a;
-    int32_t t;               // update number, used when t_in is null
-    const int32_t* t_in;     // device counter of applied updates (t = *t_in + 1), or null
-    int32_t* t_out;          // receives t (the other counter slot), or null
-    int32_t stop_at_first;   // skip the step if an earlier iteration satisfied
+    int32_t t;               // update number of the first iteration
+    int32_t iters;           // iterations of this launch
+    ct::StopArgs stop;
     const float* gw;         // per-particle gradient weights (gradient mode), or null
     const float* wts;        // per-particle term weights [n_terms][ld] (extended kernels), or null
     int32_t* hits;           // cost mode: touching sphere-box pairs per particle, or null
@@ -37,9 +36,7 @@ struct BatchArgs {
     int32_t* queue;          // device int[2], zero between launches
     int32_t n_workgroups;
     AdamArgs a;
-    int32_t t;
-    const int32_t* t_in;
-    int32_t* t_out;
+    int32_t t, iters;
 };
 using BatchFn = hipError_t (*)(const BatchArgs&, hipStream_t);
 

@@ -298,8 +298,8 @@ def plain_solve(gp: GpuProblem, n: int, iters: int, seed: int, chunk: int = 10, 
                 adam: B.CtAdam | None = None, X=None, fixed_grasps: bool = True, init=None) -> SolveResult:
     """The plain method: uniform seeds (or `init(X, M, V)`, which enqueues
     another initializer and is timed with the solve), then Adam until the
-    first satisfying particle or the iteration budget.  The whole budget is enqueued at once as
-    replays of one captured `chunk`-step graph with a GPU event after each;
+    first satisfying particle or the iteration budget.  The whole budget is enqueued at once in
+    calls of `chunk` iterations with a GPU event after each;
     with stop_at_first the device skips every step after the first satisfying
     iteration, so no host polling is needed.  Time to first = GPU time to the
     end of the chunk holding that iteration."""
@@ -358,8 +358,7 @@ def al_solve(gp: GpuProblem, n: int, iters: int, seed: int, rho: float = 10.0, o
                   ascent on the weights).
     Stops at the first satisfying particle (unweighted Eq. (3)) like
     plain_solve.  Uniform seeds, or `init(X, M, V)` (timed with the solve).
-    `outer` must be a multiple of `chunk` (weights move between captured
-    chunks)."""
+    `outer` must be a multiple of `chunk` (weights move between chunks)."""
     if mode not in ("phr", "dual"):
         raise ValueError(f"mode must be 'phr' or 'dual', not {mode!r}")
     if outer <= 0 or chunk <= 0 or outer % chunk:

@@ -186,7 +186,7 @@ def collect(scene_seeds, robot_seed: int = 0, n: int = 1024, iters: int = 1000, 
                 gb.gps[j].seed_uniform(init_seed + s, gb.X[j], gb.M[j], gb.V[j], n)
             else:
                 proposer.seed(proposer.prepare(prob), init_seed + s, gb.X[j], gb.M[j], gb.V[j], n)
-        for t in range(0, iters, 50):       # replays of one captured 50-step graph
+        for t in range(0, iters, 50):
             gb.optimize(t, min(50, iters - t), adam)
         torch.cuda.synchronize()
         t_gpu += time.perf_counter() - t0
