@@ -19,6 +19,21 @@ enum Mode { MODE_COST = 0, MODE_GRAD = 1, MODE_STEP = 2 };
 // lanes per workgroup of the particle kernel (four wave64s)
 constexpr int WG = 256;
 
+// Iterations of one launch of the fused step at most: bounds a launch's time
+// (an iteration of 200,000 particles takes about a millisecond) at a staging
+// cost of a few microseconds every 64 iterations.
+constexpr int MAX_LAUNCH_ITERS = 64;
+
+// One joint and its link's spheres, read as one block of scalars: the
+// Denavit-Hartenberg constants, the link's robot spheres rs[s0 .. s0 + ns),
+// and the sphere holding all of them (as lbs).  Entry 7 is the tool (no joint).
+struct alignas(64) Joint {
+    float ca, sa, a, d, th0;
+    int s0, ns, pad0;
+    float4 lb;
+    float pad1[4];
+};
+
 // A yaw-only oriented box: centre, cos/sin of its yaw, half extents.
 struct Box {
     float cx, cy, cz, c, s, hx, hy, hz;
@@ -29,6 +44,14 @@ struct Box {
 // u0 = -(c tx + s ty), u1 = s tx - c ty (two FMAs per horizontal axis).
 struct SBox {
     float c, s, u0, u1, tz, hx, hy, hz;
+};
+
+// A box for the bounding-sphere culling tests, an upright cylinder around it:
+// for a static box m2x, m2y = -2 (cx, cy) and kc = -(cx^2 + cy^2) + a margin
+// for the rounding of the test; for a moved object m2x, m2y = (cx, cy) of its
+// initial pose.  z, hz: centre height and half height; r: footprint circle.
+struct CullBox {
+    float m2x, m2y, z, hz, r, kc, pad0, pad1;
 };
 
 // weight slots
@@ -55,8 +78,8 @@ struct Tables {
     int traj_term;     // index of the TrajLength term (or -1)
     int self_on;       // robot self-collision constraint at the key configurations on/off
     int self_term;     // index of the first self-collision term (slot s adds s), or -1
+    Joint jk[CT_N_JOINTS + 1];
     int link_start[10];  // robot spheres of link L (1..8) are rs[link_start[L] .. link_start[L+1])
-    float ca[CT_N_JOINTS], sa[CT_N_JOINTS], a[CT_N_JOINTS], d[CT_N_JOINTS], th0[CT_N_JOINTS];
     float q_lo[CT_N_JOINTS], q_hi[CT_N_JOINTS];
     float tool_d;
     float q0[CT_N_JOINTS];
@@ -67,6 +90,9 @@ struct Tables {
     float4 lbs[10];                            // per link L: sphere (centre in the link frame, radius) holding
                                                // all of L's robot spheres, radius grown by a margin; w < 0: none
     SBox sbox[CT_MAX_STATIC_BOXES];
+    CullBox cbx[CT_MAX_STATIC_BOXES + CT_MAX_STEPS];   // the n_static static boxes, then the K moved objects
+    float2 ck[8 * (CT_MAX_STATIC_BOXES + CT_MAX_STEPS)];   // [8][n_static + K]: thresholds of link L's bounding
+                                               // sphere against each (xy as in the culling test, z)
     Box obj0[CT_MAX_STEPS];                    // moved object of step k at its initial pose
     float p0_yaw[CT_MAX_STEPS];                // its initial yaw
     float place_z[CT_MAX_STEPS];               // centre height when placed on the table
@@ -79,6 +105,49 @@ struct Tables {
 
 // particles per workgroup tile for a K-step skeleton and SPLIT lanes per slot
 __host__ __device__ constexpr int tile_particles(int K, int SPLIT) { return WG / (2 * K * SPLIT); }
+
+// Byte offsets of a tile's LDS for a K-step skeleton (mode MODE_*, W
+// waypoints, n_static static boxes, n_rs robot spheres).  Arrays whose size
+// the skeleton length alone decides come first.
+struct TileLayout {
+    int xs, ms, vs, plc, cpart, flg, okp, wave, osl, ob0, frz, ctl, bc, sbx, cbx, tpart, hpart, rs, ck, part, total;
+    int np;   // floats of one lane's gradient partials, odd (consecutive lanes start in different banks)
+};
+
+__host__ __device__ inline TileLayout tile_layout(int K, int split, int mode, int W, int n_static, int n_rs) {
+    const int P = tile_particles(K, split), slots = P * 2 * K, state = CT_STEP_DIM * K * P * 4;
+    const int mv = mode == MODE_STEP && W == 0 ? state : 0;
+    TileLayout o{};
+    int at = 0;
+    auto take = [&](int bytes) {
+        const int here = at;
+        at += (bytes + 15) & ~15;
+        return here;
+    };
+    o.xs = take(state);
+    o.plc = take(K * P * 16);
+    o.cpart = take(slots * 4);
+    o.flg = take(slots * 4);
+    o.okp = take(P * 4);
+    o.wave = take(WG / 64 * 2048);
+    o.osl = take(K * CT_MAX_OBJ_SPHERES * 16);
+    o.ob0 = take(K * (int)sizeof(Box));
+    o.frz = take(CT_STEP_DIM * K);
+    o.ctl = take(16);
+    o.bc = take(mode == MODE_STEP ? MAX_LAUNCH_ITERS * 8 : 0);
+    o.ms = take(mv);
+    o.vs = take(mv);
+    o.sbx = take(n_static * (int)sizeof(SBox));
+    o.cbx = take((n_static + K) * (int)sizeof(CullBox));
+    o.tpart = take(W > 0 ? slots * 4 : 0);
+    o.hpart = take(mode == MODE_COST ? slots * 4 : 0);
+    o.rs = take(n_rs * 16);
+    o.ck = take(8 * (n_static + K) * 8);
+    o.np = (11 + 3 * K + (W > 0 ? CT_N_JOINTS : 0)) | 1;
+    o.part = take(mode == MODE_COST ? 0 : slots * split * o.np * 4);
+    o.total = at;
+    return o;
+}
 
 // Stop-at-first of the fused step: on = leave after the first iteration that
 // finds a satisfying particle; with several iterations per launch, the copies

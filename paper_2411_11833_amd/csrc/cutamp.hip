@@ -16,15 +16,6 @@
 #include "ct_tables.hpp"
 #include "pk_dispatch.hpp"
 
-namespace {
-
-// Iterations of one launch of the fused step at most: bounds a launch's time
-// (an iteration of 200,000 particles takes about a millisecond) at a
-// staging cost of a few microseconds every 64 iterations.
-constexpr int32_t MAX_LAUNCH_ITERS = 64;
-
-}  // namespace
-
 struct ct_problem {
     ct::Tables h;               // host copy of the tables
     ct::Tables* d = nullptr;    // device copy
@@ -65,6 +56,54 @@ float4 bounding_sphere(const float4* sp, int n) {
         rad = std::max(rad, std::sqrt(dx * dx + dy * dy + dz * dz) + (double)sp[i].w);
     }
     return make_float4((float)c[0], (float)c[1], (float)c[2], (float)(rad * (1 + 1e-6) + 1e-4));
+}
+
+float round_up(double v) { return std::nextafterf((float)v, INFINITY); }
+
+// The culling cylinders and thresholds of the bounding-sphere tests, from the
+// FP32 boxes and spheres the kernels use.  Every threshold is rounded up, and
+// the squared ones carry a margin for the FP32 evaluation of |w|^2 - 2 w.c
+// (three roundings of values up to (|w| + |c|)^2, and a hit has |w| <= |c| +
+// e): 1e-6 (2 |c| + e)^2 is five times that.
+void cull_tables(ct::Tables& T) {
+    const int ns = T.n_static, nb = ns + T.K;
+    double e_obj = 0;   // an object's bounding sphere, at most
+    for (int k = 0; k < T.K; ++k) e_obj = std::max(e_obj, (double)T.obs[k].w);
+    auto margin = [](double c2, double e) {
+        const double m = 2 * std::sqrt(c2) + e;
+        return 1e-6 * m * m;
+    };
+    for (int b = 0; b < nb; ++b) {
+        ct::CullBox& C = T.cbx[b];
+        double c2 = 0, r;
+        if (b < ns) {
+            const ct::SBox& B = T.sbox[b];
+            // centre back from the box-frame offsets: t = -R (u0, u1)
+            const double cx = -((double)B.c * B.u0 - (double)B.s * B.u1);
+            const double cy = -((double)B.s * B.u0 + (double)B.c * B.u1);
+            r = std::hypot((double)B.hx, (double)B.hy) * (1 + 1e-6);
+            C.m2x = (float)(-2 * cx);
+            C.m2y = (float)(-2 * cy);
+            C.z = B.tz;
+            C.hz = B.hz;
+            c2 = cx * cx + cy * cy;
+            C.kc = round_up(-c2 + margin(c2, e_obj + r));
+        } else {
+            const ct::Box& O = T.obj0[b - ns];
+            r = std::hypot((double)O.hx, (double)O.hy) * (1 + 1e-6);
+            C.m2x = O.cx;
+            C.m2y = O.cy;
+            C.z = O.cz;
+            C.hz = O.hz;
+        }
+        C.r = round_up(r);
+        for (int L = 1; L <= 8; ++L) {
+            const double rb = T.lbs[L].w, e = rb + C.r;
+            float2& th = T.ck[(L - 1) * nb + b];
+            th.x = round_up(b < ns ? e * e - c2 + margin(c2, e) : e * e * (1 + 1e-6));
+            th.y = round_up(rb + C.hz);
+        }
+    }
 }
 
 bool valid_box(const double* b) {
@@ -169,8 +208,10 @@ int run_pk(const ct_problem* P, int mode, const PkArgs& a, hipStream_t st, int s
     PkArgs b = a;
     b.wts = weighted ? P->wts : nullptr;
     if (b.wts && P->wts_ld != a.ld) return CT_ERR_INVALID_ARG;
-    PkFn f = pick_kernel(split ? split : effective_split(P, a.n), P->K, mode, P->h.self_on || b.wts);
+    if (!split) split = effective_split(P, a.n);
+    PkFn f = pick_kernel(split, P->K, mode, P->h.self_on || b.wts);
     if (!f) return CT_ERR_UNSUPPORTED;
+    b.lds = ct::tile_layout(P->K, split, mode, P->h.W, P->h.n_static, P->h.link_start[9]).total;
     return err_of(f(P->d, b, st));
 }
 
@@ -285,11 +326,11 @@ extern "C" int ct_problem_create(const ct_robot* robot, const ct_scene* scene, c
     T.n_os = scene->n_obj_spheres;
     for (int i = 0; i < CT_N_JOINTS; ++i) {
         const double* r = robot->dh + 4 * i;
-        T.a[i] = (float)r[0];
-        T.ca[i] = (float)std::cos(r[1]);
-        T.sa[i] = (float)std::sin(r[1]);
-        T.d[i] = (float)r[2];
-        T.th0[i] = (float)r[3];
+        T.jk[i].a = (float)r[0];
+        T.jk[i].ca = (float)std::cos(r[1]);
+        T.jk[i].sa = (float)std::sin(r[1]);
+        T.jk[i].d = (float)r[2];
+        T.jk[i].th0 = (float)r[3];
         T.q_lo[i] = (float)robot->q_lo[i];
         T.q_hi[i] = (float)robot->q_hi[i];
         T.q0[i] = sk->q0 ? (float)sk->q0[i] : 0.f;
@@ -310,6 +351,11 @@ extern "C" int ct_problem_create(const ct_robot* robot, const ct_scene* scene, c
     for (int L = 0; L < 10; ++L)
         T.lbs[L] = (L >= 1 && L <= 8) ? bounding_sphere(T.rs + T.link_start[L], T.link_start[L + 1] - T.link_start[L])
                                       : make_float4(0.f, 0.f, 0.f, -1.f);
+    for (int L = 1; L <= 8; ++L) {
+        T.jk[L - 1].s0 = T.link_start[L];
+        T.jk[L - 1].ns = T.link_start[L + 1] - T.link_start[L];
+        T.jk[L - 1].lb = T.lbs[L];
+    }
     // boxes that never move
     int nb = 0;
     T.sbox[nb++] = to_sbox(scene->table);
@@ -351,6 +397,7 @@ extern "C" int ct_problem_create(const ct_robot* robot, const ct_scene* scene, c
         lo[19] = (float)scene->region_lo[1];
         hi[19] = (float)scene->region_hi[1];
     }
+    cull_tables(T);
     for (int c = 0; c < 2; ++c) {
         T.region_lo[c] = (float)scene->region_lo[c];
         T.region_hi[c] = (float)scene->region_hi[c];
@@ -689,7 +736,7 @@ extern "C" int ct_optimize(ct_problem* P, float* X, float* M, float* V, int64_t 
     if (n == 0 || iters == 0) return CT_OK;
     hipStream_t st = (hipStream_t)stream;
     const int split = effective_split(P, n);
-    int32_t per = MAX_LAUNCH_ITERS;
+    int32_t per = ct::MAX_LAUNCH_ITERS;
     ct::StopArgs stop{};
     stop.on = stop_at_first ? 1 : 0;
     if (stop.on && iters > 1 && !stop_workspace(P, n, ld, split, st, stop)) per = 1;
@@ -833,6 +880,9 @@ int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, int32_t iters, hip
         g.a = a;
         g.t = t;
         g.iters = iters;
+        for (const ct_problem* P : B->probs)
+            g.lds = std::max(g.lds, 16 + ct::tile_layout(P->K, batch_split(B), ct::MODE_STEP, P->h.W, P->h.n_static,
+                                                         P->h.link_start[9]).total);
         return err_of(f(g, st));
     }
     // reference point: one ordinary launch per skeleton
@@ -927,8 +977,8 @@ extern "C" int ct_batch_step(ct_batch* B, int64_t t, const ct_adam* adam, void* 
 extern "C" int ct_batch_optimize(ct_batch* B, int64_t t0, int32_t iters, const ct_adam* adam, void* stream) {
     if (!B || t0 < 0 || iters < 0 || t0 + iters > INT32_MAX || !valid_adam(adam)) return CT_ERR_INVALID_ARG;
     int rc = CT_OK;
-    for (int64_t done = 0; done < iters && rc == CT_OK; done += MAX_LAUNCH_ITERS)
-        rc = batch_launch(B, adam, (int32_t)(t0 + done + 1), (int32_t)std::min<int64_t>(MAX_LAUNCH_ITERS, iters - done),
+    for (int64_t done = 0; done < iters && rc == CT_OK; done += ct::MAX_LAUNCH_ITERS)
+        rc = batch_launch(B, adam, (int32_t)(t0 + done + 1), (int32_t)std::min<int64_t>(ct::MAX_LAUNCH_ITERS, iters - done),
                           (hipStream_t)stream);
     return rc;
 }

@@ -27,6 +27,16 @@
 
 #include "ct_tables.hpp"
 
+#ifndef CT_JOINT_UNROLL
+#define CT_JOINT_UNROLL 1
+#endif
+#ifndef CT_WPE
+#define CT_WPE 2
+#endif
+#ifndef CT_WPB
+#define CT_WPB 2
+#endif
+
 namespace ct {
 
 
@@ -38,21 +48,20 @@ __device__ __forceinline__ float box_d2(float px, float py, float pz, float hx, 
     const float mx = fmaxf(fabsf(px) - hx, 0.f);
     const float my = fmaxf(fabsf(py) - hy, 0.f);
     const float mz = fmaxf(fabsf(pz) - hz, 0.f);
-    return mx * mx + my * my + mz * mz;
+    return fmaf(mz, mz, fmaf(mx, mx, my * my));
 }
 
 // Penetration of a sphere that touches the box (its squared outside distance
 // is below r^2), from the centre p in the box frame: pen = r - sdf with
 // sdf = ||max(u, 0)|| + min(max_i u_i, 0), u = |p| - h (App. "Collision
-// Representation": spheres against oriented boxes), and lam * d pen / d
-// centre in world coordinates (box yaw cos c, sin s).
+// Representation": spheres against oriented boxes), and v = d sdf / d centre
+// = -d pen / d centre in world coordinates (box yaw cos c, sin s).
 // Tie conventions: sign(0) = +1; among equal interior depths the lowest axis.
 __device__ __forceinline__ void pair_hit(float px, float py, float pz, float r, float c, float s, float hx,
-                                         float hy, float hz, float lam, float& pen, float& gx, float& gy,
-                                         float& gz) {
+                                         float hy, float hz, float& pen, float& vx, float& vy, float& vz) {
     const float ux = fabsf(px) - hx, uy = fabsf(py) - hy, uz = fabsf(pz) - hz;
     const float mx = fmaxf(ux, 0.f), my = fmaxf(uy, 0.f), mz = fmaxf(uz, 0.f);
-    const float d2 = mx * mx + my * my + mz * mz;
+    const float d2 = fmaf(mz, mz, fmaf(mx, mx, my * my));
     float sdf, ax, ay, az;  // sdf and d sdf / d p
     if (d2 > 0.f) {
         const float inv = fast_rsq(d2);
@@ -74,175 +83,26 @@ __device__ __forceinline__ void pair_hit(float px, float py, float pz, float r, 
     }
     pen = r - sdf;
     // d pen / d centre = -R d sdf / d p
-    gx = -lam * (c * ax - s * ay);
-    gy = -lam * (s * ax + c * ay);
-    gz = -lam * az;
+    vx = fmaf(c, ax, -(s * ay));
+    vy = fmaf(c, ay, s * ax);
+    vz = az;
 }
 
-// Poses of the moved objects as seen by one lane's step: placed by an earlier
-// step (at P(rho_j), a particle variable) or still at the initial pose.
-// The moved objects as seen by one lane's step k: object j (j < K) was
-// placed by an earlier step (at P(rho_j), a particle variable) or is still
-// at its initial pose (tables).  With the skeleton length known at compile
-// time (KT > 0) the lane keeps the K poses in registers and the loops over
-// them unroll; KT = 0 reads K at run time and the poses from the particle's
-// staged placements in LDS (the many-skeleton kernel).
+// The centres of the moved objects as one lane's step k sees them, for the
+// culling tests: object j (j < K) was placed by an earlier step (at P(rho_j),
+// a particle variable) or is still at its initial pose.  With the skeleton
+// length known at compile time the lane keeps the K centres in registers;
+// KT = 0 (the many-skeleton kernel) reads them from the tile's LDS.
 template <int KT>
 struct MoveCtx {
-    float x[KT], y[KT], c[KT], s[KT];
-    int k;
-    __device__ __forceinline__ int count() const { return KT; }
-    __device__ __forceinline__ void pose(const Tables* __restrict__, int j, float& bx, float& by, float& bc,
-                                         float& bs) const {
-        bx = x[j]; by = y[j]; bc = c[j]; bs = s[j];
-    }
+    float x[KT], y[KT];
+    int k, p;   // step, particle of the tile
 };
 
 template <>
 struct MoveCtx<0> {
-    const float4* plc;   // plc[j * pstride] = (x, y, cos yaw, sin yaw) of rho_j
-    int pstride;
-    int K, k;
-    __device__ __forceinline__ int count() const { return K; }
-    __device__ __forceinline__ void pose(const Tables* __restrict__ T, int j, float& bx, float& by, float& bc,
-                                         float& bs) const {
-        const bool placed = j < k;
-        const float4 pl = plc[j * pstride];
-        const Box& O = T->obj0[j];
-        bx = placed ? pl.x : O.cx; by = placed ? pl.y : O.cy;
-        bc = placed ? pl.z : O.c; bs = placed ? pl.w : O.s;
-    }
+    int k, p;
 };
-
-// A run of NB spheres of one lane against every box of step k: static boxes
-// (uniform, one scalar load per box for the whole run) and the other moved
-// objects (per lane).  The NB distance tests are independent dependency
-// chains; the penetration branch runs only when some lane's sphere touches
-// the box.  Accumulates the unweighted penetration, each sphere's weighted
-// centre gradient, and the weighted gradient with respect to the placements
-// rho_j of boxes placed by earlier steps.
-// Boxes that the bounding sphere (world centre w, radius rb) of some lane's
-// sphere set touches: bit b of smask for static box b, bit j of omask for
-// moved object j.  The masks are wave-uniform (ballot), so the sphere loops
-// skip a box only when no lane of the wave needs it.  The bound holds every
-// sphere of the set with a margin, so a skipped box touches none of them and
-// every penetration sum is unchanged.
-// The SPLIT lanes of a slot hold the same bounding sphere, so they share the
-// static boxes out: lane si tests boxes si, si + SPLIT, ... (from the
-// workgroup's LDS copy sbl), and the ballot bits of the lanes with a given si
-// (every SPLIT-th lane of the wave) tell whether some slot touches that box.
-template <int KT, int SPLIT>
-__device__ __forceinline__ void touched_boxes(const Tables* __restrict__ T, const SBox* __restrict__ sbl, int si,
-                                              const MoveCtx<KT>& mc, float wx, float wy, float wz, float rb,
-                                              uint32_t& smask, uint32_t& omask) {
-    const float r2 = rb * rb;
-    smask = 0u;
-    omask = 0u;
-    const int nsb = T->n_static;
-    constexpr uint64_t LANES = SPLIT == 1 ? ~0ull : SPLIT == 2 ? 0x5555555555555555ull : 0x1111111111111111ull;
-    for (int b0 = 0; b0 < nsb; b0 += SPLIT) {
-        const int b = b0 + si;
-        const SBox B = sbl[min(b, nsb - 1)];
-        const float px = fmaf(B.c, wx, fmaf(B.s, wy, B.u0));
-        const float py = fmaf(B.c, wy, fmaf(-B.s, wx, B.u1));
-        const float pz = wz - B.tz;
-        const uint64_t hit = __ballot(b < nsb && box_d2(px, py, pz, B.hx, B.hy, B.hz) < r2);
-#pragma unroll
-        for (int u = 0; u < SPLIT; ++u)
-            if (hit & (LANES << u)) smask |= 1u << (b0 + u);
-    }
-#pragma unroll
-    for (int j = 0; j < mc.count(); ++j) {
-        const Box O = T->obj0[j];
-        float bx, by, bc, bs;
-        mc.pose(T, j, bx, by, bc, bs);
-        const float dx = wx - bx, dy = wy - by;
-        const float px = bc * dx + bs * dy, py = bc * dy - bs * dx, pz = wz - O.cz;
-        const bool hit = j != mc.k && box_d2(px, py, pz, O.hx, O.hy, O.hz) < r2;
-        if (__ballot(hit)) omask |= 1u << j;
-    }
-}
-
-template <int KT, int NB, bool GRAD>
-__device__ __forceinline__ void run_vs_world(const Tables* __restrict__ T, const MoveCtx<KT>& mc, uint32_t smask,
-                                             uint32_t omask, const float (&cx)[NB], const float (&cy)[NB],
-                                             const float (&cz)[NB], const float (&r)[NB], float lam,
-                                             float (&pen_sum)[NB], float (&gx)[NB], float (&gy)[NB],
-                                             float (&gz)[NB], float* __restrict__ gr, int& nhit) {
-    float r2[NB];
-#pragma unroll
-    for (int m = 0; m < NB; ++m) r2[m] = r[m] * r[m];
-    for (uint32_t mm = smask; mm; mm &= mm - 1u) {   // the static boxes some lane's set touches
-        const int b = __builtin_ctz(mm);
-        const SBox B = T->sbox[b];
-        bool act[NB];
-        bool any = false;
-        float px[NB], py[NB], pz[NB];
-#pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            px[m] = fmaf(B.c, cx[m], fmaf(B.s, cy[m], B.u0));
-            py[m] = fmaf(B.c, cy[m], fmaf(-B.s, cx[m], B.u1));
-            pz[m] = cz[m] - B.tz;
-            act[m] = box_d2(px[m], py[m], pz[m], B.hx, B.hy, B.hz) < r2[m];
-            any |= act[m];
-        }
-        if (any) {
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                if (act[m]) {
-                    float pen, ax, ay, az;
-                    pair_hit(px[m], py[m], pz[m], r[m], B.c, B.s, B.hx, B.hy, B.hz, lam, pen, ax, ay, az);
-                    pen_sum[m] += pen;
-                    if (!GRAD) ++nhit;
-                    if (GRAD) { gx[m] += ax; gy[m] += ay; gz[m] += az; }
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < mc.count(); ++j) {   // wave-uniform trip count
-        if (!((omask >> j) & 1u)) continue;   // wave-uniform
-        const Box O = T->obj0[j];
-        const bool placed = j < mc.k;
-        float bx, by, bc, bs;
-        mc.pose(T, j, bx, by, bc, bs);
-        const bool on = j != mc.k;   // the step's own object is held, not an obstacle
-        bool act[NB];
-        bool any = false;
-        float dx[NB], dy[NB], px[NB], py[NB], pz[NB];
-#pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            dx[m] = cx[m] - bx;
-            dy[m] = cy[m] - by;
-            px[m] = bc * dx[m] + bs * dy[m];
-            py[m] = bc * dy[m] - bs * dx[m];
-            pz[m] = cz[m] - O.cz;
-            act[m] = on && box_d2(px[m], py[m], pz[m], O.hx, O.hy, O.hz) < r2[m];
-            any |= act[m];
-        }
-        if (any) {
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                if (act[m]) {
-                    float pen, ax, ay, az;
-                    pair_hit(px[m], py[m], pz[m], r[m], bc, bs, O.hx, O.hy, O.hz, lam, pen, ax, ay, az);
-                    pen_sum[m] += pen;
-                    if (!GRAD) ++nhit;
-                    if (GRAD) {
-                        gx[m] += ax; gy[m] += ay; gz[m] += az;
-                        if (placed) {
-                            // moving the box by d equals moving the sphere by -d; turning it
-                            // about its own vertical axis equals turning the sphere back
-                            gr[3 * j] -= ax;
-                            gr[3 * j + 1] -= ay;
-                            gr[3 * j + 2] -= dx[m] * ay - dy[m] * ax;
-                        }
-                    }
-                }
-            }
-        }
-    }
-}
 
 // Bijection from the launch index to a tile index that keeps each XCD's
 // workgroups (b = x, x + 8, x + 16, ...) on a contiguous tile range.
@@ -252,12 +112,6 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t G) {
     return x * q + (x < rem ? x : rem) + b / NX;
 }
 
-// Spheres tested together against each box (independent dependency chains,
-// one box load per run): 4 in the single-skeleton kernels, 2 in the
-// many-skeleton kernel, whose run-time skeleton length leaves fewer registers.
-template <int KT>
-constexpr int run_len() { return KT > 0 ? 4 : 2; }
-
 template <int SPLIT>
 __device__ __forceinline__ float split_sum(float v) {
     if (SPLIT >= 2) v += __shfl_xor(v, 1);
@@ -265,160 +119,350 @@ __device__ __forceinline__ float split_sum(float v) {
     return v;
 }
 
+// v of the SPLIT lanes of a slot to all of them: out[j0 + u] = v of lane u.
+template <int SPLIT>
+__device__ __forceinline__ void split_bcast(float v, int j0, float out[CT_N_JOINTS]) {
+    const int b = __float_as_int(v);
+    if (SPLIT == 1) {
+        out[j0] = v;
+    } else if (SPLIT == 2) {
+        out[j0] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0xA0, 0xF, 0xF, true));
+        if (j0 + 1 < CT_N_JOINTS) out[j0 + 1] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0xF5, 0xF, 0xF, true));
+    } else {
+        out[j0] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0x00, 0xF, 0xF, true));
+        if (j0 + 1 < CT_N_JOINTS) out[j0 + 1] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0x55, 0xF, 0xF, true));
+        if (j0 + 2 < CT_N_JOINTS) out[j0 + 2] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0xAA, 0xF, 0xF, true));
+        if (j0 + 3 < CT_N_JOINTS) out[j0 + 3] = __int_as_float(__builtin_amdgcn_mov_dpp(b, 0xFF, 0xF, 0xF, true));
+    }
+}
+
 __device__ __forceinline__ void cross3(const float a[3], const float b[3], float o[3]) {
-    o[0] = a[1] * b[2] - a[2] * b[1];
-    o[1] = a[2] * b[0] - a[0] * b[2];
-    o[2] = a[0] * b[1] - a[1] * b[0];
+    o[0] = fmaf(a[1], b[2], -(a[2] * b[1]));
+    o[1] = fmaf(a[2], b[0], -(a[0] * b[2]));
+    o[2] = fmaf(a[0], b[1], -(a[1] * b[0]));
+}
+
+// z . tq + m . f of a joint axis (z, m) and a wrench (force f, moment tq).
+__device__ __forceinline__ float axis_wrench(const float z[3], const float m[3], const float f[3], const float tq[3]) {
+    return fmaf(m[2], f[2], fmaf(m[1], f[1], fmaf(m[0], f[0], fmaf(z[2], tq[2], fmaf(z[0], tq[0], z[1] * tq[1])))));
 }
 
 // One standard-DH joint: (R, t) <- (R, t) Rz(theta_i) Tz(d_i) Tx(a_i) Rx(alpha_i)
 // for joint i (0-based) with the sine and cosine of theta_i = q_i + theta0_i.
-__device__ __forceinline__ void joint_advance(const Tables* __restrict__ T, int i, float sn, float cs, float R[9],
-                                              float t[3]) {
-    const float ca = T->ca[i], sa = T->sa[i], a = T->a[i], d = T->d[i];
+__device__ __forceinline__ void joint_advance(const Joint& J, float sn, float cs, float R[9], float t[3]) {
+    const float ca = J.ca, sa = J.sa, a = J.a, d = J.d;
     const float lx = a * cs, ly = a * sn;
 #pragma unroll
     for (int rr = 0; rr < 3; ++rr) {
         const float r0 = R[3 * rr], r1 = R[3 * rr + 1], r2 = R[3 * rr + 2];
-        t[rr] += r0 * lx + r1 * ly + r2 * d;
-        const float w = r1 * cs - r0 * sn;
-        R[3 * rr] = r0 * cs + r1 * sn;
-        R[3 * rr + 1] = ca * w + r2 * sa;
-        R[3 * rr + 2] = r2 * ca - sa * w;
+        t[rr] += fmaf(r2, d, fmaf(r0, lx, r1 * ly));
+        const float w = fmaf(r1, cs, -(r0 * sn));
+        R[3 * rr] = fmaf(r0, cs, r1 * sn);
+        R[3 * rr + 1] = fmaf(r2, sa, ca * w);
+        R[3 * rr + 2] = fmaf(r2, ca, -(sa * w));
     }
 }
 
-// NB consecutive robot spheres of one lane on a link with frame (R, t):
-// lane si of a slot takes table entries s0 + si + SPLIT j, j = j0 .. j0+NB-1
-// (entries past the link's end get radius 0, which never penetrates).
-// Accumulates the link's wrench (force f, moment tq about the world origin).
-// The sphere table is the workgroup's LDS copy (rsl), read at each lane's
-// own entry.
-template <int KT, int SPLIT, int NB, bool GRAD>
-__device__ __forceinline__ void robot_run(const Tables* __restrict__ T, const float4* __restrict__ rsl, int s0,
-                                          int s1, int j0, int si, const float R[9], const float t[3],
-                                          const MoveCtx<KT>& mc, uint32_t smask, uint32_t omask, float lam,
-                                          float& coll, float f[3], float tq[3], float* __restrict__ gr, int& nhit) {
-    float cx[NB], cy[NB], cz[NB], rr[NB], gx[NB], gy[NB], gz[NB];
-#pragma unroll
-    for (int m = 0; m < NB; ++m) {
-        const int e = s0 + SPLIT * (j0 + m) + si;
-        const float4 sp = rsl[min(e, s1 - 1)];
-        rr[m] = e < s1 ? sp.w : 0.f;
-        cx[m] = R[0] * sp.x + R[1] * sp.y + R[2] * sp.z + t[0];
-        cy[m] = R[3] * sp.x + R[4] * sp.y + R[5] * sp.z + t[1];
-        cz[m] = R[6] * sp.x + R[7] * sp.y + R[8] * sp.z + t[2];
-        gx[m] = gy[m] = gz[m] = 0.f;
+// ---------------------------------------------------------------------------
+// Spheres against boxes.
+//
+// Of the ~880 sphere-box pairs of a packing configuration 2.6 penetrate, and
+// a link's bounding sphere touches 0.2 boxes on average; but over the 32 or 64
+// configurations of a wave some lane needs almost every (link, box) pair.  So
+// the lanes do not walk their own spheres: per link, the configurations whose
+// bounding sphere touches a box ("owners") are compacted, and the whole wave
+// tests their spheres, one (owner, sphere) per lane, each lane walking only
+// its owner's boxes.  The penetrations found go back through LDS to the
+// owner's lanes, which add them in the order in which a lane walking its own
+// spheres would: spheres ascending, and within a sphere the static boxes and
+// then the moved objects ascending; with SPLIT lanes per configuration lane si
+// adds the spheres si, si + SPLIT, ...  Sums are therefore the same whatever
+// the mapping of tests to lanes.
+
+// LDS of one workgroup's tile (see tile_layout for the sizes).
+struct TileLds {
+    float *xs, *ms, *vs;   // staged particles [D][P]; Adam moments (fused step without waypoints)
+    float* part;           // gradient partials, np per lane
+    float4* plc;           // [K][P] placements (x, y, cos yaw, sin yaw)
+    float4* rs;            // robot spheres
+    float4* osl;           // [K][CT_MAX_OBJ_SPHERES] object spheres
+    SBox* sbx;             // static boxes
+    CullBox* cbx;          // culling constants of the static boxes, then of the K moved objects
+    float2* ck;            // [8][n_static + K] thresholds (xy^2, z) of link L's bounding sphere
+    Box* ob0;              // [K] moved objects at their initial poses
+    float *cpart, *tpart;  // [P][2K] slot costs, transition lengths
+    int *flg, *hpart;      // [P][2K] slot flags, touching pairs
+    int* okp;              // [P] update permission
+    uint8_t* frz;          // [D] frozen dimensions
+    int* ctl;              // any_sat, halt
+    float2* bc;            // [MAX_LAUNCH_ITERS] 1 - beta1^t, 1 - beta2^t of the launch's updates (fused step)
+    float4* wave;          // WAVE_F4 per wave: owner records, then test results
+    int np, P;
+};
+
+// Orders a wave's LDS accesses for the compiler: the lanes of a wave run in
+// step and its LDS operations complete in order, so no wait is needed.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Per wave: up to OWNERS owner records of 5 float4 (one of padding: the 16
+// records of a pass start in different banks), overwritten by the results of
+// the wave's 64 tests, 2 float4 each.
+constexpr int OWNERS = 16;
+constexpr int WAVE_F4 = 128;
+
+// Boxes that a bounding sphere (world centre w, radius rb) may touch: bit b of
+// smask for static box b, bit j of omask for moved object j.  A box is tested
+// as an upright cylinder (its footprint's circle, its height), 6 vector
+// instructions where the exact box distance takes 18 and lets 30% fewer pairs
+// through: the circle's squared test |w - c|^2 < (rb + r)^2 is taken as
+// |w|^2 - 2 w.c < K with K = (rb + r)^2 - |c|^2 and a margin for its rounding
+// from the host.  The bounding sphere holds its set with a margin, so a box
+// left out touches no sphere of the set and every sum is unchanged.  The SPLIT
+// lanes of a slot hold the same bounding sphere and share the static boxes
+// out: lane si tests boxes si, si + SPLIT, ...
+template <int SPLIT>
+__device__ __forceinline__ uint32_t split_or(uint32_t v) {
+    if (SPLIT >= 2) v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);   // lanes ^ 1
+    if (SPLIT >= 4) v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);   // lanes ^ 2
+    return v;
+}
+
+// L >= 0: robot link L (thresholds from the table); L < 0: an object's sphere
+// of radius rb (thresholds formed here).
+template <int KT, int SPLIT, bool LINK>
+__device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int K, int si, const MoveCtx<KT>& mc,
+                                              const float2* __restrict__ ck, float wx, float wy, float wz, float rb,
+                                              uint32_t& smask, uint32_t& omask) {
+    const float q = wx * wx + wy * wy;
+    smask = 0u;
+    omask = 0u;
+    uint32_t bit = 1u << si;
+    for (int b0 = 0; b0 < nsb; b0 += SPLIT) {
+        const int b = min(b0 + si, nsb - 1);
+        const CullBox C = S.cbx[b];
+        float2 th;
+        if (LINK) {
+            th = ck[b];
+        } else {
+            const float e = rb + C.r;
+            th = make_float2(fmaf(e, e, C.kc), rb + C.hz);
+        }
+        const float t = fmaf(C.m2x, wx, fmaf(C.m2y, wy, q));
+        const bool hit = t < th.x && fabsf(wz - C.z) < th.y;
+        smask |= hit ? bit : 0u;
+        bit <<= SPLIT;
     }
-    // per-sphere sums over boxes, added to coll in sphere order: the same
-    // additions in the same order whatever the run length
-    float pen[NB];
+    // a box past the last one repeats it at a bit of its own
+    smask = split_or<SPLIT>(smask) & (nsb < 32 ? (1u << nsb) - 1u : ~0u);
+    if (KT == 1) return;   // the only moved object is the one in the hand
 #pragma unroll
-    for (int m = 0; m < NB; ++m) pen[m] = 0.f;
-    run_vs_world<KT, NB, GRAD>(T, mc, smask, omask, cx, cy, cz, rr, lam, pen, gx, gy, gz, gr, nhit);
-#pragma unroll
-    for (int m = 0; m < NB; ++m) coll += pen[m];
-    if (GRAD) {
-#pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            f[0] += gx[m]; f[1] += gy[m]; f[2] += gz[m];
-            tq[0] += cy[m] * gz[m] - cz[m] * gy[m];
-            tq[1] += cz[m] * gx[m] - cx[m] * gz[m];
-            tq[2] += cx[m] * gy[m] - cy[m] * gx[m];
+    for (int j = 0; j < (KT ? KT : K); ++j) {
+        const CullBox C = S.cbx[nsb + j];
+        float2 th;
+        if (LINK) {
+            th = ck[nsb + j];
+        } else {
+            const float e = rb + C.r;
+            th = make_float2(e * e * 1.000001f, rb + C.hz);
+        }
+        float bx, by;
+        if constexpr (KT > 0) {
+            bx = mc.x[j];
+            by = mc.y[j];
+        } else {
+            const float4 pl = S.plc[j * S.P + mc.p];
+            const bool placed = j < mc.k;
+            bx = placed ? pl.x : C.m2x;
+            by = placed ? pl.y : C.m2y;
+        }
+        const float dx = wx - bx, dy = wy - by;
+        const bool hit = dx * dx + dy * dy < th.x && fabsf(wz - C.z) < th.y;
+        omask |= hit ? 1u << j : 0u;
+    }
+    omask &= ~(1u << mc.k);   // the step's own object is held, not an obstacle
+}
+
+// One set of ns spheres per configuration (a link's, an object's) in the frame
+// (R, t) against the boxes of smask and omask.  tab: the set's sphere table
+// in LDS, or (OBJ) the table of step 0 (an owner's step selects its own).
+// Adds the penetrations of this lane's spheres to coll, their weighted
+// gradients to the wrench (f, tq about the world origin) and to the placement
+// partials gr.  The active lanes of the wave are its first lanes (at least
+// 48: tiles leave at most the tail of the last wave idle).
+template <int KT, int SPLIT, bool GRAD, bool OBJ>
+__device__ __forceinline__ void sphere_set(const TileLds& S, int K, const float4* __restrict__ tab, int ns, int si,
+                                           const float R[9], const float t[3], const MoveCtx<KT>& mc, uint32_t smask,
+                                           uint32_t omask, float lam, float& coll, float f[3], float tq[3],
+                                           float* __restrict__ gr, int& nhit) {
+    const bool mine = (smask | omask) != 0u;
+    const uint64_t owners = __ballot(mine);
+    if (!owners) return;   // wave-uniform: no configuration of the wave touches a box
+    const int lane = threadIdx.x & 63;
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(owners >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)owners, 0u)) / SPLIT;
+    const int na = __popcll(owners) / SPLIT, nact = __popcll(__ballot(true));
+    float4* rec = S.wave + (threadIdx.x >> 6) * WAVE_F4;
+    constexpr uint32_t CLASS = SPLIT == 1 ? ~0u : SPLIT == 2 ? 0x55555555u : 0x11111111u;
+    for (int c0 = 0; c0 < ns; c0 += 32) {
+        const int nc = min(ns - c0, 32);
+        const float inv = __builtin_amdgcn_rcpf((float)nc);
+        const int per = __builtin_amdgcn_readfirstlane(min((int)(((float)nact + 0.5f) * inv), OWNERS));
+        const int g = (int)(((float)lane + 0.5f) * inv), e = lane - g * nc;   // owner of the pass, sphere
+        for (int a0 = 0; a0 < na; a0 += per) {
+            const bool here = mine && (uint32_t)(rank - a0) < (uint32_t)per;
+            const int rel = rank - a0;
+            if (here && si == 0) {
+                float4* w = rec + rel * 5;
+                w[0] = make_float4(R[0], R[1], R[2], R[3]);
+                w[1] = make_float4(R[4], R[5], R[6], R[7]);
+                w[2] = make_float4(R[8], t[0], t[1], t[2]);
+                w[3] = make_float4(__uint_as_float(smask), __uint_as_float(omask | (uint32_t)mc.k << 8 | (uint32_t)mc.p << 16),
+                                   lam, 0.f);
+            }
+            wave_sync();
+            const bool on = g < per && a0 + g < na;
+            const float4* w = rec + (on ? g : 0) * 5;
+            const float4 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+            uint32_t sm = on ? __float_as_uint(w3.x) : 0u;
+            const uint32_t ow = __float_as_uint(w3.y);
+            const uint32_t om = on ? ow & 0xFFu : 0u;
+            const int kk = (int)(ow >> 8 & 0xFFu), pp = (int)(ow >> 16);
+            const float wl = w3.z;
+            const float4 sp = tab[(OBJ ? kk * CT_MAX_OBJ_SPHERES : 0) + c0 + e];
+            const float cx = fmaf(w0.z, sp.z, fmaf(w0.x, sp.x, w0.y * sp.y)) + w2.y;
+            const float cy = fmaf(w1.y, sp.z, fmaf(w0.w, sp.x, w1.x * sp.y)) + w2.z;
+            const float cz = fmaf(w2.x, sp.z, fmaf(w1.z, sp.x, w1.w * sp.y)) + w2.w;
+            const float r = sp.w, r2 = r * r;
+            float pen = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
+            int hits = 0;
+            while (sm) {   // this lane's owner's static boxes
+                const int b = __builtin_ctz(sm);
+                sm &= sm - 1u;
+                const SBox B = S.sbx[b];
+                const float px = fmaf(B.c, cx, fmaf(B.s, cy, B.u0));
+                const float py = fmaf(B.c, cy, fmaf(-B.s, cx, B.u1));
+                const float pz = cz - B.tz;
+                if (box_d2(px, py, pz, B.hx, B.hy, B.hz) < r2) {
+                    float pn, vx, vy, vz;
+                    pair_hit(px, py, pz, r, B.c, B.s, B.hx, B.hy, B.hz, pn, vx, vy, vz);
+                    pen += pn;
+                    ++hits;
+                    if (GRAD) { gx = fmaf(-wl, vx, gx); gy = fmaf(-wl, vy, gy); gz = fmaf(-wl, vz, gz); }
+                }
+            }
+            if (KT != 1) {
+#pragma unroll 1
+                for (int j = 0; j < (KT ? KT : K); ++j) {
+                    const bool cand = om >> j & 1u;
+                    if (!__ballot(cand)) continue;   // wave-uniform
+                    const Box O = S.ob0[j];
+                    const float4 pl = S.plc[j * S.P + pp];
+                    const bool placed = j < kk;
+                    const float bx = placed ? pl.x : O.cx, by = placed ? pl.y : O.cy;
+                    const float bc = placed ? pl.z : O.c, bs = placed ? pl.w : O.s;
+                    const float dx = cx - bx, dy = cy - by;
+                    const float px = fmaf(bc, dx, bs * dy), py = fmaf(bc, dy, -(bs * dx)), pz = cz - O.cz;
+                    const bool act = cand && box_d2(px, py, pz, O.hx, O.hy, O.hz) < r2;
+                    float vx = 0.f, vy = 0.f, vz;
+                    if (act) {
+                        float pn;
+                        pair_hit(px, py, pz, r, bc, bs, O.hx, O.hy, O.hz, pn, vx, vy, vz);
+                        pen += pn;
+                        ++hits;
+                        if (GRAD) { gx = fmaf(-wl, vx, gx); gy = fmaf(-wl, vy, gy); gz = fmaf(-wl, vz, gz); }
+                    }
+                    if (GRAD) {
+                        // moving the box by d equals moving the sphere by -d; turning it
+                        // about its own vertical axis equals turning the sphere back
+                        const uint64_t moved = __ballot(act && placed);
+                        if (moved) {
+                            if (act && placed) {
+                                const float ax = -wl * vx, ay = -wl * vy;
+                                rec[lane] = make_float4(ax, ay, fmaf(dx, ay, -(dy * ax)), 0.f);
+                            }
+                            wave_sync();
+                            if (here) {
+                                uint32_t bits = (uint32_t)(moved >> (rel * nc)) & (CLASS << si);
+                                if (nc < 32) bits &= (1u << nc) - 1u;
+                                while (bits) {
+                                    const float4 v = rec[rel * nc + __builtin_ctz(bits)];
+                                    bits &= bits - 1u;
+                                    gr[3 * j] -= v.x;
+                                    gr[3 * j + 1] -= v.y;
+                                    gr[3 * j + 2] -= v.z;
+                                }
+                            }
+                            wave_sync();
+                        }
+                    }
+                }
+            }
+            const uint64_t any = __ballot(hits != 0);
+            if (any) {
+                if (hits != 0) {
+                    rec[2 * lane] = make_float4(pen, gx, gy, gz);
+                    rec[2 * lane + 1] = make_float4(fmaf(cy, gz, -(cz * gy)), fmaf(cz, gx, -(cx * gz)), fmaf(cx, gy, -(cy * gx)),
+                                                    __int_as_float(hits));
+                }
+                wave_sync();
+                if (here) {
+                    uint32_t bits = (uint32_t)(any >> (rel * nc)) & (CLASS << si);
+                    if (nc < 32) bits &= (1u << nc) - 1u;
+                    while (bits) {
+                        const float4* v = rec + 2 * (rel * nc + __builtin_ctz(bits));
+                        bits &= bits - 1u;
+                        const float4 u = v[0], m = v[1];
+                        coll += u.x;
+                        if (GRAD) {
+                            f[0] += u.y; f[1] += u.z; f[2] += u.w;
+                            tq[0] += m.x; tq[1] += m.y; tq[2] += m.z;
+                        } else {
+                            nhit += __float_as_int(m.w);
+                        }
+                    }
+                }
+                wave_sync();
+            }
         }
     }
 }
 
-// All robot spheres of link L: runs of run_len, then 2, then 1, over the
-// (wave-uniform) number of entries each lane of the slot handles, against the
-// boxes the link's bounding sphere may touch.
+// All robot spheres of link L (frame (R, t)).
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const float4* __restrict__ rsl,
-                                             const SBox* __restrict__ sbl, int L,
-                                             int si, const float R[9], const float t[3], const MoveCtx<KT>& mc,
-                                             float lam, float& coll, float f[3], float tq[3],
-                                             float* __restrict__ gr, int& nhit) {
-    const int s0 = T->link_start[L], s1 = T->link_start[L + 1];
-    if (s1 == s0) return;
-    const float4 lb = T->lbs[L];
+__device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const Joint& J, const TileLds& S, int K, int L, int si,
+                                             const float R[9], const float t[3], const MoveCtx<KT>& mc, float lam,
+                                             float& coll, float f[3], float tq[3], float* __restrict__ gr, int& nhit) {
+    const int s0 = J.s0, ns = J.ns;
+    if (ns == 0) return;
+    const float4 lb = J.lb;
     uint32_t smask, omask;
-    touched_boxes<KT, SPLIT>(T, sbl, si, mc, R[0] * lb.x + R[1] * lb.y + R[2] * lb.z + t[0],
-                      R[3] * lb.x + R[4] * lb.y + R[5] * lb.z + t[1], R[6] * lb.x + R[7] * lb.y + R[8] * lb.z + t[2],
-                      lb.w, smask, omask);
-    if (!(smask | omask)) return;   // wave-uniform: no sphere of the link touches any box
-    const int per_lane = (s1 - s0 + SPLIT - 1) / SPLIT;
-    int j = 0;
-    constexpr int RUN = run_len<KT>();
-    for (; j + RUN <= per_lane; j += RUN)
-        robot_run<KT, SPLIT, RUN, GRAD>(T, rsl, s0, s1, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
-    if (RUN > 2 && j + 2 <= per_lane) {
-        robot_run<KT, SPLIT, 2, GRAD>(T, rsl, s0, s1, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
-        j += 2;
-    }
-    for (; j < per_lane; ++j)
-        robot_run<KT, SPLIT, 1, GRAD>(T, rsl, s0, s1, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
+    touched_boxes<KT, SPLIT, true>(S, T->n_static, K, si, mc, S.ck + (L - 1) * (T->n_static + K),
+                                   R[0] * lb.x + R[1] * lb.y + R[2] * lb.z + t[0],
+                                   R[3] * lb.x + R[4] * lb.y + R[5] * lb.z + t[1],
+                                   R[6] * lb.x + R[7] * lb.y + R[8] * lb.z + t[2], lb.w, smask, omask);
+    sphere_set<KT, SPLIT, GRAD, false>(S, K, S.rs + s0, ns, si, R, t, mc, smask, omask, lam, coll, f, tq, gr,
+                                       nhit);
 }
 
-// Runs of object spheres (table osl, object frame) transformed by (R, t):
-// lane si takes entries si + SPLIT j.  Returns the penetration sum; with GRAD
-// accumulates the force and the moment about the world origin.
-template <int KT, int SPLIT, int NB, bool GRAD>
-__device__ __forceinline__ void object_run(const Tables* __restrict__ T, const float4* __restrict__ osl, int nos,
-                                           int j0, int si, const float R[9], const float t[3], const MoveCtx<KT>& mc,
-                                           uint32_t smask, uint32_t omask, float lam, float& coll, float f[3],
-                                           float tq[3], float* __restrict__ gr, int& nhit) {
-    float cx[NB], cy[NB], cz[NB], rr[NB], gx[NB], gy[NB], gz[NB];
-#pragma unroll
-    for (int m = 0; m < NB; ++m) {
-        const int e = si + SPLIT * (j0 + m);
-        const float4 sp = osl[min(e, nos - 1)];
-        rr[m] = e < nos ? sp.w : 0.f;
-        cx[m] = R[0] * sp.x + R[1] * sp.y + R[2] * sp.z + t[0];
-        cy[m] = R[3] * sp.x + R[4] * sp.y + R[5] * sp.z + t[1];
-        cz[m] = R[6] * sp.x + R[7] * sp.y + R[8] * sp.z + t[2];
-        gx[m] = gy[m] = gz[m] = 0.f;
-    }
-    // per-sphere sums over boxes, added to coll in sphere order: the same
-    // additions in the same order whatever the run length
-    float pen[NB];
-#pragma unroll
-    for (int m = 0; m < NB; ++m) pen[m] = 0.f;
-    run_vs_world<KT, NB, GRAD>(T, mc, smask, omask, cx, cy, cz, rr, lam, pen, gx, gy, gz, gr, nhit);
-#pragma unroll
-    for (int m = 0; m < NB; ++m) coll += pen[m];
-    if (GRAD) {
-#pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            f[0] += gx[m]; f[1] += gy[m]; f[2] += gz[m];
-            tq[0] += cy[m] * gz[m] - cz[m] * gy[m];
-            tq[1] += cz[m] * gx[m] - cx[m] * gz[m];
-            tq[2] += cx[m] * gy[m] - cy[m] * gx[m];
-        }
-    }
-}
-
+// The object spheres of this lane's step (frame (R, t)); use = false: this
+// lane has none here (every lane of the wave calls, so that all of them can
+// take tests).
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void object_spheres(const Tables* __restrict__ T, const SBox* __restrict__ sbl,
-                                               const float4* __restrict__ osl, int nos, float4 ob, int si, const float R[9], const float t[3],
-                                               const MoveCtx<KT>& mc, float lam, float& coll, float f[3],
-                                               float tq[3], float* __restrict__ gr, int& nhit) {
-    if (nos <= 0) return;
+__device__ __forceinline__ void object_spheres(const Tables* __restrict__ T, const TileLds& S, int K, bool use,
+                                               float4 ob, int si, const float R[9], const float t[3],
+                                               const MoveCtx<KT>& mc, float lam, float& coll, float f[3], float tq[3],
+                                               float* __restrict__ gr, int& nhit) {
+    if (T->n_os <= 0) return;
     uint32_t smask, omask;
-    touched_boxes<KT, SPLIT>(T, sbl, si, mc, R[0] * ob.x + R[1] * ob.y + R[2] * ob.z + t[0],
-                      R[3] * ob.x + R[4] * ob.y + R[5] * ob.z + t[1], R[6] * ob.x + R[7] * ob.y + R[8] * ob.z + t[2],
-                      ob.w, smask, omask);
-    if (!(smask | omask)) return;   // wave-uniform: the held object touches no box
-    const int per_lane = (nos + SPLIT - 1) / SPLIT;
-    int j = 0;
-    constexpr int RUN = run_len<KT>();
-    for (; j + RUN <= per_lane; j += RUN)
-        object_run<KT, SPLIT, RUN, GRAD>(T, osl, nos, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
-    if (RUN > 2 && j + 2 <= per_lane) {
-        object_run<KT, SPLIT, 2, GRAD>(T, osl, nos, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
-        j += 2;
-    }
-    for (; j < per_lane; ++j)
-        object_run<KT, SPLIT, 1, GRAD>(T, osl, nos, j, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
+    touched_boxes<KT, SPLIT, false>(S, T->n_static, K, si, mc, nullptr,
+                                    R[0] * ob.x + R[1] * ob.y + R[2] * ob.z + t[0],
+                                    R[3] * ob.x + R[4] * ob.y + R[5] * ob.z + t[1],
+                                    R[6] * ob.x + R[7] * ob.y + R[8] * ob.z + t[2], ob.w, smask, omask);
+    if (!use) smask = omask = 0u;
+    sphere_set<KT, SPLIT, GRAD, true>(S, K, S.osl, T->n_os, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
 }
 
 // dist_from_bounds of v against [lo, hi] and its gradient (scaled by lam).
@@ -452,6 +496,21 @@ __device__ __forceinline__ float bounds_dist(const float v[N], const float* lo, 
 // index La .. Lb-1) feels the wrench (g_b, c_b x g_b) through its axis S_j.
 // Per La, the b-side wrenches are summed by link and folded onto the axes as
 // in the world pass: dJ/dq_j = <S_j, W_total> - <S_j, W of links <= j>.
+
+// The joint of joint_advance, its products left to the compiler to fuse.
+__device__ __forceinline__ void self_advance(const Joint& J, float sn, float cs, float R[9], float t[3]) {
+    const float ca = J.ca, sa = J.sa, a = J.a, d = J.d;
+    const float lx = a * cs, ly = a * sn;
+#pragma unroll
+    for (int rr = 0; rr < 3; ++rr) {
+        const float r0 = R[3 * rr], r1 = R[3 * rr + 1], r2 = R[3 * rr + 2];
+        t[rr] += r0 * lx + r1 * ly + r2 * d;
+        const float w = r1 * cs - r0 * sn;
+        R[3 * rr] = r0 * cs + r1 * sn;
+        R[3 * rr + 1] = ca * w + r2 * sa;
+        R[3 * rr + 2] = r2 * ca - sa * w;
+    }
+}
 
 // NB consecutive spheres of link Lb of one lane (entries b0 + si + SPLIT j,
 // j = j0 .. j0+NB-1, in a frame (Q, o) relative to link La's frame) against
@@ -560,7 +619,7 @@ __device__ __forceinline__ void self_pass(const Tables* __restrict__ T, int si, 
         for (int j = 1; j < CT_N_JOINTS; ++j) {   // (Q, o) is frame j: joint j's axis (0-based)
             if (j < La) continue;                  // wave-uniform
             if (GRAD && j > La) gq[j] -= axis_dot(Q, o, F, Mo);
-            joint_advance(T, j, jsn[j], jcs[j], Q, o);
+            self_advance(T->jk[j], jsn[j], jcs[j], Q, o);
             if (j + 1 >= La + 2) self_block<SPLIT, GRAD>(T, La, j + 1, si, Q, o, lam, pen, F, Mo);
         }
         // the tool: frame 7 moved along its z-axis
@@ -573,7 +632,7 @@ __device__ __forceinline__ void self_pass(const Tables* __restrict__ T, int si, 
             for (int j = 1; j < CT_N_JOINTS; ++j) {
                 if (j < La) continue;
                 gq[j] += axis_dot(R, t, F, Mo);
-                if (j + 1 < CT_N_JOINTS) joint_advance(T, j, jsn[j], jcs[j], R, t);
+                if (j + 1 < CT_N_JOINTS) self_advance(T->jk[j], jsn[j], jcs[j], R, t);
             }
         }
     }
@@ -630,9 +689,9 @@ struct LaneOut {
 // world-frame wrenches: dJ/dq_j = z_j . tau + (o_j x z_j) . f for the wrench
 // of everything beyond joint j), and the grasp / placement partials gg, gr.
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const float4* __restrict__ rsl,
-                                            const SBox* __restrict__ sbl, const float4* __restrict__ osl_k, int si,
-                                            const float q[CT_N_JOINTS], bool held, bool kin, bool placing,
+__device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const TileLds& S, int K, int si,
+                                            const float jsn[CT_N_JOINTS], const float jcs[CT_N_JOINTS], bool held,
+                                            bool kin, bool placing,
                                             float lam, const MoveCtx<KT>& mc, float gx, float gy, float gz,
                                             float g_c, float g_s, float rho_x, float rho_y, float rho_c,
                                             float rho_s, float& coll, float gq[CT_N_JOINTS], float gg[4],
@@ -649,28 +708,29 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
     // of the largest, and the subtracted products are of that size.)
     float R[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f};
     float t[3] = {0.f, 0.f, 0.f};
-    float jsn[CT_N_JOINTS], jcs[CT_N_JOINTS], cj[CT_N_JOINTS];
+    float cj[CT_N_JOINTS];
     float f[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};   // wrench of the links done so far
-#pragma unroll 1
-    for (int i = 0; i < CT_N_JOINTS; ++i) {
-        if (GRAD) {
-            const float z[3] = {R[2], R[5], R[8]};
-            float m[3];
-            cross3(t, z, m);
-            cj[i] = z[0] * tq[0] + z[1] * tq[1] + z[2] * tq[2] + m[0] * f[0] + m[1] * f[1] + m[2] * f[2];
+    // links 1..7, then the tool (spheres of the tool frame, t = its origin)
+#pragma unroll CT_JOINT_UNROLL
+    for (int i = 0; i <= CT_N_JOINTS; ++i) {
+        const Joint J = T->jk[i];
+        if (i < CT_N_JOINTS) {
+            if (GRAD) {
+                const float z[3] = {R[2], R[5], R[8]};
+                float m[3];
+                cross3(t, z, m);
+                cj[i] = axis_wrench(z, m, f, tq);
+            }
+            joint_advance(J, jsn[i], jcs[i], R, t);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) t[j] = fmaf(R[3 * j + 2], T->tool_d, t[j]);
         }
-        float sn, cs;
-        sincosf(q[i] + T->th0[i], &sn, &cs);
-        jsn[i] = sn;
-        jcs[i] = cs;
-        joint_advance(T, i, sn, cs, R, t);
-        link_spheres<KT, SPLIT, GRAD>(T, rsl, sbl, i + 1, si, R, t, mc, lam, coll, f, tq, gr, nhit);
+        link_spheres<KT, SPLIT, GRAD>(T, J, S, K, i + 1, si, R, t, mc, lam, coll, f, tq, gr, nhit);
     }
-    // ---- tool frame: tool spheres, the held object, the kinematic constraint
-    const float te[3] = {t[0] + R[2] * T->tool_d, t[1] + R[5] * T->tool_d, t[2] + R[8] * T->tool_d};
-    link_spheres<KT, SPLIT, GRAD>(T, rsl, sbl, 8, si, R, te, mc, lam, coll, f, tq, gr, nhit);
+    const float* te = t;
 
-    if (held) {
+    if (__ballot(held)) {
         // held object frame O = F_ee G^-1, G = Trans(g) Rz(gyaw) Rx(pi); the
         // rotation H = Rz(gyaw) Rx(pi) is symmetric and its own inverse
         const float H[9] = {g_c, g_s, 0.f, g_s, -g_c, 0.f, 0.f, 0.f, -1.f};
@@ -684,9 +744,8 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
                              te[1] - (RO[3] * gx + RO[4] * gy + RO[5] * gz),
                              te[2] - (RO[6] * gx + RO[7] * gy + RO[8] * gz)};
         float fo[3] = {0.f, 0.f, 0.f}, to[3] = {0.f, 0.f, 0.f};
-        object_spheres<KT, SPLIT, GRAD>(T, sbl, osl_k, T->n_os, T->obs[k], si, RO, tO, mc, lam, coll, fo, to, gr,
-                                        nhit);
-        if (GRAD) {
+        object_spheres<KT, SPLIT, GRAD>(T, S, K, held, T->obs[k], si, RO, tO, mc, lam, coll, fo, to, gr, nhit);
+        if (GRAD && held) {
             // d/dg: every held point moves by -R_O dg;  d/dgyaw: the held
             // object turns about the tool z-axis through the tool origin
             gg[0] -= RO[0] * fo[0] + RO[3] * fo[1] + RO[6] * fo[2];
@@ -762,8 +821,9 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
             const float z[3] = {Q[2], Q[5], Q[8]};
             float m[3];
             cross3(o, z, m);
-            gq[i] += z[0] * tq[0] + z[1] * tq[1] + z[2] * tq[2] + m[0] * f[0] + m[1] * f[1] + m[2] * f[2] - cj[i];
-            if (i + 1 < CT_N_JOINTS) joint_advance(T, i, jsn[i], jcs[i], Q, o);
+            gq[i] += fmaf(m[2], f[2], fmaf(m[1], f[1], fmaf(m[0], f[0], fmaf(z[2], tq[2], fmaf(z[1], tq[1], z[0] * tq[0]))))) -
+                     cj[i];
+            if (i + 1 < CT_N_JOINTS) joint_advance(T->jk[i], jsn[i], jcs[i], Q, o);
         }
     }
     if (self) self_pass<SPLIT, GRAD>(T, si, jsn, jcs, slw ? slw->self : T->w[W_SELF], self_pen, gq);
@@ -786,11 +846,8 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
 // part[0 .. 18+3K): [0,7) own q, [7,11) grasp, [11, 11+3K) placements
 // (accumulated in place), [11+3K, 18+3K) foreign q.
 template <int KT, int SPLIT, int MODE, bool EXT>
-__device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const float* __restrict__ xs,
-                                             int xs_stride, const float4* __restrict__ plc,
-                                             const float4* __restrict__ osl, const float4* __restrict__ rsl,
-                                             const SBox* __restrict__ sbl, int K_rt, int slot, int si,
-                                             float* __restrict__ part, float* __restrict__ terms,
+__device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const TileLds& S, int K_rt, int p,
+                                             int slot, int si, float* __restrict__ part, float* __restrict__ terms,
                                              int64_t term_ld, int64_t i_glob, bool write_terms,
                                              const float* __restrict__ wts) {
     constexpr bool GRAD = MODE != MODE_COST;
@@ -810,6 +867,9 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     constexpr bool KIND_UNIFORM = KT > 0 && LANES_PER_SLOT % 64 == 0;
     const int k = STEP_UNIFORM ? __builtin_amdgcn_readfirstlane(slot >> 1) : slot >> 1;
     const bool placing = KIND_UNIFORM ? (__builtin_amdgcn_readfirstlane(slot) & 1) : (slot & 1);
+    const int xs_stride = S.P;
+    const float* xs = S.xs + p;
+    const float4* plc = S.plc + p;
     auto X = [&](int d) { return xs[d * xs_stride]; };
     const int b0 = CT_STEP_DIM * k;
     float* gr = part + 11;   // placement partials, this lane's own
@@ -827,13 +887,10 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
             const float4 pl = plc[j * xs_stride];
             mc.x[j] = placed ? pl.x : T->obj0[j].cx;
             mc.y[j] = placed ? pl.y : T->obj0[j].cy;
-            mc.c[j] = placed ? pl.z : T->obj0[j].c;
-            mc.s[j] = placed ? pl.w : T->obj0[j].s;
         }
-        mc.k = k;
-    } else {
-        mc = MoveCtx<0>{plc, xs_stride, K, k};
     }
+    mc.k = k;
+    mc.p = p;
     if (GRAD) {
         for (int j = 0; j < 3 * K; ++j) gr[j] = 0.f;
     }
@@ -853,25 +910,40 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     float gg[4] = {0.f, 0.f, 0.f, 0.f};
     float coll = 0.f, coll_m = 0.f, kin_pos = 0.f, kin_rot = 0.f, selfc = 0.f;
     int nhit = 0;   // touching sphere-box pairs (cost mode only; the adjoint's work)
-    const float4* osl_k = osl + k * CT_MAX_OBJ_SPHERES;
 
     // waypoints w = 1..W of the transition, then the configuration itself
     for (int w = 1; w <= W + 1; ++w) {
         const bool key = w == W + 1;   // wave-uniform
         const float s = key ? 1.f : (float)w / (float)(W + 1);
-        float q[CT_N_JOINTS], gw[CT_N_JOINTS];
+        // sines and cosines of the configuration's joint angles: the SPLIT
+        // lanes of the slot take every SPLIT-th joint and exchange them
+        float jsn[CT_N_JOINTS], jcs[CT_N_JOINTS], gw[CT_N_JOINTS];
 #pragma unroll
-        for (int j = 0; j < CT_N_JOINTS; ++j) {
+        for (int j0 = 0; j0 < CT_N_JOINTS; j0 += SPLIT) {
+            const int j = min(j0 + si, CT_N_JOINTS - 1);
+            float th0 = T->jk[j0].th0;
+#pragma unroll
+            for (int u = 1; u < SPLIT; ++u)
+                if (j0 + u < CT_N_JOINTS && si == u) th0 = T->jk[j0 + u].th0;
             const float b = qb(j);
-            q[j] = key ? b : qa(j) + s * (b - qa(j));
-            gw[j] = 0.f;
+            float q = b;
+            if (!key) {
+                const float a = start_is_var ? X(qa_row + j) : T->q0[j];
+                q = a + s * (b - a);
+            }
+            float sn, cs;
+            sincosf(q + th0, &sn, &cs);
+            split_bcast<SPLIT>(sn, j0, jsn);
+            split_bcast<SPLIT>(cs, j0, jcs);
         }
+#pragma unroll
+        for (int j = 0; j < CT_N_JOINTS; ++j) gw[j] = 0.f;
         float cw = 0.f;
         // the object is in the hand at both configurations of its step and
         // along the holding transition
         const bool held = key || placing;
         const float lam = key ? (sw ? sw->coll : T->w[W_COLL]) : (sw ? sw->mcoll : T->w[W_MCOLL]);
-        config_pass<KT, SPLIT, GRAD>(T, rsl, sbl, osl_k, si, q, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
+        config_pass<KT, SPLIT, GRAD>(T, S, K, si, jsn, jcs, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
                                      rho_c, rho_s, cw, gw, gg, gr, kin_pos, kin_rot, sw, key && self_on, selfc, nhit);
         if (key) coll += cw; else coll_m += cw;
         if (GRAD) {
@@ -923,21 +995,23 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
             grasp = bounds_dist<3>(gv, T->grasp_lo[k], T->grasp_hi[k], sw ? sw->grasp : T->w[W_GRASP], gb);
             if (GRAD) { gg[0] += gb[0]; gg[1] += gb[1]; gg[2] += gb[2]; }
         }
+    }
+    if (__ballot(!placing)) {
         // CFreePlace: the object's spheres at its placement P(rho_k); the
         // object frame's force and moment give the placement gradient
         const float Rp[9] = {rho_c, -rho_s, 0.f, rho_s, rho_c, 0.f, 0.f, 0.f, 1.f};
         const float tp[3] = {rho_x, rho_y, T->place_z[k]};
         float fp[3] = {0.f, 0.f, 0.f}, mp[3] = {0.f, 0.f, 0.f};
-        object_spheres<KT, SPLIT, GRAD>(T, sbl, osl_k, T->n_os, T->obs[k], si, Rp, tp, mc, lc, coll_obj, fp, mp, gr,
-                                        nhit);
-        if (GRAD) {
+        object_spheres<KT, SPLIT, GRAD>(T, S, K, !placing, T->obs[k], si, Rp, tp, mc, lc, coll_obj, fp, mp, gr, nhit);
+        if (GRAD && !placing) {
             // translation: the force; turning about the vertical through the
             // placement origin: z of the moment about that point
             gr[3 * k] += fp[0];
             gr[3 * k + 1] += fp[1];
             gr[3 * k + 2] += mp[2] - (tp[0] * fp[1] - tp[1] * fp[0]);
         }
-    } else if (si == 0) {
+    }
+    if (placing && si == 0) {
         // StablePlace containment: footprint corners inside the region
         const float hx = T->obj0[k].hx, hy = T->obj0[k].hy, lpl = sw ? sw->place : T->w[W_PLACE];
 #pragma unroll
@@ -985,7 +1059,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
 #pragma unroll
         for (int j = 0; j < CT_N_JOINTS; ++j) {
             part[j] = gq[j];
-            part[11 + 3 * K + j] = gqa[j];
+            if (W > 0) part[11 + 3 * K + j] = gqa[j];
             gsum += gq[j] + gqa[j];
         }
 #pragma unroll
@@ -1045,30 +1119,35 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
 // ---------------------------------------------------------------------------
 // Workgroup-level tile: P particles x 2K slots x SPLIT lanes, K at run time.
 
-// Largest LDS footprint over K = 1..CT_MAX_STEPS for a given SPLIT:
-//   staged particles  D P = 21 K floor(128 / (K SPLIT))  <= 2688 / SPLIT floats
-//   placements        K P                                <= 128 / SPLIT float4
-//   lane partials     P 2K SPLIT (18 + 3K)                <= 256 (18 + 3 * 6) floats
-//   slot records      P 2K                                <= 256 / SPLIT
-//   staged moments    2 D P (fused step only; the same bound as the particles)
-template <int SPLIT>
-struct TileSmem {
-    float xs[2688 / SPLIT];
-    float ms[2688 / SPLIT], vs[2688 / SPLIT];
-    uint8_t frz[CT_MAX_STEPS * CT_STEP_DIM];
-    float4 rs[CT_MAX_ROBOT_SPHERES];
-    SBox sbx[CT_MAX_STATIC_BOXES];
-    float4 plc[128 / SPLIT];
-    float part[WG * (18 + 3 * CT_MAX_STEPS)];
-    float cpart[WG / SPLIT];
-    float tpart[WG / SPLIT];
-    int flg[WG / SPLIT];
-    int hpart[WG / SPLIT];
-    int okp[128 / SPLIT];
-    float4 osl[CT_MAX_STEPS * CT_MAX_OBJ_SPHERES];
-    int any_sat;
-    int halt;
-};
+// LDS of a tile (dynamic; the host passes tile_layout(...).total).  At K = 4,
+// 60 robot spheres and 9 static boxes a fused step without waypoints takes 75
+// KB at SPLIT 1 and 53 KB at SPLIT 2: two workgroups per compute unit.
+__device__ __forceinline__ TileLds tile_lds(char* base, const TileLayout& o, int P) {
+    TileLds S;
+    S.xs = (float*)(base + o.xs);
+    S.ms = (float*)(base + o.ms);
+    S.vs = (float*)(base + o.vs);
+    S.part = (float*)(base + o.part);
+    S.plc = (float4*)(base + o.plc);
+    S.rs = (float4*)(base + o.rs);
+    S.osl = (float4*)(base + o.osl);
+    S.sbx = (SBox*)(base + o.sbx);
+    S.cbx = (CullBox*)(base + o.cbx);
+    S.ck = (float2*)(base + o.ck);
+    S.ob0 = (Box*)(base + o.ob0);
+    S.cpart = (float*)(base + o.cpart);
+    S.tpart = (float*)(base + o.tpart);
+    S.flg = (int*)(base + o.flg);
+    S.hpart = (int*)(base + o.hpart);
+    S.okp = (int*)(base + o.okp);
+    S.frz = (uint8_t*)(base + o.frz);
+    S.ctl = (int*)(base + o.ctl);
+    S.bc = (float2*)(base + o.bc);
+    S.wave = (float4*)(base + o.wave);
+    S.np = o.np;
+    S.P = P;
+    return S;
+}
 
 // What one tile reads and writes (one skeleton's buffers).
 struct TileIO {
@@ -1098,7 +1177,7 @@ struct TileIO {
 // tile's tail every time.  cost and mask are those of the last iteration.
 // Returns the number of iterations run (stop-at-first may leave early).
 template <int KT, int SPLIT, int MODE, bool EXT>
-__device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<SPLIT>& sm, float lr, float b1,
+__device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds, float lr, float b1,
                                         float b2, float eps, int32_t t, int iters) {
     const Tables* __restrict__ T = io.T;
     const int K = KT ? KT : T->K;
@@ -1106,19 +1185,26 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
     const int LPP = SLOTS * SPLIT;
     const int P = WG / LPP;
     const int D = CT_STEP_DIM * K;
-    const int NP = 18 + 3 * K;
     const int64_t n = io.n, ld = io.ld;
     const int tid = threadIdx.x;
 
+    const int W = T->W, nsb = T->n_static;
+    const TileLayout lay = tile_layout(K, SPLIT, MODE, W, nsb, T->link_start[9]);
+    const TileLds S = tile_lds(lds, lay, P);
+    const int NP = S.np;
+    // moments in LDS, or (waypoints: the partials leave no room) read and
+    // written in place by every iteration
+    constexpr bool MV = MODE == MODE_STEP;
+    const bool mv_lds = MV && W == 0;
+
     // phase 0: stage this tile's particles (coalesced along particles) and,
-    // for the fused step, their Adam moments and the frozen flags; the
-    // placements' poses, and the robot and object sphere tables.  A lane
-    // issues all of its loads before the first wait (NST is an upper bound
-    // on its share; with the skeleton length known at compile time, exact),
-    // so the tile pays one memory latency here and none in phase 2.
+    // for the fused step, their Adam moments and the frozen flags, and the
+    // problem's tables.  A lane issues all of its loads before the first wait
+    // (NST is an upper bound on its share; with the skeleton length known at
+    // compile time, exact), so the tile pays one memory latency here and none
+    // in phase 2.
     {
         constexpr int NST = (KT ? CT_STEP_DIM * KT * tile_particles(KT, SPLIT) : 2688 / SPLIT) / WG + 1;
-        constexpr bool MV = MODE == MODE_STEP;
         float xv[NST], mv[NST], vv[NST];
 #pragma unroll
         for (int u = 0; u < NST; ++u) {
@@ -1130,30 +1216,38 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
                 const int64_t a = d * ld + i;
                 if (MV && io.redo) {
                     xv[u] = io.Xb[a]; mv[u] = io.Mb[a]; vv[u] = io.Vb[a];
+                    if (!mv_lds) { io.M[a] = mv[u]; io.V[a] = vv[u]; }
                 } else {
                     xv[u] = io.X[a];
-                    if (MV) { mv[u] = io.M[a]; vv[u] = io.V[a]; }
+                    if (MV && (mv_lds || io.Xb)) { mv[u] = io.M[a]; vv[u] = io.V[a]; }
                     if (MV && io.Xb) { io.Xb[a] = xv[u]; io.Mb[a] = mv[u]; io.Vb[a] = vv[u]; }
                 }
             }
         }
-        if (MV && tid < D) sm.frz[tid] = io.frozen ? io.frozen[tid] : 0;
+        if (MV && tid < D) S.frz[tid] = io.frozen ? io.frozen[tid] : 0;
 #pragma unroll
         for (int u = 0; u < NST; ++u) {
             const int idx = tid + u * WG;
             if (idx < D * P) {
-                sm.xs[idx] = xv[u];
-                if (MV) { sm.ms[idx] = mv[u]; sm.vs[idx] = vv[u]; }
+                S.xs[idx] = xv[u];
+                if (mv_lds) { S.ms[idx] = mv[u]; S.vs[idx] = vv[u]; }
             }
         }
     }
     for (int idx = tid; idx < K * CT_MAX_OBJ_SPHERES; idx += WG)
-        sm.osl[idx] = T->os[idx / CT_MAX_OBJ_SPHERES][idx % CT_MAX_OBJ_SPHERES];
-    for (int idx = tid; idx < T->link_start[9]; idx += WG) sm.rs[idx] = T->rs[idx];
-    if (tid < T->n_static) sm.sbx[tid] = T->sbox[tid];
+        S.osl[idx] = T->os[idx / CT_MAX_OBJ_SPHERES][idx % CT_MAX_OBJ_SPHERES];
+    for (int idx = tid; idx < T->link_start[9]; idx += WG) S.rs[idx] = T->rs[idx];
+    for (int idx = tid; idx < 8 * (nsb + K); idx += WG) S.ck[idx] = T->ck[idx];
+    if (tid < nsb + K) S.cbx[tid] = T->cbx[tid];
+    if (tid < nsb) S.sbx[tid] = T->sbox[tid];
+    if (tid < K) S.ob0[tid] = T->obj0[tid];
+    if (MV && tid >= WG - MAX_LAUNCH_ITERS) {
+        const int u = tid - (WG - MAX_LAUNCH_ITERS);
+        if (u < iters) S.bc[u] = make_float2(1.f - powf(b1, (float)(t + u)), 1.f - powf(b2, (float)(t + u)));
+    }
     if (tid == 0) {
-        sm.any_sat = 0;
-        sm.halt = 0;
+        S.ctl[0] = 0;   // some particle of the tile satisfies
+        S.ctl[1] = 0;   // leave the loop
     }
     __syncthreads();
 
@@ -1162,20 +1256,20 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
     float J = 0.f;   // cost and mask of the iteration (lanes tid < P)
     int m = 0;
     for (;;) {
-        const int32_t tn = t + done, iter = tn - 1;   // update number of this iteration, its 0-based index
+        const int32_t iter = t + done - 1;   // 0-based index of this iteration
         const bool last = MODE != MODE_STEP || done + 1 == iters;
         // stop-at-first: an earlier iteration of another tile found a particle
         if (MODE == MODE_STEP && io.stop && tid == 0)
-            sm.halt = __hip_atomic_load(io.first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < iter ? 1 : 0;
+            S.ctl[1] = __hip_atomic_load(io.first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < iter ? 1 : 0;
         for (int idx = tid; idx < K * P; idx += WG) {
             const int j = idx / P, p = idx - j * P;
-            const float* col = sm.xs + p;
+            const float* col = S.xs + p;
             float sj, cj;
             sincosf(col[(CT_STEP_DIM * j + 20) * P], &sj, &cj);
-            sm.plc[idx] = make_float4(col[(CT_STEP_DIM * j + 18) * P], col[(CT_STEP_DIM * j + 19) * P], cj, sj);
+            S.plc[idx] = make_float4(col[(CT_STEP_DIM * j + 18) * P], col[(CT_STEP_DIM * j + 19) * P], cj, sj);
         }
         __syncthreads();
-        if (MODE == MODE_STEP && sm.halt) break;   // workgroup-uniform
+        if (MODE == MODE_STEP && S.ctl[1]) break;   // workgroup-uniform
 
         // phase 1: every lane evaluates its slot.  Lanes are slot-major (the SPLIT
         // lanes of a slot adjacent, then the tile's particles, then the slots), so
@@ -1187,14 +1281,20 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
             if (slot < SLOTS) {
                 const int64_t i = p0 + p;
                 const bool wt = (MODE == MODE_COST) && io.terms != nullptr && i < n;
-                const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(T, sm.xs + p, P, sm.plc + p, sm.osl, sm.rs, sm.sbx, K, slot, si,
-                                                         sm.part + (size_t)((p * SLOTS + slot) * SPLIT + si) * NP,
-                                                         io.terms, ld, i, wt, i < n ? io.wts : nullptr);
+                // the table pointer is made opaque per iteration: hoisted out of
+                // the loop, the tables' values would not fit the registers
+                // (constant address space: they are read with scalar loads)
+                uint64_t Ta = (uint64_t)T;
+                asm volatile("" : "+s"(Ta));
+                const Tables* Ti = (const Tables*)(const __attribute__((address_space(4))) Tables*)Ta;
+                const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(Ti, S, K, p, slot, si,
+                                                                  S.part + ((p * SLOTS + slot) * SPLIT + si) * NP,
+                                                                  io.terms, ld, i, wt, i < n ? io.wts : nullptr);
                 if (si == 0) {
-                    sm.cpart[p * SLOTS + slot] = o.cost;
-                    sm.tpart[p * SLOTS + slot] = o.traj;
-                    sm.flg[p * SLOTS + slot] = o.flags;
-                    if (MODE == MODE_COST) sm.hpart[p * SLOTS + slot] = o.hits;
+                    S.cpart[p * SLOTS + slot] = o.cost;
+                    if (W > 0) S.tpart[p * SLOTS + slot] = o.traj;
+                    S.flg[p * SLOTS + slot] = o.flags;
+                    if (MODE == MODE_COST) S.hpart[p * SLOTS + slot] = o.hits;
                 }
             }
         }
@@ -1207,56 +1307,57 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
             J = 0.f;
             m = 1;
             for (int s = 0; s < SLOTS; ++s) {
-                J += sm.cpart[tid * SLOTS + s];
-                m &= sm.flg[tid * SLOTS + s] & 1;
-                ok &= (sm.flg[tid * SLOTS + s] >> 1) & 1;
+                J += S.cpart[tid * SLOTS + s];
+                m &= S.flg[tid * SLOTS + s] & 1;
+                ok &= (S.flg[tid * SLOTS + s] >> 1) & 1;
             }
             ok &= __builtin_isfinite(J) ? 1 : 0;
             m &= __builtin_isfinite(J) ? 1 : 0;
             // the solution returned on stop is the satisfying iterate itself
             // (the pre-update x the mask describes), so it keeps its value
-            sm.okp[tid] = ok & (io.stop ? 1 - m : 1);
+            S.okp[tid] = ok & (io.stop ? 1 - m : 1);
             if (i < n) {
                 if (MODE == MODE_COST && io.terms && T->traj_term >= 0) {
                     float tl = 0.f;
-                    for (int s = 0; s < SLOTS; ++s) tl += sm.tpart[tid * SLOTS + s];
+                    for (int s = 0; s < SLOTS; ++s) tl += S.tpart[tid * SLOTS + s];
                     io.terms[(int64_t)T->traj_term * ld + i] = tl;
                 }
                 if (MODE == MODE_COST && io.hits) {
                     int h = 0;
-                    for (int s = 0; s < SLOTS; ++s) h += sm.hpart[tid * SLOTS + s];
+                    for (int s = 0; s < SLOTS; ++s) h += S.hpart[tid * SLOTS + s];
                     io.hits[i] = h;
                 }
-                if (m) sm.any_sat = 1;
+                if (m) S.ctl[0] = 1;
             }
         }
         __syncthreads();
-        const bool sat = sm.any_sat;   // workgroup-uniform; stays set: only the first iteration counts
+        const bool sat = S.ctl[0];   // workgroup-uniform; stays set: only the first iteration counts
         if (sat && !reported && io.first_sat && !io.redo && tid == 0) atomicMin(io.first_sat, iter);
         reported = reported || sat;
 
         if (MODE != MODE_COST) {
             // phase 2: sum each coordinate's partials over slots and split lanes
             // in a fixed order, then write G or apply Adam in place
-            const float bc1 = 1.f - powf(b1, (float)tn), bc2 = 1.f - powf(b2, (float)tn);
+            const float2 bc = MODE == MODE_STEP ? S.bc[done] : make_float2(1.f, 1.f);
+            const float bc1 = bc.x, bc2 = bc.y;
             const int FQ = 11 + 3 * K;   // foreign-configuration partials
             for (int idx = tid; idx < D * P; idx += WG) {
                 const int d = idx / P, p = idx - d * P;
                 const int64_t i = p0 + p;
                 if (i >= n) continue;
                 const int k = d / CT_STEP_DIM, r = d - CT_STEP_DIM * k;
-                const float* pp = sm.part + (size_t)p * SLOTS * SPLIT * NP;
-                auto lane = [&](int slot, int si) { return pp + (size_t)(slot * SPLIT + si) * NP; };
+                const float* pp = S.part + p * SLOTS * SPLIT * NP;
+                auto lane = [&](int slot, int si) { return pp + (slot * SPLIT + si) * NP; };
                 float g = 0.f;
 #pragma unroll
                 for (int si = 0; si < SPLIT; ++si) {
                     if (r < 7) {
-                        // q_grasp of step k: its slot, plus the start of the holding transition
-                        g += lane(2 * k, si)[r] + lane(2 * k + 1, si)[FQ + r];
+                        // q_grasp of step k: its slot, plus (waypoints) the start of the holding transition
+                        g += lane(2 * k, si)[r] + (W > 0 ? lane(2 * k + 1, si)[FQ + r] : 0.f);
                     } else if (r < 14) {
-                        // q_place of step k: its slot, plus the start of the next free transition
+                        // q_place of step k: its slot, plus (waypoints) the start of the next free transition
                         g += lane(2 * k + 1, si)[r - 7];
-                        if (k + 1 < K) g += lane(2 * k + 2, si)[FQ + (r - 7)];
+                        if (W > 0 && k + 1 < K) g += lane(2 * k + 2, si)[FQ + (r - 7)];
                     } else if (r < 18) {
                         g += lane(2 * k, si)[7 + (r - 14)] + lane(2 * k + 1, si)[7 + (r - 14)];
                     } else {
@@ -1266,15 +1367,21 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
                 if (MODE == MODE_GRAD) {
                     const int64_t a = d * ld + i;
                     io.G[a] = io.gw ? io.gw[i] * g : g;
-                } else if (!sm.frz[d]) {
-                    if (!sm.okp[p]) continue;
+                } else if (!S.frz[d]) {
+                    if (!S.okp[p]) continue;
+                    const int64_t a = d * ld + i;
                     const float gs = io.gscale * g;
-                    const float m1 = b1 * sm.ms[idx] + (1.f - b1) * gs;
-                    const float v1 = b2 * sm.vs[idx] + (1.f - b2) * gs * gs;
+                    const float m1 = b1 * (mv_lds ? S.ms[idx] : io.M[a]) + (1.f - b1) * gs;
+                    const float v1 = b2 * (mv_lds ? S.vs[idx] : io.V[a]) + (1.f - b2) * gs * gs;
                     const float mh = m1 / bc1, vh = v1 / bc2;
-                    sm.xs[idx] = sm.xs[idx] - lr * mh / (sqrtf(vh) + eps);
-                    sm.ms[idx] = m1;
-                    sm.vs[idx] = v1;
+                    S.xs[idx] = S.xs[idx] - lr * mh / (sqrtf(vh) + eps);
+                    if (mv_lds) {
+                        S.ms[idx] = m1;
+                        S.vs[idx] = v1;
+                    } else {
+                        io.M[a] = m1;
+                        io.V[a] = v1;
+                    }
                 }
             }
         }
@@ -1292,11 +1399,13 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
         for (int idx = tid; idx < D * P; idx += WG) {
             const int d = idx / P, p = idx - d * P;
             const int64_t i = p0 + p;
-            if (i >= n || sm.frz[d]) continue;
+            if (i >= n || S.frz[d]) continue;
             const int64_t a = d * ld + i;
-            io.X[a] = sm.xs[idx];
-            io.M[a] = sm.ms[idx];
-            io.V[a] = sm.vs[idx];
+            io.X[a] = S.xs[idx];
+            if (mv_lds) {
+                io.M[a] = S.ms[idx];
+                io.V[a] = S.vs[idx];
+            }
         }
     }
     return done;
@@ -1311,13 +1420,13 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, TileSmem<S
 // iteration again, from the copy, up to it; when no particle was found in the
 // launch it returns at once.  A launch of one iteration needs neither.
 template <int SPLIT, int MODE, int KT, bool EXT>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void particle_kernel(
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPE))) void particle_kernel(
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
     float* __restrict__ G, float* __restrict__ cost, float* __restrict__ terms, uint8_t* __restrict__ mask,
     int32_t* __restrict__ first_sat, const uint8_t* __restrict__ frozen, int64_t n, int64_t ld, float lr,
     float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, StopArgs stop, const float* __restrict__ gw,
     const float* __restrict__ wts, int32_t* __restrict__ hits) {
-    __shared__ TileSmem<SPLIT> sm;
+    extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int run = iters;
     if (MODE == MODE_STEP && stop.on) {
         // every workgroup takes the same branch: this launch only writes
@@ -1344,7 +1453,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
         io.redo = stop.redo;
     }
     const int ran =
-        run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT), sm, lr, b1, b2, eps, t, run);
+        run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT), tile_mem, lr, b1, b2, eps, t, run);
     if (MODE == MODE_STEP && stop.ran && !stop.redo && threadIdx.x == 0) stop.ran[blockIdx.x] = ran;
 }
 
@@ -1355,12 +1464,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
 // run every iteration of an item before they take the next; the last
 // workgroup to leave resets the queue for the next launch.
 template <int SPLIT, bool EXT>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void batch_kernel(const BatchSkel* __restrict__ skels,
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPB))) void batch_kernel(const BatchSkel* __restrict__ skels,
                                                    const int2* __restrict__ items, int32_t n_items,
                                                    int32_t* __restrict__ queue, float lr, float b1, float b2,
                                                    float eps, int32_t t, int32_t iters) {
-    __shared__ TileSmem<SPLIT> sm;
-    __shared__ int item_s;
+    extern __shared__ __attribute__((aligned(16))) char tile_mem[];
+    int& item_s = *(int*)tile_mem;   // ahead of the tile's own LDS
     for (;;) {
         if (threadIdx.x == 0) item_s = atomicAdd(&queue[0], 1);
         __syncthreads();
@@ -1373,7 +1482,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ba
         const BatchSkel& b = skels[w.x];
         const TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
                         b.n, b.ld, b.gscale};
-        run_tile<0, SPLIT, MODE_STEP, EXT>(io, (int64_t)w.y * tile_particles(b.T->K, SPLIT), sm, lr, b1, b2, eps, t,
+        run_tile<0, SPLIT, MODE_STEP, EXT>(io, (int64_t)w.y * tile_particles(b.T->K, SPLIT), tile_mem + 16, lr, b1, b2, eps, t,
                                            iters);
         __syncthreads();
     }
