@@ -27,16 +27,6 @@
 
 #include "ct_tables.hpp"
 
-#ifndef CT_JOINT_UNROLL
-#define CT_JOINT_UNROLL 1
-#endif
-#ifndef CT_WPE
-#define CT_WPE 2
-#endif
-#ifndef CT_WPB
-#define CT_WPB 2
-#endif
-
 namespace ct {
 
 
@@ -90,18 +80,12 @@ __device__ __forceinline__ void pair_hit(float px, float py, float pz, float r, 
 
 // The centres of the moved objects as one lane's step k sees them, for the
 // culling tests: object j (j < K) was placed by an earlier step (at P(rho_j),
-// a particle variable) or is still at its initial pose.  With the skeleton
-// length known at compile time the lane keeps the K centres in registers;
-// KT = 0 (the many-skeleton kernel) reads them from the tile's LDS.
+// a particle variable) or is still at its initial pose.  The lane keeps the
+// K centres in registers.
 template <int KT>
 struct MoveCtx {
     float x[KT], y[KT];
     int k, p;   // step, particle of the tile
-};
-
-template <>
-struct MoveCtx<0> {
-    int k, p;
 };
 
 // Bijection from the launch index to a tile index that keeps each XCD's
@@ -233,7 +217,7 @@ __device__ __forceinline__ uint32_t split_or(uint32_t v) {
 // L >= 0: robot link L (thresholds from the table); L < 0: an object's sphere
 // of radius rb (thresholds formed here).
 template <int KT, int SPLIT, bool LINK>
-__device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int K, int si, const MoveCtx<KT>& mc,
+__device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si, const MoveCtx<KT>& mc,
                                               const float2* __restrict__ ck, float wx, float wy, float wz, float rb,
                                               uint32_t& smask, uint32_t& omask) {
     const float q = wx * wx + wy * wy;
@@ -259,7 +243,7 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int K, 
     smask = split_or<SPLIT>(smask) & (nsb < 32 ? (1u << nsb) - 1u : ~0u);
     if (KT == 1) return;   // the only moved object is the one in the hand
 #pragma unroll
-    for (int j = 0; j < (KT ? KT : K); ++j) {
+    for (int j = 0; j < KT; ++j) {
         const CullBox C = S.cbx[nsb + j];
         float2 th;
         if (LINK) {
@@ -268,17 +252,7 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int K, 
             const float e = rb + C.r;
             th = make_float2(e * e * 1.000001f, rb + C.hz);
         }
-        float bx, by;
-        if constexpr (KT > 0) {
-            bx = mc.x[j];
-            by = mc.y[j];
-        } else {
-            const float4 pl = S.plc[j * S.P + mc.p];
-            const bool placed = j < mc.k;
-            bx = placed ? pl.x : C.m2x;
-            by = placed ? pl.y : C.m2y;
-        }
-        const float dx = wx - bx, dy = wy - by;
+        const float dx = wx - mc.x[j], dy = wy - mc.y[j];
         const bool hit = dx * dx + dy * dy < th.x && fabsf(wz - C.z) < th.y;
         omask |= hit ? 1u << j : 0u;
     }
@@ -293,7 +267,7 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int K, 
 // partials gr.  The active lanes of the wave are its first lanes (at least
 // 48: tiles leave at most the tail of the last wave idle).
 template <int KT, int SPLIT, bool GRAD, bool OBJ>
-__device__ __forceinline__ void sphere_set(const TileLds& S, int K, const float4* __restrict__ tab, int ns, int si,
+__device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __restrict__ tab, int ns, int si,
                                            const float R[9], const float t[3], const MoveCtx<KT>& mc, uint32_t smask,
                                            uint32_t omask, float lam, float& coll, float f[3], float tq[3],
                                            float* __restrict__ gr, int& nhit) {
@@ -355,7 +329,7 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, int K, const float4
             }
             if (KT != 1) {
 #pragma unroll 1
-                for (int j = 0; j < (KT ? KT : K); ++j) {
+                for (int j = 0; j < KT; ++j) {
                     const bool cand = om >> j & 1u;
                     if (!__ballot(cand)) continue;   // wave-uniform
                     const Box O = S.ob0[j];
@@ -432,18 +406,18 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, int K, const float4
 
 // All robot spheres of link L (frame (R, t)).
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const Joint& J, const TileLds& S, int K, int L, int si,
+__device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const Joint& J, const TileLds& S, int L, int si,
                                              const float R[9], const float t[3], const MoveCtx<KT>& mc, float lam,
                                              float& coll, float f[3], float tq[3], float* __restrict__ gr, int& nhit) {
     const int s0 = J.s0, ns = J.ns;
     if (ns == 0) return;
     const float4 lb = J.lb;
     uint32_t smask, omask;
-    touched_boxes<KT, SPLIT, true>(S, T->n_static, K, si, mc, S.ck + (L - 1) * (T->n_static + K),
+    touched_boxes<KT, SPLIT, true>(S, T->n_static, si, mc, S.ck + (L - 1) * (T->n_static + KT),
                                    R[0] * lb.x + R[1] * lb.y + R[2] * lb.z + t[0],
                                    R[3] * lb.x + R[4] * lb.y + R[5] * lb.z + t[1],
                                    R[6] * lb.x + R[7] * lb.y + R[8] * lb.z + t[2], lb.w, smask, omask);
-    sphere_set<KT, SPLIT, GRAD, false>(S, K, S.rs + s0, ns, si, R, t, mc, smask, omask, lam, coll, f, tq, gr,
+    sphere_set<KT, SPLIT, GRAD, false>(S, S.rs + s0, ns, si, R, t, mc, smask, omask, lam, coll, f, tq, gr,
                                        nhit);
 }
 
@@ -451,18 +425,18 @@ __device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const
 // lane has none here (every lane of the wave calls, so that all of them can
 // take tests).
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void object_spheres(const Tables* __restrict__ T, const TileLds& S, int K, bool use,
+__device__ __forceinline__ void object_spheres(const Tables* __restrict__ T, const TileLds& S, bool use,
                                                float4 ob, int si, const float R[9], const float t[3],
                                                const MoveCtx<KT>& mc, float lam, float& coll, float f[3], float tq[3],
                                                float* __restrict__ gr, int& nhit) {
     if (T->n_os <= 0) return;
     uint32_t smask, omask;
-    touched_boxes<KT, SPLIT, false>(S, T->n_static, K, si, mc, nullptr,
+    touched_boxes<KT, SPLIT, false>(S, T->n_static, si, mc, nullptr,
                                     R[0] * ob.x + R[1] * ob.y + R[2] * ob.z + t[0],
                                     R[3] * ob.x + R[4] * ob.y + R[5] * ob.z + t[1],
                                     R[6] * ob.x + R[7] * ob.y + R[8] * ob.z + t[2], ob.w, smask, omask);
     if (!use) smask = omask = 0u;
-    sphere_set<KT, SPLIT, GRAD, true>(S, K, S.osl, T->n_os, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
+    sphere_set<KT, SPLIT, GRAD, true>(S, S.osl, T->n_os, si, R, t, mc, smask, omask, lam, coll, f, tq, gr, nhit);
 }
 
 // dist_from_bounds of v against [lo, hi] and its gradient (scaled by lam).
@@ -689,7 +663,7 @@ struct LaneOut {
 // world-frame wrenches: dJ/dq_j = z_j . tau + (o_j x z_j) . f for the wrench
 // of everything beyond joint j), and the grasp / placement partials gg, gr.
 template <int KT, int SPLIT, bool GRAD>
-__device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const TileLds& S, int K, int si,
+__device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const TileLds& S, int si,
                                             const float jsn[CT_N_JOINTS], const float jcs[CT_N_JOINTS], bool held,
                                             bool kin, bool placing,
                                             float lam, const MoveCtx<KT>& mc, float gx, float gy, float gz,
@@ -711,7 +685,7 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
     float cj[CT_N_JOINTS];
     float f[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};   // wrench of the links done so far
     // links 1..7, then the tool (spheres of the tool frame, t = its origin)
-#pragma unroll CT_JOINT_UNROLL
+#pragma unroll 1
     for (int i = 0; i <= CT_N_JOINTS; ++i) {
         const Joint J = T->jk[i];
         if (i < CT_N_JOINTS) {
@@ -726,7 +700,7 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
 #pragma unroll
             for (int j = 0; j < 3; ++j) t[j] = fmaf(R[3 * j + 2], T->tool_d, t[j]);
         }
-        link_spheres<KT, SPLIT, GRAD>(T, J, S, K, i + 1, si, R, t, mc, lam, coll, f, tq, gr, nhit);
+        link_spheres<KT, SPLIT, GRAD>(T, J, S, i + 1, si, R, t, mc, lam, coll, f, tq, gr, nhit);
     }
     const float* te = t;
 
@@ -744,7 +718,7 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
                              te[1] - (RO[3] * gx + RO[4] * gy + RO[5] * gz),
                              te[2] - (RO[6] * gx + RO[7] * gy + RO[8] * gz)};
         float fo[3] = {0.f, 0.f, 0.f}, to[3] = {0.f, 0.f, 0.f};
-        object_spheres<KT, SPLIT, GRAD>(T, S, K, held, T->obs[k], si, RO, tO, mc, lam, coll, fo, to, gr, nhit);
+        object_spheres<KT, SPLIT, GRAD>(T, S, held, T->obs[k], si, RO, tO, mc, lam, coll, fo, to, gr, nhit);
         if (GRAD && held) {
             // d/dg: every held point moves by -R_O dg;  d/dgyaw: the held
             // object turns about the tool z-axis through the tool origin
@@ -846,12 +820,12 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
 // part[0 .. 18+3K): [0,7) own q, [7,11) grasp, [11, 11+3K) placements
 // (accumulated in place), [11+3K, 18+3K) foreign q.
 template <int KT, int SPLIT, int MODE, bool EXT>
-__device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const TileLds& S, int K_rt, int p,
+__device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const TileLds& S, int p,
                                              int slot, int si, float* __restrict__ part, float* __restrict__ terms,
                                              int64_t term_ld, int64_t i_glob, bool write_terms,
                                              const float* __restrict__ wts) {
     constexpr bool GRAD = MODE != MODE_COST;
-    const int K = KT ? KT : K_rt;
+    constexpr int K = KT;
     const bool self_on = EXT && T->self_on;   // wave-uniform; compiled out without EXT
     // per-particle weights only in extended kernels; plain kernels read lambda
     // from the tables where each term needs it
@@ -862,9 +836,9 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     // the step, and at K = 1, 2 also the slot kind, is the same for every
     // lane of a wave: say so, so that step-indexed tables are scalar loads
     // and the kind's branches are uniform.
-    constexpr int LANES_PER_SLOT = KT ? tile_particles(KT, SPLIT) * SPLIT : 1;
-    constexpr bool STEP_UNIFORM = KT > 0 && (2 * LANES_PER_SLOT) % 64 == 0;
-    constexpr bool KIND_UNIFORM = KT > 0 && LANES_PER_SLOT % 64 == 0;
+    constexpr int LANES_PER_SLOT = tile_particles(KT, SPLIT) * SPLIT;
+    constexpr bool STEP_UNIFORM = (2 * LANES_PER_SLOT) % 64 == 0;
+    constexpr bool KIND_UNIFORM = LANES_PER_SLOT % 64 == 0;
     const int k = STEP_UNIFORM ? __builtin_amdgcn_readfirstlane(slot >> 1) : slot >> 1;
     const bool placing = KIND_UNIFORM ? (__builtin_amdgcn_readfirstlane(slot) & 1) : (slot & 1);
     const int xs_stride = S.P;
@@ -880,14 +854,12 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     const float4 own = plc[k * xs_stride];
     const float rho_x = own.x, rho_y = own.y, rho_c = own.z, rho_s = own.w;
     MoveCtx<KT> mc;
-    if constexpr (KT > 0) {
 #pragma unroll
-        for (int j = 0; j < KT; ++j) {
-            const bool placed = j < k;
-            const float4 pl = plc[j * xs_stride];
-            mc.x[j] = placed ? pl.x : T->obj0[j].cx;
-            mc.y[j] = placed ? pl.y : T->obj0[j].cy;
-        }
+    for (int j = 0; j < KT; ++j) {
+        const bool placed = j < k;
+        const float4 pl = plc[j * xs_stride];
+        mc.x[j] = placed ? pl.x : T->obj0[j].cx;
+        mc.y[j] = placed ? pl.y : T->obj0[j].cy;
     }
     mc.k = k;
     mc.p = p;
@@ -943,7 +915,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
         // along the holding transition
         const bool held = key || placing;
         const float lam = key ? (sw ? sw->coll : T->w[W_COLL]) : (sw ? sw->mcoll : T->w[W_MCOLL]);
-        config_pass<KT, SPLIT, GRAD>(T, S, K, si, jsn, jcs, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
+        config_pass<KT, SPLIT, GRAD>(T, S, si, jsn, jcs, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
                                      rho_c, rho_s, cw, gw, gg, gr, kin_pos, kin_rot, sw, key && self_on, selfc, nhit);
         if (key) coll += cw; else coll_m += cw;
         if (GRAD) {
@@ -1002,7 +974,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
         const float Rp[9] = {rho_c, -rho_s, 0.f, rho_s, rho_c, 0.f, 0.f, 0.f, 1.f};
         const float tp[3] = {rho_x, rho_y, T->place_z[k]};
         float fp[3] = {0.f, 0.f, 0.f}, mp[3] = {0.f, 0.f, 0.f};
-        object_spheres<KT, SPLIT, GRAD>(T, S, K, !placing, T->obs[k], si, Rp, tp, mc, lc, coll_obj, fp, mp, gr, nhit);
+        object_spheres<KT, SPLIT, GRAD>(T, S, !placing, T->obs[k], si, Rp, tp, mc, lc, coll_obj, fp, mp, gr, nhit);
         if (GRAD && !placing) {
             // translation: the force; turning about the vertical through the
             // placement origin: z of the moment about that point
@@ -1117,7 +1089,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-level tile: P particles x 2K slots x SPLIT lanes, K at run time.
+// Workgroup-level tile: P particles x 2K slots x SPLIT lanes.
 
 // LDS of a tile (dynamic; the host passes tile_layout(...).total).  At K = 4,
 // 60 robot spheres and 9 static boxes a fused step without waypoints takes 75
@@ -1180,11 +1152,10 @@ template <int KT, int SPLIT, int MODE, bool EXT>
 __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds, float lr, float b1,
                                         float b2, float eps, int32_t t, int iters) {
     const Tables* __restrict__ T = io.T;
-    const int K = KT ? KT : T->K;
-    const int SLOTS = 2 * K;
-    const int LPP = SLOTS * SPLIT;
-    const int P = WG / LPP;
-    const int D = CT_STEP_DIM * K;
+    constexpr int K = KT;
+    constexpr int SLOTS = 2 * K;
+    constexpr int P = tile_particles(K, SPLIT);
+    constexpr int D = CT_STEP_DIM * K;
     const int64_t n = io.n, ld = io.ld;
     const int tid = threadIdx.x;
 
@@ -1200,11 +1171,10 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
     // phase 0: stage this tile's particles (coalesced along particles) and,
     // for the fused step, their Adam moments and the frozen flags, and the
     // problem's tables.  A lane issues all of its loads before the first wait
-    // (NST is an upper bound on its share; with the skeleton length known at
-    // compile time, exact), so the tile pays one memory latency here and none
+    // (NST is an upper bound on its share), so the tile pays one memory latency here and none
     // in phase 2.
     {
-        constexpr int NST = (KT ? CT_STEP_DIM * KT * tile_particles(KT, SPLIT) : 2688 / SPLIT) / WG + 1;
+        constexpr int NST = (D * P + WG - 1) / WG;
         float xv[NST], mv[NST], vv[NST];
 #pragma unroll
         for (int u = 0; u < NST; ++u) {
@@ -1287,7 +1257,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
                 uint64_t Ta = (uint64_t)T;
                 asm volatile("" : "+s"(Ta));
                 const Tables* Ti = (const Tables*)(const __attribute__((address_space(4))) Tables*)Ta;
-                const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(Ti, S, K, p, slot, si,
+                const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(Ti, S, p, slot, si,
                                                                   S.part + ((p * SLOTS + slot) * SPLIT + si) * NP,
                                                                   io.terms, ld, i, wt, i < n ? io.wts : nullptr);
                 if (si == 0) {
@@ -1420,7 +1390,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
 // iteration again, from the copy, up to it; when no particle was found in the
 // launch it returns at once.  A launch of one iteration needs neither.
 template <int SPLIT, int MODE, int KT, bool EXT>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPE))) void particle_kernel(
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void particle_kernel(
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
     float* __restrict__ G, float* __restrict__ cost, float* __restrict__ terms, uint8_t* __restrict__ mask,
     int32_t* __restrict__ first_sat, const uint8_t* __restrict__ frozen, int64_t n, int64_t ld, float lr,
@@ -1458,13 +1428,39 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPE))) vo
 }
 
 
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
+// One tile of a skeleton of KT steps for the many-skeleton kernel.  The length
+// is compiled in: with the length at run time the kernel kept 336 bytes of
+// spills per lane and read the moved objects from LDS (64 skeletons of 1 to 6
+// steps: 41.4 ms per 50 iterations, 36.9 with it compiled in).  It is a
+// function of its own, not inlined, since six inlined copies share no stack
+// and keep 2.1 KB (39.4 ms).  A function's arguments arrive in vector
+// registers; all of them are the same for the whole workgroup and are made
+// uniform again, so the tables stay scalar loads.
+template <int KT, int SPLIT, bool EXT>
+__device__ __attribute__((noinline)) void batch_tile(uint64_t skel, uint32_t lds, int32_t tile, float lr, float b1,
+                                                     float b2, float eps, int32_t t, int32_t iters) {
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)skel);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(skel >> 32));
+    const BatchSkel& b = *(const BatchSkel*)(const __attribute__((address_space(4))) BatchSkel*)(hi << 32 | lo);
+    const TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
+                    b.n, b.ld, b.gscale};
+    char* mem = (char*)(__attribute__((address_space(3))) char*)__builtin_amdgcn_readfirstlane(lds);
+    run_tile<KT, SPLIT, MODE_STEP, EXT>(io, (int64_t)__builtin_amdgcn_readfirstlane(tile) * tile_particles(KT, SPLIT),
+                                        mem, uniform(lr), uniform(b1), uniform(b2), uniform(eps),
+                                        __builtin_amdgcn_readfirstlane(t), __builtin_amdgcn_readfirstlane(iters));
+}
+
 // Many skeletons of different lengths and sizes, `iters` iterations in one
 // launch: a fixed number of workgroups pull (skeleton, tile) items from a
 // device queue (items ordered by cost, largest first) until it is empty, and
 // run every iteration of an item before they take the next; the last
 // workgroup to leave resets the queue for the next launch.
 template <int SPLIT, bool EXT>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPB))) void batch_kernel(const BatchSkel* __restrict__ skels,
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void batch_kernel(const BatchSkel* __restrict__ skels,
                                                    const int2* __restrict__ items, int32_t n_items,
                                                    int32_t* __restrict__ queue, float lr, float b1, float b2,
                                                    float eps, int32_t t, int32_t iters) {
@@ -1479,11 +1475,16 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CT_WPB))) vo
         __syncthreads();
         if (it >= n_items) break;
         const int2 w = items[it];
-        const BatchSkel& b = skels[w.x];
-        const TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
-                        b.n, b.ld, b.gscale};
-        run_tile<0, SPLIT, MODE_STEP, EXT>(io, (int64_t)w.y * tile_particles(b.T->K, SPLIT), tile_mem + 16, lr, b1, b2, eps, t,
-                                           iters);
+        const uint64_t sk = (uint64_t)&skels[w.x];
+        const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(tile_mem + 16);
+        switch (skels[w.x].T->K) {
+            case 1: batch_tile<1, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 2: batch_tile<2, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 3: batch_tile<3, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 4: batch_tile<4, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 5: batch_tile<5, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            default: batch_tile<6, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+        }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
