@@ -85,7 +85,7 @@ __device__ __forceinline__ void pair_hit(float px, float py, float pz, float r, 
 template <int KT>
 struct MoveCtx {
     float x[KT], y[KT];
-    int k, p;   // step, particle of the tile
+    int k, p;   // step, column of the tile
 };
 
 // Bijection from the launch index to a tile index that keeps each XCD's
@@ -823,7 +823,7 @@ template <int KT, int SPLIT, int MODE, bool EXT>
 __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const TileLds& S, int p,
                                              int slot, int si, float* __restrict__ part, float* __restrict__ terms,
                                              int64_t term_ld, int64_t i_glob, bool write_terms,
-                                             const float* __restrict__ wts) {
+                                             const float* __restrict__ wts, bool live) {
     constexpr bool GRAD = MODE != MODE_COST;
     constexpr int K = KT;
     const bool self_on = EXT && T->self_on;   // wave-uniform; compiled out without EXT
@@ -852,7 +852,10 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     float g_s, g_c;
     sincosf(gyaw, &g_s, &g_c);
     const float4 own = plc[k * xs_stride];
-    const float rho_x = own.x, rho_y = own.y, rho_c = own.z, rho_s = own.w;
+    // a column without a particle is evaluated at NaN sines and placement: its
+    // centres are NaN, touch nothing and join no test
+    const float none = __builtin_nanf("");
+    const float rho_x = live ? own.x : none, rho_y = own.y, rho_c = own.z, rho_s = own.w;
     MoveCtx<KT> mc;
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
@@ -905,6 +908,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
             }
             float sn, cs;
             sincosf(q + th0, &sn, &cs);
+            sn = live ? sn : none;
             split_bcast<SPLIT>(sn, j0, jsn);
             split_bcast<SPLIT>(cs, j0, jcs);
         }
@@ -1138,6 +1142,7 @@ struct TileIO {
     float *Xb = nullptr, *Mb = nullptr, *Vb = nullptr;   // copies of the state the launch started from, or null
     int redo = 0;   // start from those copies, run every iteration, report nothing
     int32_t* hits = nullptr;   // cost mode: touching sphere-box pairs per particle, or null
+    int spread = 0;            // log2 of the tile's columns per particle
 };
 
 
@@ -1158,6 +1163,9 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
     constexpr int D = CT_STEP_DIM * K;
     const int64_t n = io.n, ld = io.ld;
     const int tid = threadIdx.x;
+    // the particle of column p (n: none)
+    const int spread = io.spread, gap = (1 << spread) - 1, PS = P >> spread;
+    auto particle = [&](int p) -> int64_t { return (p & gap) || (p >> spread) >= PS ? n : p0 + (p >> spread); };
 
     const int W = T->W, nsb = T->n_static;
     const TileLayout lay = tile_layout(K, SPLIT, MODE, W, nsb, T->link_start[9]);
@@ -1180,7 +1188,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
         for (int u = 0; u < NST; ++u) {
             const int idx = tid + u * WG;
             const int d = idx / P, p = idx - d * P;
-            const int64_t i = p0 + p;
+            const int64_t i = particle(p);
             xv[u] = mv[u] = vv[u] = 0.f;
             if (idx < D * P && i < n) {
                 const int64_t a = d * ld + i;
@@ -1249,7 +1257,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
             const int si = tid % SPLIT, rest = tid / SPLIT;
             const int slot = rest / P, p = rest - slot * P;
             if (slot < SLOTS) {
-                const int64_t i = p0 + p;
+                const int64_t i = particle(p);
                 const bool wt = (MODE == MODE_COST) && io.terms != nullptr && i < n;
                 // the table pointer is made opaque per iteration: hoisted out of
                 // the loop, the tables' values would not fit the registers
@@ -1259,7 +1267,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
                 const Tables* Ti = (const Tables*)(const __attribute__((address_space(4))) Tables*)Ta;
                 const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(Ti, S, p, slot, si,
                                                                   S.part + ((p * SLOTS + slot) * SPLIT + si) * NP,
-                                                                  io.terms, ld, i, wt, i < n ? io.wts : nullptr);
+                                                                  io.terms, ld, i, wt, i < n ? io.wts : nullptr, i < n);
                 if (si == 0) {
                     S.cpart[p * SLOTS + slot] = o.cost;
                     if (W > 0) S.tpart[p * SLOTS + slot] = o.traj;
@@ -1272,7 +1280,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
 
         // phase 1.5: per-particle cost, mask, update permission
         if (tid < P) {
-            const int64_t i = p0 + tid;
+            const int64_t i = particle(tid);
             int ok = 1;
             J = 0.f;
             m = 1;
@@ -1313,7 +1321,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
             const int FQ = 11 + 3 * K;   // foreign-configuration partials
             for (int idx = tid; idx < D * P; idx += WG) {
                 const int d = idx / P, p = idx - d * P;
-                const int64_t i = p0 + p;
+                const int64_t i = particle(p);
                 if (i >= n) continue;
                 const int k = d / CT_STEP_DIM, r = d - CT_STEP_DIM * k;
                 const float* pp = S.part + p * SLOTS * SPLIT * NP;
@@ -1360,15 +1368,15 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
         __syncthreads();
     }
 
-    if (tid < P && p0 + tid < n) {
-        if (io.cost) io.cost[p0 + tid] = J;
-        if (io.mask) io.mask[p0 + tid] = (uint8_t)m;
+    if (tid < P && particle(tid) < n) {
+        if (io.cost) io.cost[particle(tid)] = J;
+        if (io.mask) io.mask[particle(tid)] = (uint8_t)m;
     }
     if (MODE == MODE_STEP) {
         // every entry by the lane that updated it in phase 2
         for (int idx = tid; idx < D * P; idx += WG) {
             const int d = idx / P, p = idx - d * P;
-            const int64_t i = p0 + p;
+            const int64_t i = particle(p);
             if (i >= n || S.frz[d]) continue;
             const int64_t a = d * ld + i;
             io.X[a] = S.xs[idx];
@@ -1394,7 +1402,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
     float* __restrict__ G, float* __restrict__ cost, float* __restrict__ terms, uint8_t* __restrict__ mask,
     int32_t* __restrict__ first_sat, const uint8_t* __restrict__ frozen, int64_t n, int64_t ld, float lr,
-    float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, StopArgs stop, const float* __restrict__ gw,
+    float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, int32_t spread, StopArgs stop, const float* __restrict__ gw,
     const float* __restrict__ wts, int32_t* __restrict__ hits) {
     extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int run = iters;
@@ -1414,6 +1422,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     // that share cache lines of X, M and V then share one L2
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     TileIO io{T, X, M, V, G, cost, terms, mask, first_sat, frozen, gw, n, ld, gscale, EXT ? wts : nullptr};
+    io.spread = spread;
     if (MODE == MODE_COST) io.hits = hits;
     if (MODE == MODE_STEP) {
         io.stop = stop.on;
@@ -1422,8 +1431,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
         io.Vb = stop.Vb;
         io.redo = stop.redo;
     }
-    const int ran =
-        run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT), tile_mem, lr, b1, b2, eps, t, run);
+    const int ran = run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT, spread), tile_mem, lr, b1, b2, eps,
+                                                   t, run);
     if (MODE == MODE_STEP && stop.ran && !stop.redo && threadIdx.x == 0) stop.ran[blockIdx.x] = ran;
 }
 
@@ -1442,14 +1451,15 @@ __device__ __forceinline__ float uniform(float x) {
 // uniform again, so the tables stay scalar loads.
 template <int KT, int SPLIT, bool EXT>
 __device__ __attribute__((noinline)) void batch_tile(uint64_t skel, uint32_t lds, int32_t tile, float lr, float b1,
-                                                     float b2, float eps, int32_t t, int32_t iters) {
+                                                     float b2, float eps, int32_t t, int32_t iters, int32_t spread) {
     const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)skel);
     const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(skel >> 32));
     const BatchSkel& b = *(const BatchSkel*)(const __attribute__((address_space(4))) BatchSkel*)(hi << 32 | lo);
-    const TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
+    TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
                     b.n, b.ld, b.gscale};
+    io.spread = __builtin_amdgcn_readfirstlane(spread);
     char* mem = (char*)(__attribute__((address_space(3))) char*)__builtin_amdgcn_readfirstlane(lds);
-    run_tile<KT, SPLIT, MODE_STEP, EXT>(io, (int64_t)__builtin_amdgcn_readfirstlane(tile) * tile_particles(KT, SPLIT),
+    run_tile<KT, SPLIT, MODE_STEP, EXT>(io, (int64_t)__builtin_amdgcn_readfirstlane(tile) * tile_particles(KT, SPLIT, io.spread),
                                         mem, uniform(lr), uniform(b1), uniform(b2), uniform(eps),
                                         __builtin_amdgcn_readfirstlane(t), __builtin_amdgcn_readfirstlane(iters));
 }
@@ -1463,7 +1473,7 @@ template <int SPLIT, bool EXT>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void batch_kernel(const BatchSkel* __restrict__ skels,
                                                    const int2* __restrict__ items, int32_t n_items,
                                                    int32_t* __restrict__ queue, float lr, float b1, float b2,
-                                                   float eps, int32_t t, int32_t iters) {
+                                                   float eps, int32_t t, int32_t iters, int32_t spread) {
     extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int& item_s = *(int*)tile_mem;   // ahead of the tile's own LDS
     for (;;) {
@@ -1478,12 +1488,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ba
         const uint64_t sk = (uint64_t)&skels[w.x];
         const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(tile_mem + 16);
         switch (skels[w.x].T->K) {
-            case 1: batch_tile<1, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
-            case 2: batch_tile<2, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
-            case 3: batch_tile<3, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
-            case 4: batch_tile<4, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
-            case 5: batch_tile<5, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
-            default: batch_tile<6, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 1: batch_tile<1, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            case 2: batch_tile<2, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            case 3: batch_tile<3, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            case 4: batch_tile<4, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            case 5: batch_tile<5, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            default: batch_tile<6, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
         }
         __syncthreads();
     }
