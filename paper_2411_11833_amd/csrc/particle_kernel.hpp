@@ -662,7 +662,7 @@ struct LaneOut {
 // dJ/dq of this configuration into gq (folded onto the joint axes from
 // world-frame wrenches: dJ/dq_j = z_j . tau + (o_j x z_j) . f for the wrench
 // of everything beyond joint j), and the grasp / placement partials gg, gr.
-template <int KT, int SPLIT, bool GRAD>
+template <int KT, int SPLIT, bool GRAD, int JU>
 __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const TileLds& S, int si,
                                             const float jsn[CT_N_JOINTS], const float jcs[CT_N_JOINTS], bool held,
                                             bool kin, bool placing,
@@ -685,7 +685,7 @@ __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const 
     float cj[CT_N_JOINTS];
     float f[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};   // wrench of the links done so far
     // links 1..7, then the tool (spheres of the tool frame, t = its origin)
-#pragma unroll 1
+#pragma unroll JU
     for (int i = 0; i <= CT_N_JOINTS; ++i) {
         const Joint J = T->jk[i];
         if (i < CT_N_JOINTS) {
@@ -826,6 +826,14 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
                                              const float* __restrict__ wts, bool live) {
     constexpr bool GRAD = MODE != MODE_COST;
     constexpr int K = KT;
+    // how far config_pass unrolls its loop over the 8 links: fully where the
+    // copies fit the 256 registers of two waves per SIMD, so that a link's
+    // tables are loaded while the one before is tested (16384 waypoint
+    // gradients 1.21 -> 1.14 ms, 100 steps of 256 one-step particles 1.39 ->
+    // 1.31); the longer fused steps and the extended kernels would spill (64
+    // skeletons 37.1 -> 39.3 ms, an augmented-Lagrangian round 2.16 -> 2.32)
+    // and take pairs (36.7, 2.13)
+    constexpr int JU = !EXT && (MODE != MODE_STEP || KT == 1) ? 8 : 2;
     const bool self_on = EXT && T->self_on;   // wave-uniform; compiled out without EXT
     // per-particle weights only in extended kernels; plain kernels read lambda
     // from the tables where each term needs it
@@ -919,7 +927,7 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
         // along the holding transition
         const bool held = key || placing;
         const float lam = key ? (sw ? sw->coll : T->w[W_COLL]) : (sw ? sw->mcoll : T->w[W_MCOLL]);
-        config_pass<KT, SPLIT, GRAD>(T, S, si, jsn, jcs, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
+        config_pass<KT, SPLIT, GRAD, JU>(T, S, si, jsn, jcs, held, key, placing, lam, mc, gx, gy, gz, g_c, g_s, rho_x, rho_y,
                                      rho_c, rho_s, cw, gw, gg, gr, kin_pos, kin_rot, sw, key && self_on, selfc, nhit);
         if (key) coll += cw; else coll_m += cw;
         if (GRAD) {
