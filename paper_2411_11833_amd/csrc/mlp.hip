@@ -32,7 +32,7 @@ struct ct_mlp {
     std::vector<int64_t> woff, boff;
     int64_t n_params = 0;
     float *P = nullptr, *Mo = nullptr, *Vo = nullptr, *G = nullptr;
-    std::vector<uint16_t*> Wb, WbT;
+    std::vector<uint16_t*> Wb, WbT, Wf;   // BF16 weights: [npad][kpad], [kpad][npad], fragment-major
     uint16_t *X0 = nullptr, *X0T = nullptr;
     std::vector<float*> Z;
     std::vector<uint16_t*> H, HT, D, DT;
@@ -137,7 +137,7 @@ int refresh(ct_mlp* m, hipStream_t st) {
     for (int l = 0; l < m->L; ++l) {
         const int64_t cnt = (int64_t)m->npad[l] * m->kpad[l];
         hipLaunchKernelGGL(refresh_kernel, dim3(blocks(cnt, 256)), dim3(256), 0, st, m->P + m->woff[l], m->din[l],
-                           m->dout[l], m->kpad[l], m->npad[l], m->Wb[l], m->WbT[l]);
+                           m->dout[l], m->kpad[l], m->npad[l], m->Wb[l], m->WbT[l], m->Wf[l]);
     }
     return err_of(hipGetLastError());
 }
@@ -147,9 +147,8 @@ int refresh(ct_mlp* m, hipStream_t st) {
 // every weight once from L2, so blocks are as tall as 256 workgroups allow
 // (128 rows from 32,768 rows, 64 from 16,384, else 32); below 8,192 rows the
 // per-layer launches are faster.
-bool fused_ok(const ct_mlp* m, int64_t rows) {
-    return m->s.hidden == FH && m->s.d_out <= FUSED_MAX_OUT && rows >= 256 * 32;
-}
+bool fused_shape(const ct_mlp* m) { return m->s.hidden == FH && m->s.d_out <= FUSED_MAX_OUT; }
+bool fused_ok(const ct_mlp* m, int64_t rows) { return fused_shape(m) && rows >= 256 * 32; }
 
 int infer_fused(ct_mlp* m, int64_t rows, hipStream_t st) {
     FusedArgs f{};
@@ -159,7 +158,7 @@ int infer_fused(ct_mlp* m, int64_t rows, hipStream_t st) {
     f.L = m->L;
     f.d_out = m->s.d_out;
     for (int l = 0; l < m->L; ++l) {
-        f.W[l] = m->Wb[l];
+        f.W[l] = m->Wf[l];
         f.bias[l] = m->P + m->boff[l];
     }
     f.Y = m->Y;
@@ -361,6 +360,7 @@ int adam(ct_mlp* m, int64_t t, const ct_adam* ad, hipStream_t st) {
         a.boff[l] = m->boff[l];
         a.Wb[l] = m->Wb[l];
         a.WbT[l] = m->WbT[l];
+        a.Wf[l] = m->Wf[l];
     }
     const int64_t total = a.wstart[m->L] + a.bstart[m->L];
     hipLaunchKernelGGL(adam_refresh_kernel, dim3(blocks(total, 256)), dim3(256), 0, st, a);
@@ -411,9 +411,11 @@ int ct_mlp_create(const ct_mlp_shape* shape, ct_mlp** out) {
     ok = ok && m->alloc(m->part, m->part_cap);
     m->Wb.assign(m->L, nullptr);
     m->WbT.assign(m->L, nullptr);
+    m->Wf.assign(m->L, nullptr);
     for (int l = 0; l < m->L && ok; ++l) {
         ok = m->alloc(m->Wb[l], (int64_t)m->npad[l] * m->kpad[l]);
         if (ok && l > 0) ok = m->alloc(m->WbT[l], (int64_t)m->npad[l] * m->kpad[l]);
+        if (ok && fused_shape(m)) ok = m->alloc(m->Wf[l], (int64_t)m->npad[l] * m->kpad[l]);
     }
     m->Z.assign(shape->depth, nullptr);
     m->H.assign(shape->depth, nullptr);

@@ -123,6 +123,23 @@ __device__ __forceinline__ void normal4(uint32_t c0, uint32_t c1, uint32_t c2, u
 }
 
 // ---------------------------------------------------------------------------
+// weight layouts
+
+constexpr int FH = 512;   // hidden width of the fused inference kernel
+
+// Element (o, i) of a weight matrix [npad][kpad] in fragment-major order: 1 KB
+// blocks of 16 rows x 32 columns, each the 64 lanes' operand fragments of one
+// MFMA (lane l: row l % 16, columns 8 (l / 16) .. + 7), so that a wave reads a
+// fragment as one contiguous kilobyte; the blocks of a K slice follow each
+// other, so that the waves of all compute units, which walk K in step, spread
+// over the channels of L2.  Fragments read from the [npad][kpad] rows were 16
+// segments of 64 bytes 1 KB apart, in a quarter of the channels: the inference
+// pass of 8192 rows took 48 us, of 32768 rows 72; now 24.5 and 60.
+__device__ __forceinline__ int64_t frag_at(int o, int i, int npad) {
+    return ((int64_t)(i >> 5) * (npad >> 4) + (o >> 4)) * 512 + ((i >> 3) & 3) * 128 + (o & 15) * 8 + (i & 7);
+}
+
+// ---------------------------------------------------------------------------
 // C = A * B^T on the matrix cores
 
 enum Epi { EPI_HID_TRAIN = 0, EPI_HID_INFER = 1, EPI_OUT = 2, EPI_BWD = 3, EPI_DW = 4 };
@@ -605,14 +622,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_pipe_kernel(GemmArgs g) {
 // wave w computes 16-column block w of every row.  Same operations, operand
 // order and K order as the layer-by-layer inference kernels.
 
-constexpr int FH = 512;               // hidden width
 constexpr int FUSED_MAX_OUT = 128;    // output columns (8 waves x 16)
 
 struct FusedArgs {
     const uint16_t* X;   // [M][kin] BF16 input rows
     int M, kin, L;       // rows, padded input width (32 .. 512, multiple of 32), linear layers (2 .. MAX_LAYERS)
     int d_out;           // 1 .. FUSED_MAX_OUT
-    const uint16_t* W[MAX_LAYERS];   // layer l: [npad][kpad] BF16 (kpad = kin for l = 0, else FH)
+    const uint16_t* W[MAX_LAYERS];   // layer l: fragment-major BF16 (frag_at; kpad = kin for l = 0, else FH)
     const float* bias[MAX_LAYERS];
     float* Y;            // [M][d_out] FP32
     const f32x4_t* gelu_tab;
@@ -623,8 +639,8 @@ struct FusedArgs {
 // touches at one chunk land in 16 different bank groups
 __device__ __forceinline__ int fused_at(int r, int c) { return r * FH + (((c >> 3) ^ (r & 15)) << 3) + (c & 7); }
 
-// Weight fragments of FJ row blocks (rows wrow + 16 j K, K contiguous, K / 32
-// slices) go straight into registers through a ring of 4, three K slices
+// Weight fragments of FJ consecutive row blocks (wfrag: this lane's 16 bytes
+// of the first block's slice 0) go straight into registers through a ring of 4, three K slices
 // ahead (loads past the last slice repeat it, unused).  fused_pre loads
 // slices 0..2 (issued early, e.g. before the previous layer's epilogue);
 // fused_k then runs every slice: acc[i][j] += activation row block i (from
@@ -632,27 +648,27 @@ __device__ __forceinline__ int fused_at(int r, int c) { return r * FH + (((c >> 
 // K / 32 at run time, in an unconditional loop of 4 slices (so the
 // compiler's waits leave three slices in flight) and a remainder.
 template <int FJ>
-__device__ __forceinline__ void fused_wload(const uint16_t* __restrict__ wrow, int K, int s, u32x4_t (&b)[FJ]) {
+__device__ __forceinline__ void fused_wload(const uint16_t* __restrict__ wfrag, int K, int N, int s, u32x4_t (&b)[FJ]) {
     s = min(s, (K >> 5) - 1);
 #pragma unroll
-    for (int j = 0; j < FJ; ++j) b[j] = *(const u32x4_t*)(wrow + (int64_t)j * 16 * K + s * 32);
+    for (int j = 0; j < FJ; ++j) b[j] = *(const u32x4_t*)(wfrag + s * 32 * N + j * 512);
 }
 
 template <int FJ>
-__device__ __forceinline__ void fused_pre(const uint16_t* __restrict__ wrow, int K, u32x4_t (&w0)[FJ],
+__device__ __forceinline__ void fused_pre(const uint16_t* __restrict__ wfrag, int K, int N, u32x4_t (&w0)[FJ],
                                           u32x4_t (&w1)[FJ], u32x4_t (&w2)[FJ]) {
-    fused_wload<FJ>(wrow, K, 0, w0);
-    fused_wload<FJ>(wrow, K, 1, w1);
-    fused_wload<FJ>(wrow, K, 2, w2);
+    fused_wload<FJ>(wfrag, K, N, 0, w0);
+    fused_wload<FJ>(wfrag, K, N, 1, w1);
+    fused_wload<FJ>(wfrag, K, N, 2, w2);
 }
 
 template <int FI, int FJ, int NK>
-__device__ __forceinline__ void fused_k(f32x4_t (&acc)[FI][FJ], const uint16_t* __restrict__ wrow, int K,
+__device__ __forceinline__ void fused_k(f32x4_t (&acc)[FI][FJ], const uint16_t* __restrict__ wfrag, int K, int N,
                                         const uint16_t* hs, u32x4_t (&w0)[FJ], u32x4_t (&w1)[FJ],
                                         u32x4_t (&w2)[FJ], u32x4_t (&w3)[FJ]) {
     const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
     auto step = [&](int s, const u32x4_t (&cur)[FJ], u32x4_t (&nxt)[FJ]) {
-        fused_wload<FJ>(wrow, K, s + 3, nxt);   // into the registers slice s - 1 used
+        fused_wload<FJ>(wfrag, K, N, s + 3, nxt);   // into the registers slice s - 1 used
         // keep the loads here: left alone, the scheduler sinks them next to
         // their first use a ring later, which exposes their latency
         __builtin_amdgcn_sched_barrier(0);
@@ -699,12 +715,13 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
     const int m0 = xcd_swizzle((int)blockIdx.x, (int)gridDim.x) * TM;
     const int n0 = w * 16;   // the output layer's columns of this wave
     const int lo = a.L - 1;
-    // hidden weight rows 64 w + 16 j + r16, output weight rows n0 + r16
-    // (present up to the padded row count), 8 K values at 32 s + 8 q
-    auto hrow = [&](int l) { return a.W[l] + (int64_t)(w * 64 + r16) * (l == 0 ? a.kin : FH) + q * 8; };
-    const uint16_t* orow = a.W[lo] + (int64_t)(n0 + r16) * FH + q * 8;
+    // hidden weight rows 64 w .. 64 w + 63, output weight rows n0 .. n0 + 15
+    // (present up to the padded row count)
+    auto hrow = [&](int l) { return a.W[l] + w * 4 * 512 + lane * 8; };
+    const uint16_t* orow = a.W[lo] + w * 512 + lane * 8;
+    const int on = (a.d_out + 31) & ~31;   // its padded row count
     u32x4_t w0[4], w1[4], w2[4], w3[4];
-    fused_pre<4>(hrow(0), a.kin, w0, w1, w2);
+    fused_pre<4>(hrow(0), a.kin, FH, w0, w1, w2);
     // input rows (rows past M repeat row M - 1; their outputs are not stored)
     const int cpr = a.kin >> 3;
     for (int e = tid; e < TM * cpr; e += 512) {
@@ -731,12 +748,12 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
 #pragma unroll
             for (int i = 0; i < FI; ++i) acc[i][j] = b0;
         }
-        fused_k<FI, 4, 0>(acc, hrow(l), l == 0 ? a.kin : FH, hs, w0, w1, w2, w3);
+        fused_k<FI, 4, 0>(acc, hrow(l), l == 0 ? a.kin : FH, FH, hs, w0, w1, w2, w3);
         // the next layer's first weight slices travel during the epilogue
         if (l + 1 < lo)
-            fused_pre<4>(hrow(l + 1), FH, w0, w1, w2);
+            fused_pre<4>(hrow(l + 1), FH, FH, w0, w1, w2);
         else if (n0 < a.d_out)
-            fused_pre<1>(orow, FH, o0, o1, o2);
+            fused_pre<1>(orow, FH, on, o0, o1, o2);
         __syncthreads();   // every wave has read this layer's inputs
 #pragma unroll
         for (int i = 0; i < FI; ++i) {
@@ -765,7 +782,7 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
 #pragma unroll
         for (int i = 0; i < FI; ++i) acc[i][0] = b0;
     }
-    fused_k<FI, 1, 0>(acc, orow, FH, hs, o0, o1, o2, o3);
+    fused_k<FI, 1, 0>(acc, orow, FH, on, hs, o0, o1, o2, o3);
     const bool vec_out = (a.d_out & 3) == 0;
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
@@ -1142,6 +1159,7 @@ struct AdamRefreshArgs {
     int64_t woff[MAX_LAYERS], boff[MAX_LAYERS];
     uint16_t* Wb[MAX_LAYERS];
     uint16_t* WbT[MAX_LAYERS];   // null: none kept for that layer
+    uint16_t* Wf[MAX_LAYERS];    // the same values fragment-major, or null
 };
 
 __device__ __forceinline__ float adam_one(const AdamRefreshArgs& a, int64_t idx) {
@@ -1170,6 +1188,7 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshArgs a) {
         if (o < a.dout[l] && i < a.din[l]) v = to_bf16(adam_one(a, a.woff[l] + (int64_t)o * a.din[l] + i));
         a.Wb[l][loc] = v;
         if (a.WbT[l]) a.WbT[l][(int64_t)i * a.npad[l] + o] = v;
+        if (a.Wf[l]) a.Wf[l][frag_at(o, i, a.npad[l])] = v;
         return;
     }
     const int64_t b0 = e0 - a.wstart[a.L];
@@ -1180,16 +1199,18 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshArgs a) {
     if (j < a.dout[l]) adam_one(a, a.boff[l] + j);
 }
 
-// BF16 copies of one layer's weights: Wb [npad][kpad] and WbT [kpad][npad]
-// (null to skip), zero outside the real [dout][din] block
+// BF16 copies of one layer's weights: Wb [npad][kpad], WbT [kpad][npad] and
+// Wf (frag_at; null to skip either), zero outside the real [dout][din] block
 __global__ __launch_bounds__(256) void refresh_kernel(const float* __restrict__ W, int din, int dout, int kpad,
-                                                      int npad, uint16_t* __restrict__ Wb, uint16_t* __restrict__ WbT) {
+                                                      int npad, uint16_t* __restrict__ Wb, uint16_t* __restrict__ WbT,
+                                                      uint16_t* __restrict__ Wf) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (int64_t)npad * kpad) return;
     const int o = (int)(e / kpad), i = (int)(e % kpad);
     const uint16_t v = (o < dout && i < din) ? to_bf16(W[(int64_t)o * din + i]) : (uint16_t)0;
     Wb[e] = v;
     if (WbT) WbT[(int64_t)i * npad + o] = v;
+    if (Wf) Wf[frag_at(o, i, npad)] = v;
 }
 
 // seeds: x = y std + mean, angles wrapped into [-pi, pi), clamped into
