@@ -614,7 +614,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_pipe_kernel(GemmArgs g) {
 // once every wave has read them), so only the input rows, the weights (from
 // L2, each layer's read once per workgroup) and the outputs cross the memory
 // hierarchy.  Hidden layers: wave w computes columns 64 w .. 64 w + 63 of
-// all TM rows, weight fragments straight into registers three K slices
+// all TM rows, weight fragments straight into registers one or two K slices
 // ahead, activation fragments from LDS.  The MFMAs take the operands swapped (as in
 // the inference epilogue of the layer-by-layer kernel), so a lane ends with
 // 4 consecutive columns of one row: bias in the accumulators, then GELU and
@@ -640,13 +640,14 @@ struct FusedArgs {
 __device__ __forceinline__ int fused_at(int r, int c) { return r * FH + (((c >> 3) ^ (r & 15)) << 3) + (c & 7); }
 
 // Weight fragments of FJ consecutive row blocks (wfrag: this lane's 16 bytes
-// of the first block's slice 0) go straight into registers through a ring of 4, three K slices
-// ahead (loads past the last slice repeat it, unused).  fused_pre loads
-// slices 0..2 (issued early, e.g. before the previous layer's epilogue);
-// fused_k then runs every slice: acc[i][j] += activation row block i (from
-// LDS) x weight block j.  NK > 0: the slice count, fully unrolled; NK = 0:
-// K / 32 at run time, in an unconditional loop of 4 slices (so the
-// compiler's waits leave three slices in flight) and a remainder.
+// of the first block's slice 0) go straight into registers through a ring of
+// R slices, R - 1 ahead (loads past the last slice repeat it, unused).
+// fused_pre loads the first R - 1 (issued early, e.g. before the previous
+// layer's epilogue); fused_k then runs every slice: acc[i][j] += activation
+// row block i (from LDS) x weight block j, each row block's next activation
+// fragment read while the others multiply.  With contiguous fragments depth
+// beyond 2 (128 rows) or 3 bought nothing and spilled at 128 rows, where ring
+// 4 and activations read as needed took 60 us for 32768 rows, this 55.
 template <int FJ>
 __device__ __forceinline__ void fused_wload(const uint16_t* __restrict__ wfrag, int K, int N, int s, u32x4_t (&b)[FJ]) {
     s = min(s, (K >> 5) - 1);
@@ -654,53 +655,46 @@ __device__ __forceinline__ void fused_wload(const uint16_t* __restrict__ wfrag, 
     for (int j = 0; j < FJ; ++j) b[j] = *(const u32x4_t*)(wfrag + s * 32 * N + j * 512);
 }
 
-template <int FJ>
-__device__ __forceinline__ void fused_pre(const uint16_t* __restrict__ wfrag, int K, int N, u32x4_t (&w0)[FJ],
-                                          u32x4_t (&w1)[FJ], u32x4_t (&w2)[FJ]) {
-    fused_wload<FJ>(wfrag, K, N, 0, w0);
-    fused_wload<FJ>(wfrag, K, N, 1, w1);
-    fused_wload<FJ>(wfrag, K, N, 2, w2);
+template <int R, int FJ>
+__device__ __forceinline__ void fused_pre(const uint16_t* __restrict__ wfrag, int K, int N, u32x4_t (&w)[R][FJ]) {
+#pragma unroll
+    for (int s = 0; s + 1 < R; ++s) fused_wload<FJ>(wfrag, K, N, s, w[s]);
 }
 
-template <int FI, int FJ, int NK>
+template <int R, int FI, int FJ>
 __device__ __forceinline__ void fused_k(f32x4_t (&acc)[FI][FJ], const uint16_t* __restrict__ wfrag, int K, int N,
-                                        const uint16_t* hs, u32x4_t (&w0)[FJ], u32x4_t (&w1)[FJ],
-                                        u32x4_t (&w2)[FJ], u32x4_t (&w3)[FJ]) {
+                                        const uint16_t* hs, u32x4_t (&w)[R][FJ]) {
     const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    const int nk = K >> 5;
+    auto act = [&](int i, int s) {
+        return *(const u32x4_t*)(hs + fused_at(i * 16 + r16, min(s, nk - 1) * 32 + q * 8));
+    };
+    u32x4_t af[FI];
+#pragma unroll
+    for (int i = 0; i < FI; ++i) af[i] = act(i, 0);
     auto step = [&](int s, const u32x4_t (&cur)[FJ], u32x4_t (&nxt)[FJ]) {
-        fused_wload<FJ>(wfrag, K, N, s + 3, nxt);   // into the registers slice s - 1 used
+        fused_wload<FJ>(wfrag, K, N, s + R - 1, nxt);   // into the registers slice s - 1 used
         // keep the loads here: left alone, the scheduler sinks them next to
         // their first use a ring later, which exposes their latency
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < FI; ++i) {
-            const bf16x8_t af =
-                __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(hs + fused_at(i * 16 + r16, s * 32 + q * 8)));
 #pragma unroll
             for (int j = 0; j < FJ; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[j]), af,
-                                                                   acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[j]),
+                                                                   __builtin_bit_cast(bf16x8_t, af[i]), acc[i][j], 0, 0, 0);
+            af[i] = act(i, s + 1);   // while the other row blocks multiply
         }
     };
-    auto four = [&](int s) {
-        step(s, w0, w3);
-        step(s + 1, w1, w0);
-        step(s + 2, w2, w1);
-        step(s + 3, w3, w2);
-    };
-    if constexpr (NK > 0) {
-        static_assert(NK % 4 == 0, "whole rings");
+    // whole rings, then the last nk mod R slices (the ring ends where it
+    // started, so they take the same registers)
+    int s = 0;
+    for (; s + R <= nk; s += R)
 #pragma unroll
-        for (int s = 0; s < NK; s += 4) four(s);
-    } else {
-        // whole rings, then the last nk mod 4 slices (the ring ends where it
-        // started, so they take the same registers)
-        const int nk = K >> 5, n4 = nk & ~3;
-        for (int s = 0; s < n4; s += 4) four(s);
-        if (nk - n4 > 0) step(n4, w0, w3);
-        if (nk - n4 > 1) step(n4 + 1, w1, w0);
-        if (nk - n4 > 2) step(n4 + 2, w2, w1);
-    }
+        for (int u = 0; u < R; ++u) step(s + u, w[u], w[(u + R - 1) % R]);
+#pragma unroll
+    for (int u = 0; u + 1 < R; ++u)
+        if (s + u < nk) step(s + u, w[u], w[(u + R - 1) % R]);
 }
 
 // TM rows per workgroup (32, 64 or 128): TM / 16 row blocks of 16 per wave
@@ -720,8 +714,9 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
     auto hrow = [&](int l) { return a.W[l] + w * 4 * 512 + lane * 8; };
     const uint16_t* orow = a.W[lo] + w * 512 + lane * 8;
     const int on = (a.d_out + 31) & ~31;   // its padded row count
-    u32x4_t w0[4], w1[4], w2[4], w3[4];
-    fused_pre<4>(hrow(0), a.kin, FH, w0, w1, w2);
+    constexpr int R = TM == 128 ? 2 : 3;   // 128 rows: a longer ring would spill
+    u32x4_t wr[R][4], orr[R][1];
+    fused_pre<R, 4>(hrow(0), a.kin, FH, wr);
     // input rows (rows past M repeat row M - 1; their outputs are not stored)
     const int cpr = a.kin >> 3;
     for (int e = tid; e < TM * cpr; e += 512) {
@@ -739,7 +734,6 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
     }
     __syncthreads();
 
-    u32x4_t o0[1], o1[1], o2[1], o3[1];
     for (int l = 0; l < lo; ++l) {
         f32x4_t acc[FI][4];
 #pragma unroll
@@ -748,12 +742,12 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
 #pragma unroll
             for (int i = 0; i < FI; ++i) acc[i][j] = b0;
         }
-        fused_k<FI, 4, 0>(acc, hrow(l), l == 0 ? a.kin : FH, FH, hs, w0, w1, w2, w3);
+        fused_k<R, FI, 4>(acc, hrow(l), l == 0 ? a.kin : FH, FH, hs, wr);
         // the next layer's first weight slices travel during the epilogue
         if (l + 1 < lo)
-            fused_pre<4>(hrow(l + 1), FH, FH, w0, w1, w2);
+            fused_pre<R, 4>(hrow(l + 1), FH, FH, wr);
         else if (n0 < a.d_out)
-            fused_pre<1>(orow, FH, on, o0, o1, o2);
+            fused_pre<R, 1>(orow, FH, on, orr);
         __syncthreads();   // every wave has read this layer's inputs
 #pragma unroll
         for (int i = 0; i < FI; ++i) {
@@ -782,7 +776,7 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
 #pragma unroll
         for (int i = 0; i < FI; ++i) acc[i][0] = b0;
     }
-    fused_k<FI, 1, 0>(acc, orow, FH, on, hs, o0, o1, o2, o3);
+    fused_k<R, FI, 1>(acc, orow, FH, on, hs, orr);
     const bool vec_out = (a.d_out & 3) == 0;
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
