@@ -579,7 +579,7 @@ int ct_mlp_sample(ct_mlp* mlp, const float* feats, uint64_t seed, const float* m
     hipStream_t st = (hipStream_t)stream;
     int rc = forward(mlp, feats, 1, nullptr, nullptr, 0, n, seed, false, st);
     if (rc != CT_OK) return rc;
-    hipLaunchKernelGGL(sample_store_kernel, dim3(blocks(n, SEED_TILE)), dim3(256), 0, st, mlp->Y, mlp->s.d_out, n, mean,
+    hipLaunchKernelGGL(sample_store_kernel, dim3(blocks(n, SEED_TILE), blocks(mlp->s.d_out, SEED_DIMS)), dim3(256), 0, st, mlp->Y, mlp->s.d_out, n, mean,
                        std_, lo, hi, wrap, X, M, V, ld);
     return err_of(hipGetLastError());
 }
