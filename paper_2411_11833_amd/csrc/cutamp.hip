@@ -497,6 +497,25 @@ extern "C" int ct_al_weights(const ct_problem* P, const float* terms, int64_t n,
     return err_of(hipGetLastError());
 }
 
+namespace {
+// Counts and H (null: counts only).  One workgroup does both up to FEAS_SMALL
+// constraint terms, where the second launch costs more than the chip's width
+// gives: 33 x 1000 terms 5.3 us against 6.8 in two launches, 33 x 4096 equal
+// (whole calls 11.4 against 12.3), 66 x 4096 18.4 against 12.4.
+constexpr int64_t FEAS_SMALL = int64_t(1) << 17;
+
+int launch_feasibility(const ct_problem* P, const float* terms, int64_t n, int64_t ld, float penalty, int32_t* cnt,
+                       float* H, hipStream_t st) {
+    if (H && P->nc <= ct::FEAS_SMALL_NC && P->nc * n <= FEAS_SMALL) {
+        hipLaunchKernelGGL(ct::feas_small_kernel, dim3(1), dim3(1024), 0, st, P->d, terms, n, ld, P->nc, penalty, cnt, H);
+        return err_of(hipGetLastError());
+    }
+    hipLaunchKernelGGL(ct::feas_count_kernel, dim3(P->nc), dim3(256), 0, st, P->d, terms, n, ld, cnt);
+    if (H) hipLaunchKernelGGL(ct::feas_h_kernel, dim3(1), dim3(64), 0, st, cnt, P->nc, penalty, H);
+    return err_of(hipGetLastError());
+}
+}  // namespace
+
 extern "C" int ct_feasibility(const ct_problem* P, const float* terms, int64_t n, int64_t ld, float penalty,
                               int32_t* counts, float* H, void* stream) {
     if (!P || !std::isfinite(penalty)) return CT_ERR_INVALID_ARG;
@@ -504,9 +523,7 @@ extern "C" int ct_feasibility(const ct_problem* P, const float* terms, int64_t n
     if (terms && ((uintptr_t)terms % 256)) return CT_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
     int32_t* cnt = counts ? counts : P->counts;
-    hipLaunchKernelGGL(ct::feas_count_kernel, dim3(P->nc), dim3(256), 0, st, P->d, terms, n, ld, cnt);
-    if (H) hipLaunchKernelGGL(ct::feas_h_kernel, dim3(1), dim3(64), 0, st, cnt, P->nc, penalty, H);
-    return err_of(hipGetLastError());
+    return launch_feasibility(P, terms, n, ld, penalty, cnt, H, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -551,9 +568,7 @@ extern "C" int ct_feasibility_noalloc(const ct_problem* P, const float* terms, i
     if (rc != CT_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     // every count is written (not accumulated), so nothing needs clearing
-    hipLaunchKernelGGL(ct::feas_count_kernel, dim3(P->nc), dim3(256), 0, st, P->d, terms, n, ld, cnt);
-    hipLaunchKernelGGL(ct::feas_h_kernel, dim3(1), dim3(64), 0, st, cnt, P->nc, penalty, H);
-    return err_of(hipGetLastError());
+    return launch_feasibility(P, terms, n, ld, penalty, cnt, H, st);
 }
 
 extern "C" int ct_step_mask(const ct_problem* P, const float* terms, int64_t n, int64_t ld, uint8_t* step_mask,
@@ -562,7 +577,7 @@ extern "C" int ct_step_mask(const ct_problem* P, const float* terms, int64_t n, 
     if (terms && ((uintptr_t)terms % 256)) return CT_ERR_INVALID_ARG;
     if (step_mask && ld_mask < n) return CT_ERR_INVALID_ARG;
     if (n == 0 || (!step_mask && !count)) return CT_OK;
-    hipLaunchKernelGGL(ct::step_mask_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(ct::step_mask_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, (hipStream_t)stream,
                        P->d, terms, n, ld, step_mask, ld_mask, count);
     return err_of(hipGetLastError());
 }
