@@ -150,9 +150,9 @@ int refresh(ct_mlp* m, hipStream_t st) {
 bool fused_shape(const ct_mlp* m) { return m->s.hidden == FH && m->s.d_out <= FUSED_MAX_OUT; }
 bool fused_ok(const ct_mlp* m, int64_t rows) { return fused_shape(m) && rows >= 256 * 32; }
 
-int infer_fused(ct_mlp* m, int64_t rows, hipStream_t st) {
+int infer_fused(ct_mlp* m, const InputArgs& in, int64_t rows, hipStream_t st) {
     FusedArgs f{};
-    f.X = m->X0;
+    f.in = in;
     f.M = (int)rows;
     f.kin = m->in_pad;
     f.L = m->L;
@@ -200,15 +200,15 @@ int forward(ct_mlp* m, const float* feats, int64_t n_feats, const int32_t* feat_
             int draws, int64_t rows, uint64_t seed, bool train, hipStream_t st, bool out_layer = true,
             bool build = true) {
     int rc = CT_OK;
+    if (!train && fused_ok(m, rows)) {
+        m->fwd_rows = -1;
+        return infer_fused(m, input_args(m, feats, n_feats, feat_of_row, draw, draws, rows, seed, false), rows, st);
+    }
     if (build) {
         const InputArgs a = input_args(m, feats, n_feats, feat_of_row, draw, draws, rows, seed, train);
         const int ng = m->s.d_noise / 4, nf = m->in_pad / 4 - ng;
         hipLaunchKernelGGL(build_inputs_kernel, dim3(blocks(rows * std::max(ng, nf), 256), 2), dim3(256), 0, st, a);
         rc = err_of(hipGetLastError());
-    }
-    if (!train && fused_ok(m, rows)) {
-        m->fwd_rows = -1;
-        return rc == CT_OK ? infer_fused(m, rows, st) : rc;
     }
     for (int l = 0; l < (out_layer ? m->L : m->L - 1) && rc == CT_OK; ++l) {
         GemmArgs g{};

@@ -607,12 +607,60 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_pipe_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
+// input rows: [features | noise | zero padding] in BF16
+
+struct InputArgs {
+    const float* feats;          // [n_feats][d_feat]
+    int64_t n_feats;
+    const int32_t* feat_of_row;  // [logical rows] or null (feature row 0); clamped into range
+    const int32_t* draw;         // [logical rows] or null (draw 0); used when draws == 0
+    int draws;                   // > 0: physical row r is logical row r / draws, draw r % draws
+    int d_feat, d_noise, in_pad;
+    int64_t rows;
+    uint32_t k0, k1;
+    uint16_t* X0;                // [rows][in_pad]
+    uint16_t* X0T;               // [in_pad][ldt] or null
+    int64_t ldt;
+};
+
+__device__ __forceinline__ uint2 pack4_bf16(const float (&v)[4]) {
+    uint2 p;
+    p.x = (uint32_t)to_bf16(v[0]) | ((uint32_t)to_bf16(v[1]) << 16);
+    p.y = (uint32_t)to_bf16(v[2]) | ((uint32_t)to_bf16(v[3]) << 16);
+    return p;
+}
+
+// Logical row b and draw s of physical row r.
+__device__ __forceinline__ void row_draw(const InputArgs& a, uint32_t r, uint32_t& b, uint32_t& s) {
+    b = a.draws > 0 ? r / (uint32_t)a.draws : r;
+    s = a.draws > 0 ? r - b * (uint32_t)a.draws : (a.draw ? (uint32_t)a.draw[b] : 0u);
+}
+
+// Columns c .. c + 3 of logical row b's features (c < d_feat).
+__device__ __forceinline__ void feature4(const InputArgs& a, int64_t b, int c, float (&v)[4]) {
+    int64_t f = a.feat_of_row ? (int64_t)a.feat_of_row[b] : 0;
+    f = f < 0 ? 0 : (f >= a.n_feats ? a.n_feats - 1 : f);
+    const float* src = a.feats + f * a.d_feat + c;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = src[q];
+}
+
+__device__ __forceinline__ void put_group(const InputArgs& a, uint32_t r, int c, uint2 p) {
+    *(uint2*)(a.X0 + (int64_t)r * a.in_pad + c) = p;
+    if (a.X0T) {
+        const uint16_t h[4] = {(uint16_t)p.x, (uint16_t)(p.x >> 16), (uint16_t)p.y, (uint16_t)(p.y >> 16)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a.X0T[(int64_t)(c + q) * a.ldt + r] = h[q];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Inference through every layer in one launch (hidden width 512)
 //
 // A workgroup of 8 waves takes TM rows through the whole network: their
 // activations stay in LDS (TM x 512 BF16, overwritten in place by each layer
-// once every wave has read them), so only the input rows, the weights (from
-// L2, each layer's read once per workgroup) and the outputs cross the memory
+// once every wave has read them), so only the features, the weights (from L2,
+// each layer's read once per workgroup) and the outputs cross the memory
 // hierarchy.  Hidden layers: wave w computes columns 64 w .. 64 w + 63 of
 // all TM rows, weight fragments straight into registers one or two K slices
 // ahead, activation fragments from LDS.  The MFMAs take the operands swapped (as in
@@ -625,7 +673,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_pipe_kernel(GemmArgs g) {
 constexpr int FUSED_MAX_OUT = 128;    // output columns (8 waves x 16)
 
 struct FusedArgs {
-    const uint16_t* X;   // [M][kin] BF16 input rows
+    InputArgs in;        // the input rows (formed here; X0 is not used)
     int M, kin, L;       // rows, padded input width (32 .. 512, multiple of 32), linear layers (2 .. MAX_LAYERS)
     int d_out;           // 1 .. FUSED_MAX_OUT
     const uint16_t* W[MAX_LAYERS];   // layer l: fragment-major BF16 (frag_at; kpad = kin for l = 0, else FH)
@@ -717,12 +765,29 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
     constexpr int R = TM == 128 ? 2 : 3;   // 128 rows: a longer ring would spill
     u32x4_t wr[R][4], orr[R][1];
     fused_pre<R, 4>(hrow(0), a.kin, FH, wr);
-    // input rows (rows past M repeat row M - 1; their outputs are not stored)
-    const int cpr = a.kin >> 3;
-    for (int e = tid; e < TM * cpr; e += 512) {
-        const int r = e / cpr, c = e - r * cpr;
-        const int row = min(m0 + r, a.M - 1);
-        *(u32x4_t*)(hs + fused_at(r, c * 8)) = *(const u32x4_t*)(a.X + (int64_t)row * a.kin + c * 8);
+    // input rows, the values build_inputs_kernel writes, straight into LDS (a
+    // pass of its own took 7.6 us for 32768 rows, 4.0 for 8192; rows past M
+    // repeat row M - 1, their outputs are not stored): first the noise groups,
+    // then the feature and zero groups
+    {
+        const int ng = a.in.d_noise / 4, nf = a.kin / 4 - ng;
+        for (int e = tid; e < TM * ng; e += 512) {
+            const int r = e / ng, gi = e - r * ng;
+            uint32_t b, s;
+            row_draw(a.in, (uint32_t)min(m0 + r, a.M - 1), b, s);
+            float v[4];
+            normal4(b, s, (uint32_t)gi, a.in.k0, a.in.k1, v);
+            *(uint2*)(hs + fused_at(r, a.in.d_feat + 4 * gi)) = pack4_bf16(v);
+        }
+        for (int e = tid; e < TM * nf; e += 512) {
+            const int r = e / nf, gi = e - r * nf;
+            const int c = 4 * gi < a.in.d_feat ? 4 * gi : 4 * gi + a.in.d_noise;
+            uint32_t b = (uint32_t)min(m0 + r, a.M - 1);
+            if (a.in.draws > 0) b /= (uint32_t)a.in.draws;
+            float v[4] = {0.f, 0.f, 0.f, 0.f};
+            if (c < a.in.d_feat) feature4(a.in, b, c, v);
+            *(uint2*)(hs + fused_at(r, c)) = pack4_bf16(v);
+        }
     }
     static_assert(GELU_PIECES == 512, "one table piece per thread");
     tab[tid] = a.gelu_tab[tid];
@@ -793,53 +858,20 @@ __global__ __launch_bounds__(512) void mlp_infer_kernel(FusedArgs a) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// input rows: [features | noise | zero padding] in BF16
-
-struct InputArgs {
-    const float* feats;          // [n_feats][d_feat]
-    int64_t n_feats;
-    const int32_t* feat_of_row;  // [logical rows] or null (feature row 0); clamped into range
-    const int32_t* draw;         // [logical rows] or null (draw 0); used when draws == 0
-    int draws;                   // > 0: physical row r is logical row r / draws, draw r % draws
-    int d_feat, d_noise, in_pad;
-    int64_t rows;
-    uint32_t k0, k1;
-    uint16_t* X0;                // [rows][in_pad]
-    uint16_t* X0T;               // [in_pad][ldt] or null
-    int64_t ldt;
-};
-
 // Two halves of the grid (blockIdx.y): the noise groups of every row, then
 // the feature and zero groups, so that the waves generating noise
 // (Philox and Box-Muller) do nothing else.  With draws > 0 a feature thread
 // serves one logical row and writes its group to all of that row's draws
 // (one feature lookup instead of one per draw).  rows * groups < 2^32 (rows
 // <= 2^24, in_pad <= 512): 32-bit index arithmetic.
-__device__ __forceinline__ uint2 pack4_bf16(const float (&v)[4]) {
-    uint2 p;
-    p.x = (uint32_t)to_bf16(v[0]) | ((uint32_t)to_bf16(v[1]) << 16);
-    p.y = (uint32_t)to_bf16(v[2]) | ((uint32_t)to_bf16(v[3]) << 16);
-    return p;
-}
-
-__device__ __forceinline__ void put_group(const InputArgs& a, uint32_t r, int c, uint2 p) {
-    *(uint2*)(a.X0 + (int64_t)r * a.in_pad + c) = p;
-    if (a.X0T) {
-        const uint16_t h[4] = {(uint16_t)p.x, (uint16_t)(p.x >> 16), (uint16_t)p.y, (uint16_t)(p.y >> 16)};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) a.X0T[(int64_t)(c + q) * a.ldt + r] = h[q];
-    }
-}
-
 __global__ __launch_bounds__(256) void build_inputs_kernel(InputArgs a) {
     const uint32_t groups = (uint32_t)a.in_pad / 4, ng = (uint32_t)a.d_noise / 4, nf = groups - ng;
     const uint32_t e = blockIdx.x * 256u + threadIdx.x;
     if (blockIdx.y == 0) {
         if (ng == 0 || e >= (uint32_t)a.rows * ng) return;
         const uint32_t r = e / ng, gi = e - r * ng;
-        const uint32_t b = a.draws > 0 ? r / (uint32_t)a.draws : r;
-        const uint32_t s = a.draws > 0 ? r - b * (uint32_t)a.draws : (a.draw ? (uint32_t)a.draw[b] : 0u);
+        uint32_t b, s;
+        row_draw(a, r, b, s);
         float v[4];
         normal4(b, s, gi, a.k0, a.k1, v);
         put_group(a, r, a.d_feat + 4 * (int)gi, pack4_bf16(v));
@@ -852,13 +884,7 @@ __global__ __launch_bounds__(256) void build_inputs_kernel(InputArgs a) {
     const uint32_t b = e / nf, gi = e - b * nf;
     const int c = 4 * (int)gi < a.d_feat ? 4 * (int)gi : 4 * (int)gi + a.d_noise;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c < a.d_feat) {
-        int64_t f = a.feat_of_row ? (int64_t)a.feat_of_row[b] : 0;
-        f = f < 0 ? 0 : (f >= a.n_feats ? a.n_feats - 1 : f);
-        const float* src = a.feats + f * a.d_feat + c;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = src[q];
-    }
+    if (c < a.d_feat) feature4(a, b, c, v);
     const uint2 p = pack4_bf16(v);
     for (uint32_t d = 0; d < per_b; ++d) put_group(a, b * per_b + d, c, p);
 }
@@ -969,11 +995,7 @@ __device__ __forceinline__ void select_input_row(const InputArgs& in, int64_t b,
         if (c >= in.d_feat && c < in.d_feat + in.d_noise) {
             normal4((uint32_t)b, (uint32_t)s, (uint32_t)(c - in.d_feat) / 4u, in.k0, in.k1, v);
         } else if (c < in.d_feat) {
-            int64_t f = in.feat_of_row ? (int64_t)in.feat_of_row[b] : 0;
-            f = f < 0 ? 0 : (f >= in.n_feats ? in.n_feats - 1 : f);
-            const float* src = in.feats + f * in.d_feat + c;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = src[q];
+            feature4(in, b, c, v);
         }
         put_group(in, (uint32_t)b, c, pack4_bf16(v));
     }
