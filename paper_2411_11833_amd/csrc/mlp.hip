@@ -240,12 +240,13 @@ int forward(ct_mlp* m, const float* feats, int64_t n_feats, const int32_t* feat_
     return rc;
 }
 
-// gradient of sum(G * Y) from the BF16 upstream gradient already in GY / GYT
-// (with loss: the loss of the rows' row_loss, scaled by inv, in the same launch
-// that finishes the gradients)
-int backward(ct_mlp* m, int64_t rows, hipStream_t st, float* loss = nullptr, float inv = 0.f) {
+// gradient of sum(G * Y) from the BF16 upstream gradient already in GY / GYT:
+// the products, and in `fin` what is left to do (the sums over split-K
+// partials and rows, and with loss the loss of the rows' row_loss, scaled by
+// inv), by finish() or by adam()
+int backward(ct_mlp* m, int64_t rows, hipStream_t st, GradFinishArgs& fin, float* loss = nullptr, float inv = 0.f) {
     int rc = CT_OK;
-    GradFinishArgs fin{};
+    fin = GradFinishArgs{};
     fin.L = m->L;
     fin.rows = rows;
     fin.ldt = m->rows_cap;
@@ -328,15 +329,20 @@ int backward(ct_mlp* m, int64_t rows, hipStream_t st, float* loss = nullptr, flo
         fin.estart[l + 1] = fin.estart[l] + up(fin.ecount[l], 256);
         fin.ostart[l + 1] = fin.ostart[l] + up(m->dout[l], 4);
     }
+    return CT_OK;
+}
+
+int finish(ct_mlp* m, const GradFinishArgs& fin, hipStream_t st) {
     const int64_t nb = std::max(blocks(fin.estart[m->L], 256), blocks(fin.ostart[m->L], 4));
-    hipLaunchKernelGGL(grad_finish_kernel, dim3((unsigned)nb, loss ? 3 : 2), dim3(256), 0, st, fin);
+    hipLaunchKernelGGL(grad_finish_kernel, dim3((unsigned)nb, 2), dim3(256), 0, st, fin);
     return err_of(hipGetLastError());
 }
 
-int adam(ct_mlp* m, int64_t t, const ct_adam* ad, hipStream_t st) {
+// Adam and the weight copies; fin: end the backward pass in the same launch
+int adam(ct_mlp* m, int64_t t, const ct_adam* ad, hipStream_t st, const GradFinishArgs* fin = nullptr) {
     const double bc1 = 1.0 - std::pow((double)ad->beta1, (double)t);
     const double bc2 = 1.0 - std::pow((double)ad->beta2, (double)t);
-    AdamRefreshArgs a{};
+    AdamArgs a{};
     a.P = m->P;
     a.Mo = m->Mo;
     a.Vo = m->Vo;
@@ -350,8 +356,8 @@ int adam(ct_mlp* m, int64_t t, const ct_adam* ad, hipStream_t st) {
     a.bc2 = (float)bc2;
     a.L = m->L;
     for (int l = 0; l < m->L; ++l) {
-        a.wstart[l + 1] = a.wstart[l] + up((int64_t)m->npad[l] * m->kpad[l], 256);
-        a.bstart[l + 1] = a.bstart[l] + up(m->dout[l], 256);
+        a.bstart[l + 1] = a.bstart[l] + (int)blocks(m->dout[l], AT_T / 64);
+        a.tstart[l + 1] = a.tstart[l] + (int)(blocks(m->npad[l], AT_O) * blocks(m->kpad[l], AT_I));
         a.din[l] = m->din[l];
         a.dout[l] = m->dout[l];
         a.kpad[l] = m->kpad[l];
@@ -362,8 +368,11 @@ int adam(ct_mlp* m, int64_t t, const ct_adam* ad, hipStream_t st) {
         a.WbT[l] = m->WbT[l];
         a.Wf[l] = m->Wf[l];
     }
-    const int64_t total = a.wstart[m->L] + a.bstart[m->L];
-    hipLaunchKernelGGL(adam_refresh_kernel, dim3(blocks(total, 256)), dim3(256), 0, st, a);
+    if (fin) {
+        a.fin = *fin;
+        a.finish = 1;
+    }
+    hipLaunchKernelGGL(adam_refresh_kernel, dim3((unsigned)(a.bstart[m->L] + 1 + a.tstart[m->L])), dim3(AT_T), 0, st, a);
     return err_of(hipGetLastError());
 }
 
@@ -520,8 +529,10 @@ int ct_mlp_backward(ct_mlp* mlp, const float* dY, int64_t rows, void* stream) {
     hipLaunchKernelGGL(out_grad_kernel, dim3(blocks(rows, 4)), dim3(256), 0, st, dY, (const float*)nullptr,
                        (const float*)nullptr, mlp->s.d_out, mlp->out_pad, rows, 1.f, mlp->GY, mlp->GYT, mlp->rows_cap,
                        (float*)nullptr);
-    const int rc = err_of(hipGetLastError());
-    return rc != CT_OK ? rc : backward(mlp, rows, st);
+    int rc = err_of(hipGetLastError());
+    GradFinishArgs fin;
+    if (rc == CT_OK) rc = backward(mlp, rows, st, fin);
+    return rc != CT_OK ? rc : finish(mlp, fin, st);
 }
 
 int ct_mlp_adam(ct_mlp* mlp, int64_t t, const ct_adam* adam_args, void* stream) {
@@ -564,8 +575,9 @@ int ct_mlp_imle_step(ct_mlp* mlp, const float* feats, int64_t n_feats, const int
     if (rc == CT_OK) rc = forward(mlp, feats, nf, feat_of_row, sel, 0, rows, seed, true, st, false, false);
     if (rc != CT_OK) return rc;
     // 4. backward (and the loss) and Adam
-    if (rc == CT_OK) rc = backward(mlp, rows, st, loss, (float)(1.0 / ((double)rows * mlp->s.d_out)));
-    if (rc == CT_OK) rc = adam(mlp, t, adam_args, st);
+    GradFinishArgs fin;
+    rc = backward(mlp, rows, st, fin, loss, (float)(1.0 / ((double)rows * mlp->s.d_out)));
+    if (rc == CT_OK) rc = adam(mlp, t, adam_args, st, &fin);
     return rc;
 }
 
