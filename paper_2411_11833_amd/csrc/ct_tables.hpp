@@ -106,12 +106,9 @@ struct Tables {
 // particles per workgroup tile for a K-step skeleton and SPLIT lanes per slot
 __host__ __device__ constexpr int tile_particles(int K, int SPLIT) { return WG / (2 * K * SPLIT); }
 
-// A tile may be spread: of its particle columns only every 2^spread-th holds a
-// particle, and the lanes of the others only help with the sphere-box tests
-// of their wave.  Particles of a tile at a spread.
-__host__ __device__ constexpr int tile_particles(int K, int SPLIT, int spread) {
-    return tile_particles(K, SPLIT) >> spread;
-}
+// A tile may hold fewer particles, `per`, than its P columns: they are spread
+// evenly (particle j in column ceil(j P / per)) and the lanes of the empty
+// columns only help with the sphere-box tests of their wave.
 
 // Byte offsets of a tile's LDS for a K-step skeleton (mode MODE_*, W
 // waypoints, n_static static boxes, n_rs robot spheres).  Arrays whose size
@@ -175,7 +172,7 @@ struct BatchSkel {
     const uint8_t* frozen;
     int64_t n, ld;
     float gscale;
-    int pad;
+    int per;   // particles of a tile
 };
 
 }  // namespace ct

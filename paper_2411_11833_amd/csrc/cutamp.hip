@@ -148,26 +148,23 @@ int default_split(int K, int64_t n) {
     return 4;
 }
 
-// Tiles of n particles of a K-step skeleton.
-int64_t tile_count(int K, int split, int spread, int64_t n) {
-    const int64_t per = ct::tile_particles(K, split, spread);
-    return (n + per - 1) / per;
-}
-
-constexpr int MAX_SPREAD = 5;
-
-// The spread of a launch of n particles: as large as lets every tile have its
-// workgroup on the chip at once, two to a compute unit (MAX_TILES).  Small
-// batches leave compute units idle, and a spread tile finishes its tests in
-// fewer passes.  The sums of a particle do not depend on it.  256 particles
-// of one step, split 4, 100 iterations: 1.62 ms at spread 0, 1.52 at 2, 1.43
-// at 3, 1.39 at 5.
+// Tiles the chip holds at once: two workgroups on each of 256 compute units.
 constexpr int64_t MAX_TILES = 512;
 
-int tile_spread(int K, int split, int64_t n) {
-    int s = 0;
-    while (s < MAX_SPREAD && ct::tile_particles(K, split, s + 1) > 0 && tile_count(K, split, s + 1, n) <= MAX_TILES) ++s;
-    return s;
+// Particles of a tile of a launch of n: the tiles go through the chip in
+// rounds of MAX_TILES, so the particles are dealt out evenly over the rounds
+// that full tiles would take.  Small batches would leave compute units idle
+// and any batch the last round; a tile with empty columns finishes its tests
+// in fewer passes, and the sums of a particle do not depend on its tile.
+// Past one round only if that fills 90% of its places.  An iteration of 256
+// particles of one step (split 4): 16.2 us in 8 full tiles, 13.0 in 256 of one;
+// 1501 of six steps: 39.9 in 301 tiles of 5, 36.2 in 501 of 3; 20000 of four
+// steps (split 1): 117 in 625 of 32, 106 in 1000 of 20; but 2600 of six: 67.8 in
+// 520 of 5, 70.2 in 867 of 3.
+int tile_per(int K, int split, int64_t n) {
+    const int64_t P = ct::tile_particles(K, split), rounds = (n + P * MAX_TILES - 1) / (P * MAX_TILES);
+    const int64_t per = std::max<int64_t>(1, (n + rounds * MAX_TILES - 1) / (rounds * MAX_TILES));
+    return (int)(rounds == 1 || 10 * n >= 9 * per * rounds * MAX_TILES ? per : P);
 }
 
 // n == 0 is an empty batch: only the handle and ld are checked
@@ -234,7 +231,7 @@ int run_pk(const ct_problem* P, int mode, const PkArgs& a, hipStream_t st, int s
     PkFn f = pick_kernel(split, P->K, mode, P->h.self_on || b.wts);
     if (!f) return CT_ERR_UNSUPPORTED;
     b.lds = ct::tile_layout(P->K, split, mode, P->h.W, P->h.n_static, P->h.link_start[9]).total;
-    b.spread = tile_spread(P->K, split, a.n);
+    b.per = tile_per(P->K, split, a.n);
     return err_of(f(P->d, b, st));
 }
 
@@ -717,7 +714,8 @@ bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t
     }
     if (cap != hipStreamCaptureStatusNone) return false;
     const size_t state = (size_t)P->D * (size_t)ld;
-    const size_t bytes = (3 * state + (size_t)tile_count(P->K, split, tile_spread(P->K, split, n), n)) * sizeof(float);
+    const int64_t per = tile_per(P->K, split, n);
+    const size_t bytes = (3 * state + (size_t)((n + per - 1) / per)) * sizeof(float);
     if (!P->ws_used && hipEventCreateWithFlags(&P->ws_used, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         P->ws_used = nullptr;
@@ -867,7 +865,6 @@ struct ct_batch {
     int32_t n_items = 0;
     int32_t* d_queue = nullptr;   // [0] next item, [1] workgroups done
     int split = 0, workgroups = 0, persistent = 1;
-    int spread = 0;               // of the tiles of d_items
     int n_cu = 256;
 };
 
@@ -876,31 +873,33 @@ namespace {
 int batch_split(const ct_batch* B) { return B->split ? B->split : 1; }
 int batch_workgroups(const ct_batch* B) { return B->workgroups ? B->workgroups : 2 * B->n_cu; }
 
-// The batch's spread, by the rule of tile_spread over the tiles of all of its
-// skeletons (8192 x 4 placements of one object, split 1: 256 tiles at spread 0,
-// 5.38 ms; 512 at 1, 4.37; 1024 at 2, 6.85).
-int batch_spread(const ct_batch* B, int split) {
-    int spread = 0;
-    for (; spread < MAX_SPREAD; ++spread) {
-        int64_t tiles = 0;
-        for (size_t s = 0; s < B->probs.size(); ++s) {
-            if (ct::tile_particles(B->probs[s]->K, split, spread + 1) == 0) return spread;
-            tiles += tile_count(B->probs[s]->K, split, spread + 1, B->skels[s].n);
-        }
-        if (tiles > MAX_TILES) break;
+// Particles of each skeleton's tiles: where full tiles leave workgroups idle,
+// every skeleton's are divided by the largest number that keeps all tiles
+// within MAX_TILES (8192 x 4 placements of one object, split 1: 256 full
+// tiles 5.38 ms; halved, 512, 4.37; quartered, 1024, 6.85).
+int64_t batch_tiles(ct_batch* B, int split, int parts) {
+    int64_t tiles = 0;
+    for (size_t s = 0; s < B->probs.size(); ++s) {
+        const int per = (ct::tile_particles(B->probs[s]->K, split) + parts - 1) / parts;
+        B->skels[s].per = per;
+        tiles += (B->skels[s].n + per - 1) / per;
     }
-    return spread;
+    return tiles;
 }
 
 // (skeleton, tile) items for the current split, largest tiles first: a tile's
 // work grows with the boxes each of its configurations is tested against
 int batch_build_items(ct_batch* B) {
     const int split = batch_split(B);
-    B->spread = batch_spread(B, split);
+    int parts = 1;
+    while (parts < 256 && batch_tiles(B, split, parts + 1) <= MAX_TILES) ++parts;
+    batch_tiles(B, split, parts);
+    if (hipMemcpy(B->d_skels, B->skels.data(), B->skels.size() * sizeof(ct::BatchSkel), hipMemcpyHostToDevice) != hipSuccess)
+        return CT_ERR_DEVICE;
     std::vector<std::pair<int, int2>> items;
     for (size_t s = 0; s < B->probs.size(); ++s) {
         const ct_problem* P = B->probs[s];
-        const int64_t tiles = tile_count(P->K, split, B->spread, B->skels[s].n);
+        const int64_t tiles = (B->skels[s].n + B->skels[s].per - 1) / B->skels[s].per;
         const int w = P->h.n_static + P->K - 1 + 2 * P->h.W * 1;
         for (int64_t t = 0; t < tiles; ++t) items.push_back({w, make_int2((int)s, (int)t)});
     }
@@ -934,7 +933,6 @@ int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, int32_t iters, hip
         g.a = a;
         g.t = t;
         g.iters = iters;
-        g.spread = B->spread;
         for (const ct_problem* P : B->probs)
             g.lds = std::max(g.lds, 16 + ct::tile_layout(P->K, batch_split(B), ct::MODE_STEP, P->h.W, P->h.n_static,
                                                          P->h.link_start[9]).total);

@@ -1150,7 +1150,7 @@ struct TileIO {
     float *Xb = nullptr, *Mb = nullptr, *Vb = nullptr;   // copies of the state the launch started from, or null
     int redo = 0;   // start from those copies, run every iteration, report nothing
     int32_t* hits = nullptr;   // cost mode: touching sphere-box pairs per particle, or null
-    int spread = 0;            // log2 of the tile's columns per particle
+    int per = 0;               // particles of a tile (1 .. P)
 };
 
 
@@ -1171,14 +1171,17 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
     constexpr int D = CT_STEP_DIM * K;
     const int64_t n = io.n, ld = io.ld;
     const int tid = threadIdx.x;
-    // the particle of column p (n: none)
-    const int spread = io.spread, gap = (1 << spread) - 1, PS = P >> spread;
-    auto particle = [&](int p) -> int64_t { return (p & gap) || (p >> spread) >= PS ? n : p0 + (p >> spread); };
-
     const int W = T->W, nsb = T->n_static;
     const TileLayout lay = tile_layout(K, SPLIT, MODE, W, nsb, T->link_start[9]);
     const TileLds S = tile_lds(lds, lay, P);
     const int NP = S.np;
+    // the particle of column p (n: none): floor(p per / P) in the first column
+    // that gives it
+    const int per = io.per;
+    auto particle = [&](int p) -> int64_t {
+        const uint32_t at = (uint32_t)(p * per), j = at / P;
+        return at - j * P < (uint32_t)per ? p0 + j : n;
+    };
     // moments in LDS, or (waypoints: the partials leave no room) read and
     // written in place by every iteration
     constexpr bool MV = MODE == MODE_STEP;
@@ -1410,7 +1413,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
     float* __restrict__ G, float* __restrict__ cost, float* __restrict__ terms, uint8_t* __restrict__ mask,
     int32_t* __restrict__ first_sat, const uint8_t* __restrict__ frozen, int64_t n, int64_t ld, float lr,
-    float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, int32_t spread, StopArgs stop, const float* __restrict__ gw,
+    float b1, float b2, float eps, float gscale, int32_t t, int32_t iters, int32_t per, StopArgs stop, const float* __restrict__ gw,
     const float* __restrict__ wts, int32_t* __restrict__ hits) {
     extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int run = iters;
@@ -1430,7 +1433,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     // that share cache lines of X, M and V then share one L2
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     TileIO io{T, X, M, V, G, cost, terms, mask, first_sat, frozen, gw, n, ld, gscale, EXT ? wts : nullptr};
-    io.spread = spread;
+    io.per = per;
     if (MODE == MODE_COST) io.hits = hits;
     if (MODE == MODE_STEP) {
         io.stop = stop.on;
@@ -1439,8 +1442,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
         io.Vb = stop.Vb;
         io.redo = stop.redo;
     }
-    const int ran = run_tile<KT, SPLIT, MODE, EXT>(io, tile * tile_particles(KT, SPLIT, spread), tile_mem, lr, b1, b2, eps,
-                                                   t, run);
+    const int ran = run_tile<KT, SPLIT, MODE, EXT>(io, tile * per, tile_mem, lr, b1, b2, eps, t, run);
     if (MODE == MODE_STEP && stop.ran && !stop.redo && threadIdx.x == 0) stop.ran[blockIdx.x] = ran;
 }
 
@@ -1459,15 +1461,15 @@ __device__ __forceinline__ float uniform(float x) {
 // uniform again, so the tables stay scalar loads.
 template <int KT, int SPLIT, bool EXT>
 __device__ __attribute__((noinline)) void batch_tile(uint64_t skel, uint32_t lds, int32_t tile, float lr, float b1,
-                                                     float b2, float eps, int32_t t, int32_t iters, int32_t spread) {
+                                                     float b2, float eps, int32_t t, int32_t iters) {
     const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)skel);
     const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(skel >> 32));
     const BatchSkel& b = *(const BatchSkel*)(const __attribute__((address_space(4))) BatchSkel*)(hi << 32 | lo);
     TileIO io{b.T, b.X, b.M, b.V, nullptr, b.cost, nullptr, b.mask, b.first_sat, b.frozen, nullptr,
                     b.n, b.ld, b.gscale};
-    io.spread = __builtin_amdgcn_readfirstlane(spread);
+    io.per = b.per;
     char* mem = (char*)(__attribute__((address_space(3))) char*)__builtin_amdgcn_readfirstlane(lds);
-    run_tile<KT, SPLIT, MODE_STEP, EXT>(io, (int64_t)__builtin_amdgcn_readfirstlane(tile) * tile_particles(KT, SPLIT, io.spread),
+    run_tile<KT, SPLIT, MODE_STEP, EXT>(io, (int64_t)__builtin_amdgcn_readfirstlane(tile) * b.per,
                                         mem, uniform(lr), uniform(b1), uniform(b2), uniform(eps),
                                         __builtin_amdgcn_readfirstlane(t), __builtin_amdgcn_readfirstlane(iters));
 }
@@ -1481,7 +1483,7 @@ template <int SPLIT, bool EXT>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void batch_kernel(const BatchSkel* __restrict__ skels,
                                                    const int2* __restrict__ items, int32_t n_items,
                                                    int32_t* __restrict__ queue, float lr, float b1, float b2,
-                                                   float eps, int32_t t, int32_t iters, int32_t spread) {
+                                                   float eps, int32_t t, int32_t iters) {
     extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int& item_s = *(int*)tile_mem;   // ahead of the tile's own LDS
     for (;;) {
@@ -1496,12 +1498,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ba
         const uint64_t sk = (uint64_t)&skels[w.x];
         const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(tile_mem + 16);
         switch (skels[w.x].T->K) {
-            case 1: batch_tile<1, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
-            case 2: batch_tile<2, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
-            case 3: batch_tile<3, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
-            case 4: batch_tile<4, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
-            case 5: batch_tile<5, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
-            default: batch_tile<6, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters, spread); break;
+            case 1: batch_tile<1, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 2: batch_tile<2, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 3: batch_tile<3, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 4: batch_tile<4, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            case 5: batch_tile<5, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
+            default: batch_tile<6, SPLIT, EXT>(sk, lds, w.y, lr, b1, b2, eps, t, iters); break;
         }
         __syncthreads();
     }

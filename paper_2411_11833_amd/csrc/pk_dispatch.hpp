@@ -23,7 +23,7 @@ struct PkArgs {
     const float* gw;         // per-particle gradient weights (gradient mode), or null
     const float* wts;        // per-particle term weights [n_terms][ld] (extended kernels), or null
     int32_t* hits;           // cost mode: touching sphere-box pairs per particle, or null
-    int spread;              // of the tiles (tile_spread)
+    int per;                 // particles of a tile (tile_per)
     int lds;                 // bytes of LDS (tile_layout)
 };
 
@@ -39,7 +39,6 @@ struct BatchArgs {
     int32_t n_workgroups;
     AdamArgs a;
     int32_t t, iters;
-    int spread;              // of the tiles the items were built for
     int lds;                 // bytes of LDS: the largest skeleton's tile and 16 for the item
 };
 using BatchFn = hipError_t (*)(const BatchArgs&, hipStream_t);

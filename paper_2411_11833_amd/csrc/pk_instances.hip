@@ -16,11 +16,10 @@ namespace {
 
 template <int S, int MODE, int K>
 hipError_t launch_pk(const ct::Tables* T, const PkArgs& g, hipStream_t st) {
-    const int P = ct::tile_particles(K, S, g.spread);
-    const dim3 grid((unsigned)((g.n + P - 1) / P));
+    const dim3 grid((unsigned)((g.n + g.per - 1) / g.per));
     hipLaunchKernelGGL((ct::particle_kernel<S, MODE, K, CT_EXT != 0>), grid, dim3(ct::WG), g.lds, st, T, g.X, g.M, g.V, g.G, g.cost,
                        g.terms, g.mask, g.first_sat, g.frozen, g.n, g.ld, g.a.lr, g.a.b1, g.a.b2, g.a.eps, g.a.gs,
-                       g.t, g.iters, g.spread, g.stop, g.gw, g.wts, g.hits);
+                       g.t, g.iters, g.per, g.stop, g.gw, g.wts, g.hits);
     return hipGetLastError();
 }
 
@@ -28,7 +27,7 @@ template <int S>
 hipError_t launch_batch(const BatchArgs& g, hipStream_t st) {
     hipLaunchKernelGGL((ct::batch_kernel<S, CT_EXT != 0>), dim3((unsigned)g.n_workgroups), dim3(ct::WG), g.lds, st,
                        static_cast<const ct::BatchSkel*>(g.skels), g.items, g.n_items, g.queue, g.a.lr, g.a.b1,
-                       g.a.b2, g.a.eps, g.t, g.iters, g.spread);
+                       g.a.b2, g.a.eps, g.t, g.iters);
     return hipGetLastError();
 }
 

@@ -1,8 +1,8 @@
-"""Small batches leave columns of a tile empty so that more lanes share its
-tests: up to 32 columns per particle, by the number of tiles.  The results of a
-particle must not depend on it: batches on both sides of the lines of the rule
-(512 tiles) against the same particles in a batch that fills its tiles, bit
-for bit."""
+"""Tiles hold as many particles as deal a batch out evenly over the rounds of
+512 tiles it takes; the lanes of a tile's empty columns share its tests.  The
+results of a particle must not depend on it: batches on both sides of the
+rule's lines against the same particles in a batch of full tiles, bit for
+bit."""
 import pytest
 
 from paper_2411_11833_amd import inputs as I
@@ -29,24 +29,25 @@ def _run(prob, split, n, X):
     return [a.clone() for a in [c0, m0, pairs, c, m, *cols]]
 
 
-@pytest.mark.parametrize("K,split,n", [(1, 1, 2), (1, 1, 16 * 512), (1, 1, 16 * 512 + 1), (1, 4, 511), (2, 4, 1025),
-                                       (2, 2, 4096), (3, 4, 5), (4, 1, 515), (5, 2, 1537), (6, 4, 1), (6, 4, 1024)])
+@pytest.mark.parametrize("K,split,n", [(1, 1, 2), (1, 1, 16 * 512 + 1), (1, 1, 128 * 512 + 1), (1, 4, 511), (2, 4, 1025),
+                                       (2, 2, 4096), (3, 4, 5), (3, 2, 7700), (4, 1, 515), (4, 4, 4097), (5, 2, 1537),
+                                       (6, 4, 1), (6, 4, 1501), (6, 4, 2561)])
 @pytest.mark.parametrize("self_collision", [0, 1])
 def test_small_batches_equal_full_tiles(K, split, n, self_collision):
     prob = I.packing(K, 1, n_objects=K, n_obstacles=3)
     prob.skeleton.self_collision = self_collision
-    full = 513 * (256 // (2 * K * split))   # one tile too many for any spread
-    X = I.uniform_particles(prob, max(full, n), seed=5)
-    small, large = _run(prob, split, n, X), _run(prob, split, max(full, n), X)
+    tiles = 512 * (256 // (2 * K * split))
+    full = -(-n // tiles) * tiles   # whole rounds of full tiles
+    X = I.uniform_particles(prob, full, seed=5)
+    small, large = _run(prob, split, n, X), _run(prob, split, full, X)
     for a, b in zip(small, large):
         assert torch.equal(a, b[..., :n])
 
 
 @pytest.mark.parametrize("sizes", [[33, 1], [2048, 2100], [6000, 9000, 1]])
 def test_small_batches_of_skeletons_equal_single_launches(sizes):
-    """The many-skeleton kernel's spread is that of all its tiles, a single
-    launch's its own; a stop at the first satisfying particle keeps one count
-    per spread tile."""
+    """The many-skeleton kernel sizes its tiles over all of its skeletons, a
+    single launch its own."""
     from paper_2411_11833_amd.binding import CtAdam
     from paper_2411_11833_amd.planner import GpuBatch
     probs = [I.packing(s, 1, n_objects=k, n_obstacles=2) for s, k in enumerate([1, 6, 3][:len(sizes)])]
