@@ -302,7 +302,7 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
             const float4 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
             uint32_t sm = on ? __float_as_uint(w3.x) : 0u;
             const uint32_t ow = __float_as_uint(w3.y);
-            const uint32_t om = on ? ow & 0xFFu : 0u;
+            uint32_t om = on ? ow & 0xFFu : 0u;
             const int kk = (int)(ow >> 8 & 0xFFu), pp = (int)(ow >> 16);
             const float wl = w3.z;
             const float4 sp = tab[(OBJ ? kk * CT_MAX_OBJ_SPHERES : 0) + c0 + e];
@@ -328,10 +328,16 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
                 }
             }
             if (KT != 1) {
-#pragma unroll 1
-                for (int j = 0; j < KT; ++j) {
-                    const bool cand = om >> j & 1u;
-                    if (!__ballot(cand)) continue;   // wave-uniform
+                // the objects of the lane's owner, lowest first: the lanes of one
+                // owner take the same object, others another; `own` follows in
+                // the owner's own lanes
+                uint32_t own = omask;
+                while (__ballot(om != 0u)) {
+                    const bool cand = om != 0u;
+                    const int j = cand ? __builtin_ctz(om) : 0;
+                    om &= om - 1u;
+                    const int jo = own ? __builtin_ctz(own) : 0;
+                    own &= own - 1u;
                     const Box O = S.ob0[j];
                     const float4 pl = S.plc[j * S.P + pp];
                     const bool placed = j < kk;
@@ -364,9 +370,9 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
                                 while (bits) {
                                     const float4 v = rec[rel * nc + __builtin_ctz(bits)];
                                     bits &= bits - 1u;
-                                    gr[3 * j] -= v.x;
-                                    gr[3 * j + 1] -= v.y;
-                                    gr[3 * j + 2] -= v.z;
+                                    gr[3 * jo] -= v.x;
+                                    gr[3 * jo + 1] -= v.y;
+                                    gr[3 * jo + 2] -= v.z;
                                 }
                             }
                             wave_sync();
