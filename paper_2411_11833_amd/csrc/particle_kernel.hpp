@@ -79,12 +79,14 @@ __device__ __forceinline__ void pair_hit(float px, float py, float pz, float r, 
 }
 
 // The centres of the moved objects as one lane's step k sees them, for the
-// culling tests: object j (j < K) was placed by an earlier step (at P(rho_j),
-// a particle variable) or is still at its initial pose.  The lane keeps the
-// K centres in registers.
-template <int KT>
+// culling tests: object j was placed by an earlier step (at P(rho_j), a
+// particle variable) or is still at its initial pose.  The SPLIT lanes of a
+// slot share the objects out, lane si holds si, si + SPLIT, ... in registers
+// (past the last: the last again).
+template <int KT, int SPLIT>
 struct MoveCtx {
-    float x[KT], y[KT];
+    static constexpr int U = (KT + SPLIT - 1) / SPLIT;
+    float x[U], y[U];
     int k, p;   // step, column of the tile
 };
 
@@ -217,7 +219,7 @@ __device__ __forceinline__ uint32_t split_or(uint32_t v) {
 // L >= 0: robot link L (thresholds from the table); L < 0: an object's sphere
 // of radius rb (thresholds formed here).
 template <int KT, int SPLIT, bool LINK>
-__device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si, const MoveCtx<KT>& mc,
+__device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si, const MoveCtx<KT, SPLIT>& mc,
                                               const float2* __restrict__ ck, float wx, float wy, float wz, float rb,
                                               uint32_t& smask, uint32_t& omask) {
     const float q = wx * wx + wy * wy;
@@ -243,7 +245,8 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si,
     smask = split_or<SPLIT>(smask) & (nsb < 32 ? (1u << nsb) - 1u : ~0u);
     if (KT == 1) return;   // the only moved object is the one in the hand
 #pragma unroll
-    for (int j = 0; j < KT; ++j) {
+    for (int u = 0; u < MoveCtx<KT, SPLIT>::U; ++u) {
+        const int j = min(u * SPLIT + si, KT - 1);
         const CullBox C = S.cbx[nsb + j];
         float2 th;
         if (LINK) {
@@ -252,10 +255,11 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si,
             const float e = rb + C.r;
             th = make_float2(e * e * 1.000001f, rb + C.hz);
         }
-        const float dx = wx - mc.x[j], dy = wy - mc.y[j];
+        const float dx = wx - mc.x[u], dy = wy - mc.y[u];
         const bool hit = dx * dx + dy * dy < th.x && fabsf(wz - C.z) < th.y;
         omask |= hit ? 1u << j : 0u;
     }
+    omask = split_or<SPLIT>(omask);
     omask &= ~(1u << mc.k);   // the step's own object is held, not an obstacle
 }
 
@@ -268,7 +272,7 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si,
 // 48: tiles leave at most the tail of the last wave idle).
 template <int KT, int SPLIT, bool GRAD, bool OBJ>
 __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __restrict__ tab, int ns, int si,
-                                           const float R[9], const float t[3], const MoveCtx<KT>& mc, uint32_t smask,
+                                           const float R[9], const float t[3], const MoveCtx<KT, SPLIT>& mc, uint32_t smask,
                                            uint32_t omask, float lam, float& coll, float f[3], float tq[3],
                                            float* __restrict__ gr, int& nhit) {
     const bool mine = (smask | omask) != 0u;
@@ -413,7 +417,7 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
 // All robot spheres of link L (frame (R, t)).
 template <int KT, int SPLIT, bool GRAD>
 __device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const Joint& J, const TileLds& S, int L, int si,
-                                             const float R[9], const float t[3], const MoveCtx<KT>& mc, float lam,
+                                             const float R[9], const float t[3], const MoveCtx<KT, SPLIT>& mc, float lam,
                                              float& coll, float f[3], float tq[3], float* __restrict__ gr, int& nhit) {
     const int s0 = J.s0, ns = J.ns;
     if (ns == 0) return;
@@ -433,7 +437,7 @@ __device__ __forceinline__ void link_spheres(const Tables* __restrict__ T, const
 template <int KT, int SPLIT, bool GRAD>
 __device__ __forceinline__ void object_spheres(const Tables* __restrict__ T, const TileLds& S, bool use,
                                                float4 ob, int si, const float R[9], const float t[3],
-                                               const MoveCtx<KT>& mc, float lam, float& coll, float f[3], float tq[3],
+                                               const MoveCtx<KT, SPLIT>& mc, float lam, float& coll, float f[3], float tq[3],
                                                float* __restrict__ gr, int& nhit) {
     if (T->n_os <= 0) return;
     uint32_t smask, omask;
@@ -672,7 +676,7 @@ template <int KT, int SPLIT, bool GRAD, int JU>
 __device__ __forceinline__ void config_pass(const Tables* __restrict__ T, const TileLds& S, int si,
                                             const float jsn[CT_N_JOINTS], const float jcs[CT_N_JOINTS], bool held,
                                             bool kin, bool placing,
-                                            float lam, const MoveCtx<KT>& mc, float gx, float gy, float gz,
+                                            float lam, const MoveCtx<KT, SPLIT>& mc, float gx, float gy, float gz,
                                             float g_c, float g_s, float rho_x, float rho_y, float rho_c,
                                             float rho_s, float& coll, float gq[CT_N_JOINTS], float gg[4],
                                             float* __restrict__ gr, float& kin_pos, float& kin_rot,
@@ -870,13 +874,14 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     // centres are NaN, touch nothing and join no test
     const float none = __builtin_nanf("");
     const float rho_x = live ? own.x : none, rho_y = own.y, rho_c = own.z, rho_s = own.w;
-    MoveCtx<KT> mc;
+    MoveCtx<KT, SPLIT> mc;
 #pragma unroll
-    for (int j = 0; j < KT; ++j) {
-        const bool placed = j < k;
+    for (int u = 0; u < MoveCtx<KT, SPLIT>::U; ++u) {
+        const int j = min(u * SPLIT + si, KT - 1);
         const float4 pl = plc[j * xs_stride];
-        mc.x[j] = placed ? pl.x : T->obj0[j].cx;
-        mc.y[j] = placed ? pl.y : T->obj0[j].cy;
+        const Box& O = S.ob0[j];
+        mc.x[u] = j < k ? pl.x : O.cx;
+        mc.y[u] = j < k ? pl.y : O.cy;
     }
     mc.k = k;
     mc.p = p;
