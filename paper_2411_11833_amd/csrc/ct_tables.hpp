@@ -115,7 +115,9 @@ __host__ __device__ constexpr int tile_particles(int K, int SPLIT) { return WG /
 // the skeleton length alone decides come first.
 struct TileLayout {
     int xs, ms, vs, plc, cpart, flg, okp, wave, osl, ob0, frz, ctl, bc, sbx, cbx, tpart, hpart, rs, ck, part, total;
-    int np;   // floats of one lane's gradient partials, odd (consecutive lanes start in different banks)
+    // floats of one lane's gradient partials, and of a particle's: both odd, so
+    // that neighbouring lanes and particles start in different banks
+    int np, pp;
 };
 
 __host__ __device__ inline TileLayout tile_layout(int K, int split, int mode, int W, int n_static, int n_rs) {
@@ -148,7 +150,8 @@ __host__ __device__ inline TileLayout tile_layout(int K, int split, int mode, in
     o.rs = take(n_rs * 16);
     o.ck = take(8 * (n_static + K) * 8);
     o.np = (11 + 3 * K + (W > 0 ? CT_N_JOINTS : 0)) | 1;
-    o.part = take(mode == MODE_COST ? 0 : slots * split * o.np * 4);
+    o.pp = (2 * K * split * o.np) | 1;
+    o.part = take(mode == MODE_COST ? 0 : P * o.pp * 4);
     o.total = at;
     return o;
 }

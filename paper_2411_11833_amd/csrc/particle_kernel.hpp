@@ -183,7 +183,7 @@ struct TileLds {
     int* ctl;              // any_sat, halt
     float2* bc;            // [MAX_LAUNCH_ITERS] 1 - beta1^t, 1 - beta2^t of the launch's updates (fused step)
     float4* wave;          // WAVE_F4 per wave: owner records, then test results
-    int np, P;
+    int np, pp, P;   // floats of a lane's, of a particle's partials; columns
 };
 
 // Orders a wave's LDS accesses for the compiler: the lanes of a wave run in
@@ -1140,6 +1140,7 @@ __device__ __forceinline__ TileLds tile_lds(char* base, const TileLayout& o, int
     S.bc = (float2*)(base + o.bc);
     S.wave = (float4*)(base + o.wave);
     S.np = o.np;
+    S.pp = o.pp;
     S.P = P;
     return S;
 }
@@ -1288,7 +1289,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
                 asm volatile("" : "+s"(Ta));
                 const Tables* Ti = (const Tables*)(const __attribute__((address_space(4))) Tables*)Ta;
                 const LaneOut o = lane_slot<KT, SPLIT, MODE, EXT>(Ti, S, p, slot, si,
-                                                                  S.part + ((p * SLOTS + slot) * SPLIT + si) * NP,
+                                                                  S.part + p * S.pp + (slot * SPLIT + si) * NP,
                                                                   io.terms, ld, i, wt, i < n ? io.wts : nullptr, i < n);
                 if (si == 0) {
                     S.cpart[p * SLOTS + slot] = o.cost;
@@ -1346,7 +1347,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
                 const int64_t i = particle(p);
                 if (i >= n) continue;
                 const int k = d / CT_STEP_DIM, r = d - CT_STEP_DIM * k;
-                const float* pp = S.part + p * SLOTS * SPLIT * NP;
+                const float* pp = S.part + p * S.pp;
                 auto lane = [&](int slot, int si) { return pp + (slot * SPLIT + si) * NP; };
                 float g = 0.f;
 #pragma unroll
