@@ -387,8 +387,8 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
             const uint64_t any = __ballot(hits != 0);
             if (any) {
                 if (hits != 0) {
-                    rec[2 * lane] = make_float4(pen, gx, gy, gz);
-                    rec[2 * lane + 1] = make_float4(fmaf(cy, gz, -(cz * gy)), fmaf(cz, gx, -(cx * gz)), fmaf(cx, gy, -(cy * gx)),
+                    rec[lane] = make_float4(pen, gx, gy, gz);
+                    rec[64 + lane] = make_float4(fmaf(cy, gz, -(cz * gy)), fmaf(cz, gx, -(cx * gz)), fmaf(cx, gy, -(cy * gx)),
                                                     __int_as_float(hits));
                 }
                 wave_sync();
@@ -396,9 +396,9 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
                     uint32_t bits = (uint32_t)(any >> (rel * nc)) & (CLASS << si);
                     if (nc < 32) bits &= (1u << nc) - 1u;
                     while (bits) {
-                        const float4* v = rec + 2 * (rel * nc + __builtin_ctz(bits));
+                        const float4* v = rec + (rel * nc + __builtin_ctz(bits));
                         bits &= bits - 1u;
-                        const float4 u = v[0], m = v[1];
+                        const float4 u = v[0], m = v[64];
                         coll += u.x;
                         if (GRAD) {
                             f[0] += u.y; f[1] += u.z; f[2] += u.w;
