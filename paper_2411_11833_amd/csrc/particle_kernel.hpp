@@ -842,8 +842,9 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     // gradients 1.21 -> 1.14 ms, 100 steps of 256 one-step particles 1.39 ->
     // 1.31); the longer fused steps and the extended kernels would spill (64
     // skeletons 37.1 -> 39.3 ms, an augmented-Lagrangian round 2.16 -> 2.32)
-    // and take pairs (36.7, 2.13)
-    constexpr int JU = !EXT && (MODE != MODE_STEP || KT == 1) ? 8 : 2;
+    // and take pairs (36.7, 2.13), as do the cost kernels past 4 steps, which
+    // would pass the 168 registers of three waves (65536 x 6 steps 243 -> 326 us)
+    constexpr int JU = !EXT && (MODE == MODE_GRAD || (MODE == MODE_COST && KT <= 4) || KT == 1) ? 8 : 2;
     const bool self_on = EXT && T->self_on;   // wave-uniform; compiled out without EXT
     // per-particle weights only in extended kernels; plain kernels read lambda
     // from the tables where each term needs it
