@@ -9,20 +9,25 @@
 // Work decomposition (one workgroup = 256 lanes = 4 wave64s):
 //   * a particle owns 2K "slots", one per robot configuration (q_grasp and
 //     q_place of each step); each slot is served by SPLIT adjacent lanes that
-//     share its sphere list.  A workgroup holds P = 256 / (2K SPLIT) particles;
+//     share its spheres, culling tests and joint sines.  A workgroup's tile has
+//     P = 256 / (2K SPLIT) particle columns (a launch may fill fewer of them);
 //     lanes are slot-major, so a wave holds the same slot of many particles.
-//   * phase 0 stages the particles' columns of the dimension-major X in LDS
-//     (coalesced rows), phase 1 runs every lane's configuration: forward
-//     kinematics, sphere transforms, sphere-vs-box penetration with its
-//     adjoint fused into the same pass, pose / bound terms; gradients leave
-//     the lane as world-frame wrenches folded onto the joint axes.
-//   * the SPLIT lanes of a slot reduce with cross-lane shuffles; slots of a
-//     particle meet in LDS; phase 2 sums each coordinate's partials in a fixed
-//     order (bit-reproducible) and writes G or applies Adam in place.
+//   * phase 0 stages the particles' columns of the dimension-major X (and the
+//     fused step's moments) and the problem's tables in LDS; the fused step
+//     then runs every iteration of the launch on them.
+//   * phase 1 runs every lane's configuration: forward kinematics link by
+//     link, each link's bounding sphere against every box, then the spheres of
+//     the configurations that touch something, spread over the wave's lanes;
+//     pose / bound terms; gradients leave the lane as world-frame wrenches
+//     folded onto the joint axes.
+//   * slots of a particle meet in LDS; phase 2 sums each coordinate's partials
+//     in a fixed order (bit-reproducible, whatever the tile's filling) and
+//     writes G or applies Adam in place.
 //
-// Box and robot-sphere tables are read with wave-uniform indices (scalar
-// loads); per-lane data are the particle's own variables and the poses of
-// the objects it has already placed.
+// What bounds it (packing, 8192 particles, K = 4, SPLIT 2; one iteration 55.8
+// us with a launch each, 41 now): 54% of the wave time is issue, 45% waits on
+// LDS and scalar loads; 230 registers keep two waves per SIMD.  Link tables
+// are scalar loads, boxes and spheres LDS reads.
 #pragma once
 
 #include "ct_tables.hpp"

@@ -221,7 +221,7 @@ def default_adam(n: int, lr: float = 1e-2) -> B.CtAdam:
 
 class GpuBatch:
     """Many skeletons bound to their own particle buffers, stepped together by
-    one persistent launch per iteration (or, for comparison, one launch per
+    one persistent launch per 64 iterations (or, for comparison, one launch per
     skeleton)."""
 
     def __init__(self, problems: list, sizes: list[int], device="cuda", fixed_grasps: bool = True,
