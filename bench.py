@@ -225,7 +225,7 @@ def config1_line(args, dev, q):
            "us_per_iter": us, "median_us_per_iter": float(np.median(us)),
            "particle_iters_per_s": n / (float(np.median(us)) * 1e-6),
            "satisfied_at_iter_100": sat, "first_sat_iter": first,
-           "bound": "latency: 256 particles fill 32 of 256 compute units' worth of workgroups; no roofline"}
+           "bound": "latency: a chain of 100 dependent iterations in 256 tiles of one particle; no roofline"}
     log(f"[bench] config 1 (256 particles, single pick-place): {res['median_us_per_iter']:.1f} us/iter, "
         f"satisfied at iteration 100: {sat}", q)
     return res
