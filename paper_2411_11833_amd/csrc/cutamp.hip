@@ -610,7 +610,7 @@ extern "C" int ct_seed_uniform(const ct_problem* P, uint64_t seed, float* X, flo
     if (!P || !X || !good_layout(X, n, ld)) return CT_ERR_INVALID_ARG;
     if ((M && !good_layout(M, n, ld)) || (V && !good_layout(V, n, ld))) return CT_ERR_INVALID_ARG;
     if (n == 0) return CT_OK;
-    const dim3 grid((unsigned)((n + 255) / 256));
+    const dim3 grid((unsigned)((n + 255) / 256), (unsigned)((P->D + 3) / 4));
     hipLaunchKernelGGL(ct::seed_uniform_kernel, grid, dim3(256), 0, (hipStream_t)stream, P->d,
                        (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), X, M, V, n, ld);
     return err_of(hipGetLastError());
