@@ -873,47 +873,64 @@ namespace {
 int batch_split(const ct_batch* B) { return B->split ? B->split : 1; }
 int batch_workgroups(const ct_batch* B) { return B->workgroups ? B->workgroups : 2 * B->n_cu; }
 
-// Particles of each skeleton's tiles: where full tiles leave workgroups idle,
-// every skeleton's are divided by the largest number that keeps all tiles
-// within MAX_TILES (8192 x 4 placements of one object, split 1: 256 full
-// tiles 5.38 ms; halved, 512, 4.37; quartered, 1024, 6.85).
-int64_t batch_tiles(ct_batch* B, int split, int parts) {
+// Particles of each skeleton's tiles (into `skels`): where full tiles leave
+// workgroups idle, every skeleton's are divided by the largest number that
+// keeps all tiles within MAX_TILES (8192 x 4 placements of one object, split
+// 1: 256 full tiles 5.38 ms; halved, 512, 4.37; quartered, 1024, 6.85).
+int64_t batch_tiles(const ct_batch* B, int split, int parts, std::vector<ct::BatchSkel>& skels) {
     int64_t tiles = 0;
     for (size_t s = 0; s < B->probs.size(); ++s) {
         const int per = (ct::tile_particles(B->probs[s]->K, split) + parts - 1) / parts;
-        B->skels[s].per = per;
-        tiles += (B->skels[s].n + per - 1) / per;
+        skels[s].per = per;
+        tiles += (skels[s].n + per - 1) / per;
     }
     return tiles;
 }
 
-// (skeleton, tile) items for the current split, largest tiles first: a tile's
-// work grows with the boxes each of its configurations is tested against
-int batch_build_items(ct_batch* B) {
-    const int split = batch_split(B);
+// The skeleton table and the (skeleton, tile) items for a split, largest tiles
+// first: a tile's work grows with the boxes each of its configurations is
+// tested against.  Launches in flight on any stream read the old tables, and a
+// copy on the legacy stream waits for none of the non-blocking ones, so the
+// new tables are buffers of their own and the old ones are freed after the
+// device is done with them.  On failure the batch keeps its split and tables.
+int batch_set_split(ct_batch* B, int split) try {
+    std::vector<ct::BatchSkel> skels = B->skels;
+    const int s_eff = split ? split : 1;
     int parts = 1;
-    while (parts < 256 && batch_tiles(B, split, parts + 1) <= MAX_TILES) ++parts;
-    batch_tiles(B, split, parts);
-    if (hipMemcpy(B->d_skels, B->skels.data(), B->skels.size() * sizeof(ct::BatchSkel), hipMemcpyHostToDevice) != hipSuccess)
-        return CT_ERR_DEVICE;
+    while (parts < 256 && batch_tiles(B, s_eff, parts + 1, skels) <= MAX_TILES) ++parts;
+    batch_tiles(B, s_eff, parts, skels);
     std::vector<std::pair<int, int2>> items;
     for (size_t s = 0; s < B->probs.size(); ++s) {
         const ct_problem* P = B->probs[s];
-        const int64_t tiles = (B->skels[s].n + B->skels[s].per - 1) / B->skels[s].per;
+        const int64_t tiles = (skels[s].n + skels[s].per - 1) / skels[s].per;
         const int w = P->h.n_static + P->K - 1 + 2 * P->h.W * 1;
         for (int64_t t = 0; t < tiles; ++t) items.push_back({w, make_int2((int)s, (int)t)});
     }
     std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
     std::vector<int2> flat(items.size());
     for (size_t i = 0; i < items.size(); ++i) flat[i] = items[i].second;
-    if (B->d_items) hipFree(B->d_items);
-    B->d_items = nullptr;
-    B->n_items = (int32_t)flat.size();
-    if (flat.empty()) return CT_OK;
-    if (hipMalloc(&B->d_items, flat.size() * sizeof(int2)) != hipSuccess) return CT_ERR_ALLOC;
-    if (hipMemcpy(B->d_items, flat.data(), flat.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess)
-        return CT_ERR_DEVICE;
-    return CT_OK;
+    const size_t sk_bytes = skels.size() * sizeof(ct::BatchSkel), it_bytes = flat.size() * sizeof(int2);
+    ct::BatchSkel* d_skels = nullptr;
+    int2* d_items = nullptr;
+    int rc = CT_OK;
+    if (hipMalloc(&d_skels, sk_bytes) != hipSuccess || (it_bytes && hipMalloc(&d_items, it_bytes) != hipSuccess))
+        rc = CT_ERR_ALLOC;
+    else if (hipMemcpy(d_skels, skels.data(), sk_bytes, hipMemcpyHostToDevice) != hipSuccess ||
+             (it_bytes && hipMemcpy(d_items, flat.data(), it_bytes, hipMemcpyHostToDevice) != hipSuccess) ||
+             hipDeviceSynchronize() != hipSuccess)
+        rc = CT_ERR_DEVICE;
+    if (rc == CT_OK) {
+        std::swap(B->d_skels, d_skels);
+        std::swap(B->d_items, d_items);
+        B->skels.swap(skels);
+        B->n_items = (int32_t)flat.size();
+        B->split = split;
+    }
+    if (d_skels) hipFree(d_skels);
+    if (d_items) hipFree(d_items);
+    return rc;
+} catch (const std::bad_alloc&) {   // host memory, before any device buffer
+    return CT_ERR_ALLOC;
 }
 
 int batch_launch(ct_batch* B, const ct_adam* adam, int32_t t, int32_t iters, hipStream_t st) {
@@ -987,14 +1004,9 @@ extern "C" int ct_batch_create(int32_t count, ct_problem* const* problems, float
         B->skels.push_back(k);
     }
     int rc = CT_OK;
-    if (hipMalloc(&B->d_skels, count * sizeof(ct::BatchSkel)) != hipSuccess ||
-        hipMalloc(&B->d_queue, 2 * sizeof(int32_t)) != hipSuccess)
-        rc = CT_ERR_ALLOC;
-    if (rc == CT_OK && hipMemcpy(B->d_skels, B->skels.data(), count * sizeof(ct::BatchSkel),
-                                 hipMemcpyHostToDevice) != hipSuccess)
-        rc = CT_ERR_DEVICE;
+    if (hipMalloc(&B->d_queue, 2 * sizeof(int32_t)) != hipSuccess) rc = CT_ERR_ALLOC;
     if (rc == CT_OK && hipMemset(B->d_queue, 0, 2 * sizeof(int32_t)) != hipSuccess) rc = CT_ERR_DEVICE;
-    if (rc == CT_OK) rc = batch_build_items(B);
+    if (rc == CT_OK) rc = batch_set_split(B, 0);
     if (rc != CT_OK) {
         ct_batch_destroy(B);
         return rc;
@@ -1015,11 +1027,14 @@ extern "C" int ct_batch_destroy(ct_batch* B) {
 
 extern "C" int ct_batch_set_tuning(ct_batch* B, int32_t split, int32_t workgroups, int32_t persistent) {
     if (!B || !(split == 0 || split == 1 || split == 2 || split == 4) || workgroups < 0) return CT_ERR_INVALID_ARG;
-    const bool rebuild = batch_split(B) != (split ? split : 1);
+    if (batch_split(B) != (split ? split : 1)) {
+        const int rc = batch_set_split(B, split);
+        if (rc != CT_OK) return rc;
+    }
     B->split = split;
     B->workgroups = workgroups;
     B->persistent = persistent ? 1 : 0;
-    return rebuild ? batch_build_items(B) : CT_OK;
+    return CT_OK;
 }
 
 extern "C" int ct_batch_step(ct_batch* B, int64_t t, const ct_adam* adam, void* stream) {
