@@ -281,7 +281,9 @@ int ct_step(const ct_problem *problem, float *X, float *M, float *V, int64_t n, 
  * with the same results.  In that mode a particle the step finds
  * satisfying is not updated, so after the stop the rows of X whose mask is 1
  * are exactly the satisfying iterates (the other rows took that step's
- * update).
+ * update).  first_sat may be shared with solves on other streams: a stop that
+ * another one reports takes effect at this call's next launch, at the same
+ * step for every particle.
  */
 int ct_optimize(ct_problem *problem, float *X, float *M, float *V, int64_t n, int64_t ld,
                 int64_t t0, int32_t iters, const ct_adam *adam, const uint8_t *frozen,

@@ -159,11 +159,15 @@ __host__ __device__ inline TileLayout tile_layout(int K, int split, int mode, in
 // Stop-at-first of the fused step: on = leave after the first iteration that
 // finds a satisfying particle; with several iterations per launch, the copies
 // [D][ld] of the state the launch started from, the iterations each workgroup
-// ran, and whether this is the second launch that runs tiles back from them.
+// ran (0: it found the solve stopped), and whether this is the second launch
+// that brings every tile to the iteration of the stop.  own: that iteration, a
+// word which nobody but a launch and its second launch reads or writes
+// (STOP_NONE before the launch, which clears own_next for the one after it).
+constexpr int32_t STOP_NONE = 0x7FFFFFFF;
 struct StopArgs {
     int32_t on, redo;
     float *Xb, *Mb, *Vb;
-    int32_t* ran;
+    int32_t *ran, *own, *own_next;
 };
 
 // One skeleton of a batch, as the persistent kernel sees it.

@@ -22,11 +22,13 @@ struct ct_problem {
     int K = 0, D = 0, n_terms = 0, nc = 0;
     int split = 0;              // 0 = default
     int32_t* counts = nullptr;  // n_constraint per-constraint counts (feasibility)
-    // stop-at-first workspace of ct_optimize (copies of X, M, V and the
-    // iterations each workgroup ran), grown on demand; `ws_used` is recorded
-    // after every use, so that a call on another stream waits for it
+    // stop-at-first workspace of ct_optimize (two control words that
+    // launches use in turn, copies of X, M, V and the iterations each workgroup
+    // ran), grown on demand; `ws_used` is recorded after every use, so that a
+    // call on another stream waits for it
     void* ws = nullptr;
     size_t ws_bytes = 0;
+    int ws_turn = 0;
     hipEvent_t ws_used = nullptr;
     hipStream_t ws_stream = nullptr;
     const float* wts = nullptr;  // per-particle term weights (ct_set_term_weights), or null
@@ -701,11 +703,13 @@ int step_impl(const ct_problem* P, float* X, float* M, float* V, int64_t n, int6
     return run_pk(P, ct::MODE_STEP, a, st, split);
 }
 
-// Workspace of a stop-at-first launch over several iterations: the copies of
-// X, M and V and one counter per workgroup, ready for use on `st`.  False
+// Workspace of a stop-at-first launch over several iterations: the control
+// words, the copies of X, M and V and one counter per workgroup, ready for use
+// on `st`.  False
 // when it cannot be had (`st` is being captured, so a replay could overlap
 // another user of the buffer, or device memory is short): the caller then
 // launches one iteration at a time, which needs none.
+constexpr size_t WS_HEAD = 64;   // words ahead of the copies: two control words, WS_HEAD / 2 apart
 bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t st, ct::StopArgs& out) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
@@ -715,7 +719,7 @@ bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t
     if (cap != hipStreamCaptureStatusNone) return false;
     const size_t state = (size_t)P->D * (size_t)ld;
     const int64_t per = tile_per(P->K, split, n);
-    const size_t bytes = (3 * state + (size_t)((n + per - 1) / per)) * sizeof(float);
+    const size_t bytes = (WS_HEAD + 3 * state + (size_t)((n + per - 1) / per)) * sizeof(float);
     if (!P->ws_used && hipEventCreateWithFlags(&P->ws_used, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         P->ws_used = nullptr;
@@ -734,12 +738,17 @@ bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t
             return false;
         }
         P->ws_bytes = bytes;
+        if (hipMemsetD32Async((hipDeviceptr_t)P->ws, ct::STOP_NONE, WS_HEAD, st) != hipSuccess) {
+            (void)hipGetLastError();
+            P->ws_bytes = 0;   // grown again, and its words set, by the next call
+            return false;
+        }
     } else if (st != P->ws_stream && hipStreamWaitEvent(st, P->ws_used, 0) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     P->ws_stream = st;
-    out.Xb = (float*)P->ws;
+    out.Xb = (float*)P->ws + WS_HEAD;
     out.Mb = out.Xb + state;
     out.Vb = out.Mb + state;
     out.ran = (int32_t*)(out.Vb + state);
@@ -778,10 +787,15 @@ extern "C" int ct_optimize(ct_problem* P, float* X, float* M, float* V, int64_t 
     int rc = CT_OK;
     for (int32_t done = 0; done < iters && rc == CT_OK;) {
         const int32_t c = std::min(per, iters - done);
+        if (stop.Xb) {
+            stop.own = (int32_t*)P->ws + WS_HEAD / 2 * P->ws_turn;
+            stop.own_next = (int32_t*)P->ws + WS_HEAD / 2 * (1 - P->ws_turn);
+        }
         rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, stop);
         if (rc == CT_OK && stop.Xb) {
             ct::StopArgs redo = stop;
             redo.redo = 1;
+            P->ws_turn = 1 - P->ws_turn;
             rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, redo);
         }
         done += c;

@@ -1166,7 +1166,8 @@ struct TileIO {
     // tile leaves its iteration loop after a step that found one
     int stop = 0;
     float *Xb = nullptr, *Mb = nullptr, *Vb = nullptr;   // copies of the state the launch started from, or null
-    int redo = 0;   // start from those copies, run every iteration, report nothing
+    int32_t* own = nullptr;   // the iteration of the launch's stop, or null (a launch of one iteration)
+    int redo = 0;   // start from those copies (or, null, from X), run every iteration, report nothing
     int32_t* hits = nullptr;   // cost mode: touching sphere-box pairs per particle, or null
     int per = 0;               // particles of a tile (1 .. P)
 };
@@ -1221,7 +1222,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
             xv[u] = mv[u] = vv[u] = 0.f;
             if (idx < D * P && i < n) {
                 const int64_t a = d * ld + i;
-                if (MV && io.redo) {
+                if (MV && io.redo && io.Xb) {
                     xv[u] = io.Xb[a]; mv[u] = io.Mb[a]; vv[u] = io.Vb[a];
                     if (!mv_lds) { io.M[a] = mv[u]; io.V[a] = vv[u]; }
                 } else {
@@ -1266,8 +1267,9 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
         const int32_t iter = t + done - 1;   // 0-based index of this iteration
         const bool last = MODE != MODE_STEP || done + 1 == iters;
         // stop-at-first: an earlier iteration of another tile found a particle
-        if (MODE == MODE_STEP && io.stop && tid == 0)
-            S.ctl[1] = __hip_atomic_load(io.first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < iter ? 1 : 0;
+        // (never at the first, so an iteration always ran before the loop ends)
+        if (MODE == MODE_STEP && io.own && tid == 0)
+            S.ctl[1] = __hip_atomic_load(io.own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < iter ? 1 : 0;
         for (int idx = tid; idx < K * P; idx += WG) {
             const int j = idx / P, p = idx - j * P;
             const float* col = S.xs + p;
@@ -1339,7 +1341,10 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
         }
         __syncthreads();
         const bool sat = S.ctl[0];   // workgroup-uniform; stays set: only the first iteration counts
-        if (sat && !reported && io.first_sat && !io.redo && tid == 0) atomicMin(io.first_sat, iter);
+        if (sat && !reported && io.first_sat && !io.redo && tid == 0) {
+            atomicMin(io.first_sat, iter);
+            if (io.own) atomicMin(io.own, iter);
+        }
         reported = reported || sat;
 
         if (MODE != MODE_COST) {
@@ -1424,8 +1429,11 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
 // a tile may run past the iteration at which another found the first
 // satisfying particle.  The launch therefore keeps a copy of the state it
 // started from, and a second launch (redo) runs the tiles that went past that
-// iteration again, from the copy, up to it; when no particle was found in the
-// launch it returns at once.  A launch of one iteration needs neither.
+// iteration again, from the copy, up to it.  A launch of one iteration needs
+// neither.  first_sat may be shared with other solves and drop at any time: a
+// workgroup reads it once, at entry.  Should some workgroups of a launch have
+// found the solve stopped and others not, the second launch runs the former
+// forward to where the latter are.
 template <int SPLIT, int MODE, int KT, bool EXT>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void particle_kernel(
     const Tables* __restrict__ T, float* __restrict__ X, float* __restrict__ M, float* __restrict__ V,
@@ -1435,15 +1443,37 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     const float* __restrict__ wts, int32_t* __restrict__ hits) {
     extern __shared__ __attribute__((aligned(16))) char tile_mem[];
     int run = iters;
+    bool fresh = false;   // redo of a workgroup that has not run
     if (MODE == MODE_STEP && stop.on) {
-        // every workgroup takes the same branch: this launch only writes
-        // values >= t - 1, a redo launch none
-        const int32_t f = __hip_atomic_load(first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (f < t - 1) return;   // stopped before this launch
+        int32_t* word = (int32_t*)tile_mem;
         if (stop.redo) {
-            if (f > t - 2 + iters) return;   // no particle found by the launch
-            run = f - t + 2;
-            if (stop.ran[blockIdx.x] == run) return;
+            // everything read here was written by the launch before
+            const int32_t ran = stop.ran[blockIdx.x], f = *stop.own;
+            if (f != STOP_NONE) run = f - t + 2;
+            if (ran == run) return;
+            if (ran == 0) {   // run now if any other workgroup did
+                if (threadIdx.x == 0) *word = 0;
+                __syncthreads();
+                for (uint32_t b = threadIdx.x; b < gridDim.x; b += WG)
+                    if (stop.ran[b]) *word = 1;
+                __syncthreads();
+                fresh = *word;
+                __syncthreads();
+                if (!fresh) return;
+            }
+        } else {
+            if (threadIdx.x == 0) *word = __hip_atomic_load(first_sat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int32_t f = *word;
+            __syncthreads();
+            if (stop.own && threadIdx.x == 0) {
+                if (blockIdx.x == 0) *stop.own_next = STOP_NONE;
+                if (f < t - 1)
+                    stop.ran[blockIdx.x] = 0;
+                else if (f <= t - 2 + iters)
+                    atomicMin(stop.own, f);   // stopped inside the launch
+            }
+            if (f < t - 1) return;   // stopped before this launch
         }
     }
     // XCD-aware tile order: consecutive workgroups are dealt round-robin to the
@@ -1455,10 +1485,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void pa
     if (MODE == MODE_COST) io.hits = hits;
     if (MODE == MODE_STEP) {
         io.stop = stop.on;
-        io.Xb = stop.Xb;
+        io.Xb = fresh ? nullptr : stop.Xb;
         io.Mb = stop.Mb;
         io.Vb = stop.Vb;
         io.redo = stop.redo;
+        io.own = stop.redo ? nullptr : stop.own;
     }
     const int ran = run_tile<KT, SPLIT, MODE, EXT>(io, tile * per, tile_mem, lr, b1, b2, eps, t, run);
     if (MODE == MODE_STEP && stop.ran && !stop.redo && threadIdx.x == 0) stop.ran[blockIdx.x] = ran;
