@@ -93,6 +93,10 @@ struct MoveCtx {
     static constexpr int U = (KT + SPLIT - 1) / SPLIT;
     float x[U], y[U];
     int k, p;   // step, column of the tile
+    // nans: a NaN centre counts as touching, so that the penetrations it is in
+    // come out non-finite; live: the column has a particle (both compile-time
+    // constants in the fused step, see lane_slot)
+    bool nans, live;
 };
 
 // Bijection from the launch index to a tile index that keeps each XCD's
@@ -211,7 +215,8 @@ constexpr int WAVE_F4 = 128;
 // through: the circle's squared test |w - c|^2 < (rb + r)^2 is taken as
 // |w|^2 - 2 w.c < K with K = (rb + r)^2 - |c|^2 and a margin for its rounding
 // from the host.  The bounding sphere holds its set with a margin, so a box
-// left out touches no sphere of the set and every sum is unchanged.  The SPLIT
+// left out touches no sphere of the set and every sum is unchanged; with
+// mc.nans only a centre known to be too far leaves a box out.  The SPLIT
 // lanes of a slot hold the same bounding sphere and share the static boxes
 // out: lane si tests boxes si, si + SPLIT, ...
 template <int SPLIT>
@@ -242,7 +247,8 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si,
             th = make_float2(fmaf(e, e, C.kc), rb + C.hz);
         }
         const float t = fmaf(C.m2x, wx, fmaf(C.m2y, wy, q));
-        const bool hit = t < th.x && fabsf(wz - C.z) < th.y;
+        const float z = fabsf(wz - C.z);
+        const bool hit = mc.nans ? !(t >= th.x) && !(z >= th.y) : t < th.x && z < th.y;
         smask |= hit ? bit : 0u;
         bit <<= SPLIT;
     }
@@ -260,8 +266,8 @@ __device__ __forceinline__ void touched_boxes(const TileLds& S, int nsb, int si,
             const float e = rb + C.r;
             th = make_float2(e * e * 1.000001f, rb + C.hz);
         }
-        const float dx = wx - mc.x[u], dy = wy - mc.y[u];
-        const bool hit = dx * dx + dy * dy < th.x && fabsf(wz - C.z) < th.y;
+        const float dx = wx - mc.x[u], dy = wy - mc.y[u], t = dx * dx + dy * dy, z = fabsf(wz - C.z);
+        const bool hit = mc.nans ? !(t >= th.x) && !(z >= th.y) : t < th.x && z < th.y;
         omask |= hit ? 1u << j : 0u;
     }
     omask = split_or<SPLIT>(omask);
@@ -280,7 +286,7 @@ __device__ __forceinline__ void sphere_set(const TileLds& S, const float4* __res
                                            const float R[9], const float t[3], const MoveCtx<KT, SPLIT>& mc, uint32_t smask,
                                            uint32_t omask, float lam, float& coll, float f[3], float tq[3],
                                            float* __restrict__ gr, int& nhit) {
-    const bool mine = (smask | omask) != 0u;
+    const bool mine = (smask | omask) != 0u && mc.live;
     const uint64_t owners = __ballot(mine);
     if (!owners) return;   // wave-uniform: no configuration of the wave touches a box
     const int lane = threadIdx.x & 63;
@@ -877,16 +883,23 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
     sincosf(gyaw, &g_s, &g_c);
     const float4 own = plc[k * xs_stride];
     // a column without a particle is evaluated at NaN sines and placement: its
-    // centres are NaN, touch nothing and join no test
+    // centres are NaN and join no test
     const float none = __builtin_nanf("");
     const float rho_x = live ? own.x : none, rho_y = own.y, rho_c = own.z, rho_s = own.w;
     MoveCtx<KT, SPLIT> mc;
+    // cost and gradient kernels let a NaN coordinate reach every penetration it
+    // enters (a term of 0 would count as satisfied); in the fused step the pose
+    // errors alone make its particle's cost non-finite and its mask 0, and the
+    // tests of NaN would cost it up to 3% (1501 x 6 steps 580 us without, 601
+    // with; 64 skeletons 32.7 and 33.2 ms)
+    mc.nans = MODE != MODE_STEP;
+    mc.live = !mc.nans || live;
 #pragma unroll
     for (int u = 0; u < MoveCtx<KT, SPLIT>::U; ++u) {
         const int j = min(u * SPLIT + si, KT - 1);
         const float4 pl = plc[j * xs_stride];
         const Box& O = S.ob0[j];
-        mc.x[u] = j < k ? pl.x : O.cx;
+        mc.x[u] = j < k ? (mc.nans ? fmaf(0.f, pl.z, pl.x) : pl.x) : O.cx;   // NaN with the yaw, too
         mc.y[u] = j < k ? pl.y : O.cy;
     }
     mc.k = k;
