@@ -1100,13 +1100,16 @@ struct GradFinishArgs {
     float* loss;
 };
 
-// loss = inv * sum of the row sums (one workgroup, fixed summation order)
+// loss = inv * sum of the row sums (one workgroup, fixed summation order: 256
+// threads add; the whole workgroup calls, for the barriers)
 __device__ __forceinline__ void loss_reduce(const float* __restrict__ row_loss, int64_t rows, float inv,
                                             float* __restrict__ loss) {
     __shared__ float red[256];
-    float acc = 0.f;
-    for (int64_t r = threadIdx.x; r < rows; r += 256) acc += row_loss[r];
-    red[threadIdx.x] = acc;
+    if (threadIdx.x < 256) {
+        float acc = 0.f;
+        for (int64_t r = threadIdx.x; r < rows; r += 256) acc += row_loss[r];
+        red[threadIdx.x] = acc;
+    }
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
@@ -1217,7 +1220,7 @@ __global__ __launch_bounds__(AT_T) void adam_refresh_kernel(AdamArgs a) {
     }
     blk -= a.bstart[a.L];
     if (blk == 0) {
-        if (a.finish && a.fin.row_loss && tid < 256) loss_reduce(a.fin.row_loss, a.fin.rows, a.fin.loss_scale, a.fin.loss);
+        if (a.finish && a.fin.row_loss) loss_reduce(a.fin.row_loss, a.fin.rows, a.fin.loss_scale, a.fin.loss);
         return;
     }
     --blk;
