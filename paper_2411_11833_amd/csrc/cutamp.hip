@@ -24,13 +24,14 @@ struct ct_problem {
     int32_t* counts = nullptr;  // n_constraint per-constraint counts (feasibility)
     // stop-at-first workspace of ct_optimize (two control words that
     // launches use in turn, copies of X, M, V and the iterations each workgroup
-    // ran), grown on demand; `ws_used` is recorded after every use, so that a
-    // call on another stream waits for it
+    // ran), grown on demand; `ws_used` is recorded after every use, and every
+    // use waits for it: a stream's handle does not tell whether the last use
+    // was on the same stream (hipStreamPerThread is another stream in every
+    // thread, and the handle of a destroyed stream is given out again)
     void* ws = nullptr;
     size_t ws_bytes = 0;
     int ws_turn = 0;
     hipEvent_t ws_used = nullptr;
-    hipStream_t ws_stream = nullptr;
     const float* wts = nullptr;  // per-particle term weights (ct_set_term_weights), or null
     int64_t wts_ld = 0;
 };
@@ -743,11 +744,10 @@ bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t
             P->ws_bytes = 0;   // grown again, and its words set, by the next call
             return false;
         }
-    } else if (st != P->ws_stream && hipStreamWaitEvent(st, P->ws_used, 0) != hipSuccess) {
+    } else if (hipStreamWaitEvent(st, P->ws_used, 0) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    P->ws_stream = st;
     out.Xb = (float*)P->ws + WS_HEAD;
     out.Mb = out.Xb + state;
     out.Vb = out.Mb + state;
