@@ -43,10 +43,25 @@ def test_calls_from_threads_wait_for_each_other():
         solve(s, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
     assert 0 < int(want[0][5].item()) < 59
-    for s in got:   # one call after another, without a wait for the device
-        t = threading.Thread(target=solve, args=(s, PER_THREAD))
-        t.start()
-        t.join()
+    # one call after another, without a wait for the device; the threads stay,
+    # as their streams go with them, whatever still runs there
+    over, threads = threading.Event(), []
+    for s in got:
+        called = threading.Event()
+
+        def work(s=s, called=called):
+            try:
+                solve(s, PER_THREAD)
+            finally:
+                called.set()
+            over.wait()
+
+        threads.append(threading.Thread(target=work))
+        threads[-1].start()
+        called.wait()
     torch.cuda.synchronize()
+    over.set()
+    for t in threads:
+        t.join()
     for a, b in zip(got, want):
         assert all(torch.equal(u, v) for u, v in zip(a, b))
