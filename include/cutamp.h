@@ -268,8 +268,9 @@ int ct_step(const ct_problem *problem, float *X, float *M, float *V, int64_t n, 
 
 /*
  * `iters` fused steps with updates t0+1 .. t0+iters, in one kernel launch
- * for every 64 of them: a workgroup keeps its particles on chip from the
- * first update of a launch to the last.  cost / mask hold the
+ * for every 64 of them (with stop_at_first and more particles than the chip
+ * holds at once, for at most an eighth of the updates so far): a workgroup
+ * keeps its particles on chip from the first update of a launch to the last.  cost / mask hold the
  * values of the last executed step; first_sat as in ct_step.  With
  * stop_at_first != 0 (first_sat required), a step whose predecessors already
  * produced a satisfying particle does nothing, so a whole iteration budget
@@ -283,7 +284,8 @@ int ct_step(const ct_problem *problem, float *X, float *M, float *V, int64_t n, 
  * are exactly the satisfying iterates (the other rows took that step's
  * update).  first_sat may be shared with solves on other streams: a stop that
  * another one reports takes effect at this call's next launch, at the same
- * step for every particle.
+ * step for every particle (calls of one iteration, and calls on a stream that
+ * is being captured, excepted: there some particles may take a step more).
  */
 int ct_optimize(ct_problem *problem, float *X, float *M, float *V, int64_t n, int64_t ld,
                 int64_t t0, int32_t iters, const ct_adam *adam, const uint8_t *frozen,

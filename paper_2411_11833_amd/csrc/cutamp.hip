@@ -26,8 +26,7 @@ struct ct_problem {
     // launches use in turn, copies of X, M, V and the iterations each workgroup
     // ran), grown on demand; `ws_used` is recorded after every use, and every
     // use waits for it: a stream's handle does not tell whether the last use
-    // was on the same stream (hipStreamPerThread is another stream in every
-    // thread, and the handle of a destroyed stream is given out again)
+    // was on the same stream (hipStreamPerThread is another one in every thread)
     void* ws = nullptr;
     size_t ws_bytes = 0;
     int ws_turn = 0;
@@ -755,6 +754,26 @@ bool stop_workspace(ct_problem* P, int64_t n, int64_t ld, int split, hipStream_t
     return true;
 }
 
+// Whether a fused step's tiles go through the chip one after another: more of
+// them than the compute units hold at once (two each, or as their LDS allows).
+bool tiles_wait(const ct_problem* P, int64_t n, int split) {
+    const int64_t per = tile_per(P->K, split, n);
+    const int lds = ct::tile_layout(P->K, split, ct::MODE_STEP, P->h.W, P->h.n_static, P->h.link_start[9]).total;
+    return (n + per - 1) / per > std::min<int64_t>(MAX_TILES, MAX_TILES / 2 * (160 * 1024 / lds));
+}
+
+// Iterations of the next launch of a stop-at-first solve whose tiles wait for
+// each other, after t updates.  The first tiles run all of them before the
+// last ones start, and run again up to a stop that a late tile finds: at most
+// an eighth of the iterations so far, so that a stop costs no more than a
+// quarter of what led to it.  64 iterations of 65536 x 4 steps stopped at the
+// first one by the last tile: 9.0 ms in one launch, 0.55 so; never stopped, 512
+// iterations take 118.6 ms either way (262144 x 1 step 89.4 and 91.5 ms, the
+// most seen).
+int32_t stop_iters(int64_t t) {
+    return (int32_t)std::min<int64_t>(ct::MAX_LAUNCH_ITERS, std::max<int64_t>(1, t / 8));
+}
+
 bool valid_step_args(const ct_problem* P, float* X, float* M, float* V, int64_t n, int64_t ld,
                      const ct_adam* adam) {
     return P && X && M && V && valid_adam(adam) && good_layout(X, n, ld) && good_layout(M, n, ld) &&
@@ -780,27 +799,28 @@ extern "C" int ct_optimize(ct_problem* P, float* X, float* M, float* V, int64_t 
     if (n == 0 || iters == 0) return CT_OK;
     hipStream_t st = (hipStream_t)stream;
     const int split = effective_split(P, n);
-    int32_t per = ct::MAX_LAUNCH_ITERS;
     ct::StopArgs stop{};
     stop.on = stop_at_first ? 1 : 0;
-    if (stop.on && iters > 1 && !stop_workspace(P, n, ld, split, st, stop)) per = 1;
+    const bool ws = stop.on && iters > 1 && stop_workspace(P, n, ld, split, st, stop);
+    const bool waves = stop.on && tiles_wait(P, n, split);
     int rc = CT_OK;
     for (int32_t done = 0; done < iters && rc == CT_OK;) {
-        const int32_t c = std::min(per, iters - done);
-        if (stop.Xb) {
+        const int32_t c = std::min(stop.on && !ws ? 1 : waves ? stop_iters(t0 + done) : ct::MAX_LAUNCH_ITERS, iters - done);
+        if (ws) {
             stop.own = (int32_t*)P->ws + WS_HEAD / 2 * P->ws_turn;
             stop.own_next = (int32_t*)P->ws + WS_HEAD / 2 * (1 - P->ws_turn);
         }
-        rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, stop);
-        if (rc == CT_OK && stop.Xb) {
-            ct::StopArgs redo = stop;
-            redo.redo = 1;
+        ct::StopArgs now = stop;
+        if (c == 1) now.Xb = now.Mb = now.Vb = nullptr;   // nothing to roll back
+        rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, now);
+        if (rc == CT_OK && ws) {
+            now.redo = 1;
             P->ws_turn = 1 - P->ws_turn;
-            rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, redo);
+            rc = step_impl(P, X, M, V, n, ld, t0 + done + 1, adam, frozen, cost, mask, first_sat, st, split, c, now);
         }
         done += c;
     }
-    if (stop.Xb && hipEventRecord(P->ws_used, st) != hipSuccess && rc == CT_OK) rc = CT_ERR_DEVICE;
+    if (ws && hipEventRecord(P->ws_used, st) != hipSuccess && rc == CT_OK) rc = CT_ERR_DEVICE;
     return rc;
 }
 

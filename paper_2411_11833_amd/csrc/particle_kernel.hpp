@@ -1443,7 +1443,7 @@ __device__ __forceinline__ int run_tile(const TileIO& io, int64_t p0, char* lds,
 // satisfying particle.  The launch therefore keeps a copy of the state it
 // started from, and a second launch (redo) runs the tiles that went past that
 // iteration again, from the copy, up to it.  A launch of one iteration needs
-// neither.  first_sat may be shared with other solves and drop at any time: a
+// no copy.  first_sat may be shared with other solves and drop at any time: a
 // workgroup reads it once, at entry.  Should some workgroups of a launch have
 // found the solve stopped and others not, the second launch runs the former
 // forward to where the latter are.
