@@ -277,9 +277,10 @@ int ct_step(const ct_problem *problem, float *X, float *M, float *V, int64_t n, 
  * can be enqueued at once and still stops at the first solution
  * (Sec. IV-B, stopping criterion).  This mode keeps copies of the state in a
  * workspace of the handle (3 dim ld floats, allocated on the first such call
- * and when a larger one needs more); on a stream that is being captured, or
- * when the memory cannot be had, it launches one iteration at a time instead,
- * with the same results.  In that mode a particle the step finds
+ * and when a larger one needs more, and released with the handle); where they
+ * would take more than 1 GiB, on a stream that is being captured, or when the
+ * memory cannot be had, it launches one iteration at a time instead, with the
+ * same results.  In that mode a particle the step finds
  * satisfying is not updated, so after the stop the rows of X whose mask is 1
  * are exactly the satisfying iterates (the other rows took that step's
  * update).  first_sat may be shared with solves on other streams: a stop that

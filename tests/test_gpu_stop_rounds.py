@@ -106,3 +106,20 @@ def test_an_early_stop_in_the_last_tile_is_cheap():
     one, many = run(1), run(64)
     print(f"1 iteration {one * 1e3:.0f} us, 64 iterations stopped at the first {many * 1e3:.0f} us")
     assert many <= 8 * one
+
+
+def test_no_copies_of_a_large_state():
+    """The handle of a solve does not hold as much memory again as its buffers."""
+    from paper_2411_11833_amd.planner import GpuProblem
+    gp = GpuProblem(_problem(6, 0, 0.0))
+    n = 720000   # 1.01 GiB of copies
+    a, b = _state(gp, n, 11), _state(gp, n, 11)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    gp.optimize(*a[:3], n, 0, 3, _adam(n), cost=a[3], mask=a[4], first_sat=a[5], stop_at_first=True)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+    for t in range(3):
+        gp.optimize(*b[:3], n, t, 1, _adam(n), cost=b[3], mask=b[4], first_sat=b[5], stop_at_first=True)
+    torch.cuda.synchronize()
+    assert all(torch.equal(u, v) for u, v in zip(a, b))
