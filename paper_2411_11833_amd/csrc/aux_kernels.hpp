@@ -256,35 +256,39 @@ __global__ __launch_bounds__(1024) void feas_small_kernel(const Tables* __restri
 // NaN term never is).  Terms as ct_cost writes them.  A workgroup takes 64
 // particles; its 4 waves share the steps (and the terms after them), so a
 // lane waits for one or two steps' loads, all in flight together: 1000
-// particles x 33 terms 9.3 us with one lane per particle, 3.9 now.
+// particles x 33 terms 9.3 us with one lane per particle, 3.9 now.  A launch
+// holds fewer than 2^32 threads, so workgroups walk batches past 2^22 x 64.
 __global__ __launch_bounds__(256) void step_mask_kernel(const Tables* __restrict__ T,
                                                         const float* __restrict__ terms, int64_t n, int64_t ld,
                                                         uint8_t* __restrict__ step_mask, int64_t ld_mask,
                                                         int32_t* __restrict__ count) {
     __shared__ int part[4][64];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-    int total = 0;
-    if (i < n) {
-        for (int k = w; k < T->K; k += 4) {
-            float v[CT_TERMS_PER_STEP];
+    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < n; i0 += (int64_t)gridDim.x * 64) {
+        const int64_t i = i0 + lane;
+        int total = 0;
+        if (i < n) {
+            for (int k = w; k < T->K; k += 4) {
+                float v[CT_TERMS_PER_STEP];
 #pragma unroll
-            for (int j = 0; j < CT_TERMS_PER_STEP; ++j) v[j] = terms[(int64_t)(CT_TERMS_PER_STEP * k + j) * ld + i];
-            int all = 1;
+                for (int j = 0; j < CT_TERMS_PER_STEP; ++j) v[j] = terms[(int64_t)(CT_TERMS_PER_STEP * k + j) * ld + i];
+                int all = 1;
 #pragma unroll
-            for (int j = 0; j < CT_TERMS_PER_STEP; ++j) {
-                const int ok = v[j] <= T->eps[step_term_eps(j)] ? 1 : 0;
-                all &= ok;
-                total += ok;
+                for (int j = 0; j < CT_TERMS_PER_STEP; ++j) {
+                    const int ok = v[j] <= T->eps[step_term_eps(j)] ? 1 : 0;
+                    all &= ok;
+                    total += ok;
+                }
+                if (step_mask) step_mask[(int64_t)k * ld_mask + i] = (uint8_t)all;
             }
-            if (step_mask) step_mask[(int64_t)k * ld_mask + i] = (uint8_t)all;
+            for (int c = CT_TERMS_PER_STEP * T->K + w; c < T->n_constraint; c += 4)
+                total += terms[(int64_t)c * ld + i] <= term_eps(T, c) ? 1 : 0;
         }
-        for (int c = CT_TERMS_PER_STEP * T->K + w; c < T->n_constraint; c += 4)
-            total += terms[(int64_t)c * ld + i] <= term_eps(T, c) ? 1 : 0;
+        part[w][lane] = total;
+        __syncthreads();
+        if (w == 0 && count && i < n) count[i] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+        __syncthreads();
     }
-    part[w][lane] = total;
-    __syncthreads();
-    if (w == 0 && count && i < n) count[i] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
 }
 
 // Indices of the set entries of a mask, in index order (one workgroup of

@@ -576,8 +576,9 @@ extern "C" int ct_step_mask(const ct_problem* P, const float* terms, int64_t n, 
     if (terms && ((uintptr_t)terms % 256)) return CT_ERR_INVALID_ARG;
     if (step_mask && ld_mask < n) return CT_ERR_INVALID_ARG;
     if (n == 0 || (!step_mask && !count)) return CT_OK;
-    hipLaunchKernelGGL(ct::step_mask_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, (hipStream_t)stream,
-                       P->d, terms, n, ld, step_mask, ld_mask, count);
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 63) / 64, int64_t(1) << 22);
+    hipLaunchKernelGGL(ct::step_mask_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, P->d, terms, n, ld,
+                       step_mask, ld_mask, count);
     return err_of(hipGetLastError());
 }
 
