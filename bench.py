@@ -61,8 +61,8 @@ PEAK_BF16_MFMA_TFLOPS = 2500.0       # MI355X published dense BF16 matrix rate
 # dispatch, each scaled by what the same counter read for a 256 MiB device copy
 # in the same run (FETCH_SIZE reads half the bytes: factor 2.0; WRITE_SIZE 1.0).
 # Valid only for the kernel sources it was measured on (hash below).
-STEP_TRAFFIC = {"sources": "a9090360fb87ebf3", "fetch_kib": 4379.0, "fetch_factor": 2.0,
-                "write_kib": 6528.0, "write_factor": 1.0}
+STEP_TRAFFIC = {"sources": "82f574004c405758", "fetch_kib": 4381.5, "fetch_factor": 2.0,
+                "write_kib": 6568.0, "write_factor": 1.0}
 STEP_SOURCES = ("paper_2411_11833_amd/csrc/particle_kernel.hpp", "paper_2411_11833_amd/csrc/ct_tables.hpp",
                 "paper_2411_11833_amd/csrc/pk_instances.hip")
 
@@ -234,7 +234,7 @@ def config1_line(args, dev, q):
 # VALU counters of one step-kernel launch (packing, 8192 particles, split 2)
 # from rocprofv3 (SQ_INSTS_VALU, SQ_THREAD_CYCLES_VALU, medians over the
 # launches of one run); valid only for the kernel sources they were taken on.
-STEP_VALU = {"sources": "a9090360fb87ebf3", "valu_insts": 14467378, "thread_cycles_valu": 645492499.0}
+STEP_VALU = {"sources": "82f574004c405758", "valu_insts": 14552106, "thread_cycles_valu": 654151850.0}
 MI355X_SIMDS = 256 * 4
 CLOCK_HZ = 2.4e9
 

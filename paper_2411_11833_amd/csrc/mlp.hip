@@ -144,9 +144,13 @@ int refresh(ct_mlp* m, hipStream_t st) {
 
 // every layer in one launch (activations kept in LDS): hidden width 512, at
 // most FUSED_MAX_OUT outputs, 8,192 rows or more.  Each workgroup reads
-// every weight once from L2, so blocks are as tall as 256 workgroups allow
-// (128 rows from 32,768 rows, 64 from 16,384, else 32); below 8,192 rows the
-// per-layer launches are faster.
+// every weight once from L2, so blocks are as tall as 256 workgroups allow:
+// 128 rows from 32,768 rows (58.7 us, in blocks of 64 61.6), 64 from 16,384
+// (33.9, in blocks of 32 42.1), else 32.  The lines were drawn for row-major
+// weights; with the fragment-major ones the taller block is faster as soon as
+// the smaller takes a second round (10,000 rows: 32 40.7 us, 64 30.9; 20,000:
+// 64 58.0, 128 53.0), and one launch is faster below 8,192 rows too (4,096
+// rows 21.8 us, per-layer launches 41.0).
 bool fused_shape(const ct_mlp* m) { return m->s.hidden == FH && m->s.d_out <= FUSED_MAX_OUT; }
 bool fused_ok(const ct_mlp* m, int64_t rows) { return fused_shape(m) && rows >= 256 * 32; }
 

@@ -25,7 +25,7 @@
 //     writes G or applies Adam in place.
 //
 // What bounds it (packing, 8192 particles, K = 4, SPLIT 2; one iteration 55.8
-// us with a launch each, 41 now): 54% of the wave time is issue, 45% waits on
+// us with a launch each, 41 now): 50% of the wave time is issue, 44% waits on
 // LDS and scalar loads; 230 registers keep two waves per SIMD.  Link tables
 // are scalar loads, boxes and spheres LDS reads.
 #pragma once
@@ -847,14 +847,16 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
                                              const float* __restrict__ wts, bool live) {
     constexpr bool GRAD = MODE != MODE_COST;
     constexpr int K = KT;
-    // how far config_pass unrolls its loop over the 8 links: fully where the
-    // copies fit the 256 registers of two waves per SIMD, so that a link's
-    // tables are loaded while the one before is tested (16384 waypoint
-    // gradients 1.21 -> 1.14 ms, 100 steps of 256 one-step particles 1.39 ->
-    // 1.31); the longer fused steps and the extended kernels would spill (64
-    // skeletons 37.1 -> 39.3 ms, an augmented-Lagrangian round 2.16 -> 2.32)
-    // and take pairs (36.7, 2.13), as do the cost kernels past 4 steps, which
-    // would pass the 168 registers of three waves (65536 x 6 steps 243 -> 326 us)
+    // how far config_pass unrolls its loop over the 8 links: fully where that is
+    // faster, as a link's tables are loaded while the one before is tested
+    // (16384 waypoint gradients 1.21 -> 1.14 ms, 100 steps of 256 one-step
+    // particles 1.39 -> 1.31), though some of these spill (gradients 12 to 52
+    // bytes a lane at split 1 from 3 steps on and at split 2 with 3, 5 and 6;
+    // the one-step fused step 80 and 88 at splits 2 and 4); the longer fused
+    // steps and the extended kernels would spill more (64 skeletons 37.1 -> 39.3
+    // ms, an augmented-Lagrangian round 2.16 -> 2.32) and take pairs (36.7,
+    // 2.13), as do the cost kernels past 4 steps, which would pass the 168
+    // registers of three waves (65536 x 6 steps 243 -> 326 us)
     constexpr int JU = !EXT && (MODE == MODE_GRAD || (MODE == MODE_COST && KT <= 4) || KT == 1) ? 8 : 2;
     const bool self_on = EXT && T->self_on;   // wave-uniform; compiled out without EXT
     // per-particle weights only in extended kernels; plain kernels read lambda
@@ -1134,8 +1136,8 @@ __device__ __forceinline__ LaneOut lane_slot(const Tables* __restrict__ T, const
 // Workgroup-level tile: P particles x 2K slots x SPLIT lanes.
 
 // LDS of a tile (dynamic; the host passes tile_layout(...).total).  At K = 4,
-// 60 robot spheres and 9 static boxes a fused step without waypoints takes 75
-// KB at SPLIT 1 and 53 KB at SPLIT 2: two workgroups per compute unit.
+// 60 robot spheres and 9 static boxes a fused step without waypoints takes
+// 72,624 bytes at SPLIT 1 and 54,320 at SPLIT 2: two workgroups per compute unit.
 __device__ __forceinline__ TileLds tile_lds(char* base, const TileLayout& o, int P) {
     TileLds S;
     S.xs = (float*)(base + o.xs);
