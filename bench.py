@@ -13,7 +13,7 @@ Also reported on the same JSON line:
   * the roofline position of the fused step kernel: algorithmic flops per
     launch / its average launch time (HIP events on its stream);
   * the waypoint motion cost (16384 particles) and 64 skeletons of uneven
-    length in one persistent launch per iteration vs one launch each;
+    length in one persistent launch per 64 iterations vs one launch each;
   * the plan-skeleton feasibility heuristic H of Eq. (5);
   * the packing step with the robot self-collision constraint switched on;
   * augmented-Lagrangian constraint weights (PHR): the weighted step kernel
@@ -393,7 +393,7 @@ def compositional(args, dev, n, q):
                 "compositional: grasps drawn in the valid grasp box, placements drawn over the centres that "
                 "keep the footprint in the goal region, then each pick-place action's configurations "
                 "optimized alone with its grasp and placement frozen (one-step problems, all actions in one "
-                "persistent launch per iteration); every 50 iterations the actions satisfying Eq. (3) are "
+                "persistent launch per 64 iterations); every 50 iterations the actions satisfying Eq. (3) are "
                 f"composed into whole particles and tested; after {args.sampling_iters} iterations the last "
                 f"composition is refined by the plain optimizer (budget {args.eval_budget}). sampling: the same "
                 f"samplers and {args.sampling_iters} configuration-sampler iterations per round, composed batches "
@@ -795,7 +795,7 @@ def main():
             f"{before:.3f} -> {after:.3f} after {iters} iterations", q)
         sg.close()
 
-    # ---- many skeletons: one persistent launch per iteration vs one per skeleton
+    # ---- many skeletons: one persistent launch per 64 iterations vs one per skeleton
     batch = None
     if not args.no_batch:
         from paper_2411_11833_amd.planner import GpuBatch

@@ -19,7 +19,7 @@ the paper's sampling networks do:
                       changes, so a colliding placement is rejected).
 
 The K one-step problems (object k moved alone, the other objects where they
-start) run together, one persistent many-skeleton launch per iteration.
+start) run together, one persistent many-skeleton launch per 64 iterations.
 Step k of composed particle i takes the i-th (cyclically) one-step particle
 that satisfies every constraint of its action (Eq. 3), or, when none does,
 one-step particle i as it stands: composition with rejection.  The paper's

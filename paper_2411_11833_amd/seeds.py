@@ -157,7 +157,7 @@ def collect(scene_seeds, robot_seed: int = 0, n: int = 1024, iters: int = 1000, 
             make=packing_problem) -> Dataset:
     """Run the plain method (fixed grasps, `iters` Adam steps) on the problem
     `make(seed)` of every scene seed (default: 4-object packing), `group`
-    scenes at a time in one persistent many-skeleton launch per iteration,
+    scenes at a time in one persistent many-skeleton launch per 50 iterations,
     and keep each scene's `keep` best final particles.
 
     Reading: the method's converged particles are its particles at the end of
